@@ -7,11 +7,6 @@
 namespace spb {
 namespace {
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -21,110 +16,74 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ void store_dz(float* p, float v) { *p = v; }
 __device__ __forceinline__ void store_dz(uint16_t* p, float v) { *p = bf16_round(v); }
 
-// One workgroup of WAVES wavefronts per row when classes is large, one wavefront per row otherwise.
-template <typename DZ, int WAVES_PER_ROW>
-__global__ __launch_bounds__(256) void softmax_xent_kernel(const float* __restrict__ logits, int ldz,
-                                                           const int32_t* __restrict__ labels, int rows, int classes,
-                                                           DZ* __restrict__ dz, int lddz, float* __restrict__ row_loss) {
-  constexpr int ROWS_PER_BLOCK = 4 / WAVES_PER_ROW;
-  constexpr int STRIDE = 64 * WAVES_PER_ROW;
-  __shared__ float red[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row = blockIdx.x * ROWS_PER_BLOCK + (WAVES_PER_ROW == 1 ? wave : 0);
-  const bool live = row < rows;                      // uniform per wavefront (per workgroup when WAVES_PER_ROW == 4)
-  const int first = WAVES_PER_ROW == 1 ? lane : (int)threadIdx.x;
-  const float* z = logits + (size_t)(live ? row : 0) * ldz;
-
-  float m = -INFINITY;
-  if (live) for (int c = first; c < classes; c += STRIDE) m = fmaxf(m, z[c]);
-  m = wave_max(m);
-  if (WAVES_PER_ROW > 1) {
-    if (lane == 0) red[wave] = m;
+// Sum or maximum over the LANES threads that share a row, in every one of them.  red: one slot per wave.
+template <int LANES, class Op>
+__device__ __forceinline__ float row_reduce(float v, float* red, Op op) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o, 64));
+  if constexpr (LANES > 64) {
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    v = red[0];
+#pragma unroll
+    for (int w = 1; w < LANES / 64; ++w) v = op(v, red[w]);
     __syncthreads();
   }
-  float s = 0.f;
-  if (live) for (int c = first; c < classes; c += STRIDE) s += expf(z[c] - m);
-  s = wave_sum(s);
-  if (WAVES_PER_ROW > 1) {
-    if (lane == 0) red[wave] = s;
-    __syncthreads();
-    s = (red[0] + red[1]) + (red[2] + red[3]);
-  }
-  if (!live) return;
-  const float lse = m + logf(s);
-  const int y = labels[row];
-  const float inv_rows = 1.f / (float)rows;
-  DZ* out = dz + (size_t)row * lddz;
-  for (int c = first; c < classes; c += STRIDE) {
-    const float p = expf(z[c] - lse);
-    store_dz(out + c, (p - (c == y ? 1.f : 0.f)) * inv_rows);
-  }
-  // a label outside [0, classes) contributes no target term instead of reading out of bounds
-  for (int c = classes + first; c < lddz; c += STRIDE) store_dz(out + c, 0.f);  // keep the pitch padding zero
-  if (first == 0) row_loss[row] = lse - ((unsigned)y < (unsigned)classes ? z[y] : 0.f);
+  return v;
 }
 
-// Long rows (a vocabulary of tens of thousands): one workgroup of 512 threads per row holds the whole row in
-// registers as 16-byte vectors, so the logits are read from memory exactly once, with every load of the row in
-// flight together; the exponentials are kept and only scaled for the gradient.  Columns between `classes` and
-// the pitch count as minus infinity on the way in and come out as zero.
+// One row per LANES threads, the whole row in registers as VECS 16-byte vectors per thread: the logits are read from
+// memory exactly once, with every load of the row in flight together; the exponentials are kept and only scaled for
+// the gradient.  Columns between `classes` and the pitch count as minus infinity on the way in and come out as zero.
+// Bound by HBM (6 bytes per logit with a bfloat16 gradient) for large rows x classes, by latency below.  VECS is the
+// smallest that holds the row, because every vector costs its exponentials whether it holds columns or not
+// (1000 rows of 4999 classes: 27.5 us with room for 32768 columns, 10.2 us with room for 8192).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr int kXentThreads = 512, kXentVecs = 16;   // rows of up to 512 * 16 * 4 = 32768 columns, pitch included
 __device__ __forceinline__ void store_dz4(float* p, const f32x4& v) { *reinterpret_cast<f32x4*>(p) = v; }
 __device__ __forceinline__ void store_dz4(uint16_t* p, const f32x4& v) {
   *reinterpret_cast<uint2*>(p) = make_uint2(bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]));
 }
-template <typename DZ>
-__global__ __launch_bounds__(kXentThreads) void softmax_xent_long_kernel(const float* __restrict__ logits, int ldz,
-                                                                        const int32_t* __restrict__ labels, int rows, int classes,
-                                                                        DZ* __restrict__ dz, int lddz, float* __restrict__ row_loss) {
-  __shared__ float red[kXentThreads / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row = blockIdx.x;
+template <typename DZ, int LANES, int VECS>
+__global__ __launch_bounds__(LANES > 256 ? LANES : 256) void softmax_xent_kernel(const float* __restrict__ logits, int ldz,
+                                                                                const int32_t* __restrict__ labels, int rows, int classes,
+                                                                                DZ* __restrict__ dz, int lddz, float* __restrict__ row_loss) {
+  constexpr int kBlock = LANES > 256 ? LANES : 256, kRows = kBlock / LANES;
+  static_assert(LANES == 64 || kRows == 1, "rows share a workgroup only where a row is one wave");
+  __shared__ float red[kBlock / 64];
+  const int sub = threadIdx.x % LANES;
+  const int row = blockIdx.x * kRows + (int)threadIdx.x / LANES;
+  if (row >= rows) return;                           // whole waves, and only where no barrier follows
   const float* z = logits + (size_t)row * ldz;
-  f32x4 v[kXentVecs];
+  const int y = labels[row];
+  f32x4 v[VECS];
   float m = -INFINITY;
 #pragma unroll
-  for (int i = 0; i < kXentVecs; ++i) {
-    const int c = 4 * ((int)threadIdx.x + kXentThreads * i);
+  for (int i = 0; i < VECS; ++i) {
+    const int c = 4 * (sub + LANES * i);
     v[i] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     if (c + 4 <= ldz) v[i] = *reinterpret_cast<const f32x4*>(z + c);
   }
 #pragma unroll
-  for (int i = 0; i < kXentVecs; ++i) {
-    const int c = 4 * ((int)threadIdx.x + kXentThreads * i);
+  for (int i = 0; i < VECS; ++i) {
+    const int c = 4 * (sub + LANES * i);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       if (c + e >= classes) v[i][e] = -INFINITY;
       m = fmaxf(m, v[i][e]);
     }
   }
-  m = wave_max(m);
-  if (lane == 0) red[wave] = m;
-  __syncthreads();
-  m = red[0];
-#pragma unroll
-  for (int w = 1; w < kXentThreads / 64; ++w) m = fmaxf(m, red[w]);
-  __syncthreads();
+  m = row_reduce<LANES>(m, red, [](float a, float b) { return fmaxf(a, b); });
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < kXentVecs; ++i)
+  for (int i = 0; i < VECS; ++i)
 #pragma unroll
     for (int e = 0; e < 4; ++e) { v[i][e] = expf(v[i][e] - m); s += v[i][e]; }
-  s = wave_sum(s);
-  if (lane == 0) red[wave] = s;
-  __syncthreads();
-  s = red[0];
-#pragma unroll
-  for (int w = 1; w < kXentThreads / 64; ++w) s += red[w];
-  const int y = labels[row];
+  s = row_reduce<LANES>(s, red, [](float a, float b) { return a + b; });
   const float scale = 1.f / (s * (float)rows), inv_rows = 1.f / (float)rows;
   DZ* out = dz + (size_t)row * lddz;
 #pragma unroll
-  for (int i = 0; i < kXentVecs; ++i) {
-    const int c = 4 * ((int)threadIdx.x + kXentThreads * i);
+  for (int i = 0; i < VECS; ++i) {
+    const int c = 4 * (sub + LANES * i);
     if (c + 4 <= lddz) {
       f32x4 g = v[i] * scale;
       // a label outside [0, classes) contributes no target term
@@ -134,7 +93,29 @@ __global__ __launch_bounds__(kXentThreads) void softmax_xent_long_kernel(const f
       store_dz4(out + c, g);
     }
   }
-  if (threadIdx.x == 0) row_loss[row] = m + logf(s) - ((unsigned)y < (unsigned)classes ? z[y] : 0.f);
+  if (sub == 0) row_loss[row] = m + logf(s) - ((unsigned)y < (unsigned)classes ? z[y] : 0.f);
+}
+
+// Rows longer than any of those (or pitches and pointers that are not whole 16-byte pieces): one workgroup per row,
+// three sweeps over it.
+template <typename DZ>
+__global__ __launch_bounds__(256) void softmax_xent_any_kernel(const float* __restrict__ logits, int ldz, const int32_t* __restrict__ labels,
+                                                               int rows, int classes, DZ* __restrict__ dz, int lddz, float* __restrict__ row_loss) {
+  __shared__ float red[4];
+  const int row = blockIdx.x;
+  const float* z = logits + (size_t)row * ldz;
+  float m = -INFINITY;
+  for (int c = threadIdx.x; c < classes; c += 256) m = fmaxf(m, z[c]);
+  m = row_reduce<256>(m, red, [](float a, float b) { return fmaxf(a, b); });
+  float s = 0.f;
+  for (int c = threadIdx.x; c < classes; c += 256) s += expf(z[c] - m);
+  s = row_reduce<256>(s, red, [](float a, float b) { return a + b; });
+  const float lse = m + logf(s), inv_rows = 1.f / (float)rows;
+  const int y = labels[row];
+  DZ* out = dz + (size_t)row * lddz;
+  for (int c = threadIdx.x; c < classes; c += 256) store_dz(out + c, (expf(z[c] - lse) - (c == y ? 1.f : 0.f)) * inv_rows);
+  for (int c = classes + threadIdx.x; c < lddz; c += 256) store_dz(out + c, 0.f);  // keep the pitch padding zero
+  if (threadIdx.x == 0) row_loss[row] = lse - ((unsigned)y < (unsigned)classes ? z[y] : 0.f);
 }
 
 // Adds the per-row losses in a fixed order (same result on every run) and stores the mean.
@@ -148,44 +129,53 @@ __global__ __launch_bounds__(256) void mean_kernel(const float* __restrict__ row
   if (threadIdx.x == 0) out[0] = ((red[0] + red[1]) + (red[2] + red[3])) / (float)rows;
 }
 
-// Few classes and few rows (a perceptron's 10-way head): everything in ONE workgroup and one launch.  A row takes
-// lpr lanes (the power of two that holds its classes), so a wave works on 64 / lpr rows at a time; the mean adds
-// each wave's rows in order and then the four waves in a fixed order.
-template <typename DZ>
-__global__ __launch_bounds__(256) void softmax_xent_one_block_kernel(const float* __restrict__ logits, int ldz,
-                                                                     const int32_t* __restrict__ labels, int rows, int classes, int lpr,
-                                                                     DZ* __restrict__ dz, int lddz, float* __restrict__ row_loss,
-                                                                     float* __restrict__ loss_out) {
-  __shared__ float red[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sub = lane % lpr, rows_per_wave = 64 / lpr;
+// Few classes (a perceptron's 10-way head): a row takes lpr lanes (the power of two that holds its classes), so a
+// wave works on 64 / lpr rows.  ONE_BLOCK: a single workgroup of 1024 threads takes all rows and adds up the mean as
+// well (each wave's rows in order, then the waves in order), which saves the second launch; otherwise a workgroup
+// takes 256 / lpr rows.
+template <typename DZ, bool ONE_BLOCK>
+__global__ __launch_bounds__(ONE_BLOCK ? 1024 : 256) void softmax_xent_few_kernel(const float* __restrict__ logits, int ldz,
+                                                                                 const int32_t* __restrict__ labels, int rows, int classes, int lpr,
+                                                                                 DZ* __restrict__ dz, int lddz, float* __restrict__ row_loss,
+                                                                                 float* __restrict__ loss_out) {
+  constexpr int kThreads = ONE_BLOCK ? 1024 : 256;
+  __shared__ float red[kThreads / 64];
+  const int sub = threadIdx.x % lpr, per_pass = kThreads / lpr;
   const float inv_rows = 1.f / (float)rows;
   float acc = 0.f;
-  for (int base = 0; base < rows; base += 4 * rows_per_wave) {
-    const int row = base + wave * rows_per_wave + lane / lpr;
+  for (int base = blockIdx.x * per_pass; base < rows; base += gridDim.x * per_pass) {
+    const int row = base + (int)threadIdx.x / lpr;
     const bool live = row < rows, mine = live && sub < classes;
     const float z = mine ? logits[(size_t)row * ldz + sub] : -INFINITY;
+    const int y = live ? labels[row] : 0;
     float m = z;
     for (int o = lpr >> 1; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
     float s = mine ? expf(z - m) : 0.f;
     for (int o = lpr >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     if (!live) continue;                       // no shuffles below
     const float lse = m + logf(s);
-    const int y = labels[row];
     DZ* out = dz + (size_t)row * lddz;
     if (mine) store_dz(out + sub, (expf(z - lse) - (sub == y ? 1.f : 0.f)) * inv_rows);
     for (int c = classes + sub; c < lddz; c += lpr) store_dz(out + c, 0.f);  // keep the pitch padding zero
-    if (sub == 0) {
-      // a label outside [0, classes) contributes no target term instead of reading out of bounds
-      const float l = lse - ((unsigned)y < (unsigned)classes ? logits[(size_t)row * ldz + y] : 0.f);
-      row_loss[row] = l;
-      acc += l;
+    // a label outside [0, classes) contributes no target term
+    const bool labelled = (unsigned)y < (unsigned)classes;
+    if (labelled ? sub == y : sub == 0) {
+      const float l = labelled ? lse - z : lse;
+      if constexpr (ONE_BLOCK) acc += l;
+      else row_loss[row] = l;
     }
   }
-  acc = wave_sum(acc);
-  if (lane == 0) red[wave] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) loss_out[0] = ((red[0] + red[1]) + (red[2] + red[3])) * inv_rows;
+  if constexpr (ONE_BLOCK) {
+    acc = wave_sum(acc);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      float t = red[0];
+#pragma unroll
+      for (int w = 1; w < kThreads / 64; ++w) t += red[w];
+      loss_out[0] = t * inv_rows;
+    }
+  }
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* __restrict__ p, size_t words) {
@@ -194,43 +184,48 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* __restrict__ p
 
 }  // namespace
 
+template <typename DZ>
+static void enqueue_softmax_xent(const float* logits, int ldz, const int32_t* labels, int rows, int classes, DZ* dz, int lddz, float* row_loss,
+                                 float* loss_out, hipStream_t stream) {
+  if (classes <= 64) {
+    int lpr = 1;
+    while (lpr < classes) lpr <<= 1;
+    // One workgroup and one launch while that is at most two passes over its 1024 threads: a pass is about 1.3 us of
+    // latency, a second launch 2.4 us (4096 rows of 24 classes in one workgroup: 688 us; over 512 workgroups: 5 us).
+    if ((long long)rows * lpr <= 2048) {
+      hipLaunchKernelGGL((softmax_xent_few_kernel<DZ, true>), dim3(1), dim3(1024), 0, stream, logits, ldz, labels, rows, classes, lpr, dz, lddz, row_loss, loss_out);
+      return;
+    }
+    const int per_block = 256 / lpr;
+    hipLaunchKernelGGL((softmax_xent_few_kernel<DZ, false>), dim3((rows + per_block - 1) / per_block), dim3(256), 0, stream, logits, ldz, labels, rows, classes, lpr,
+                       dz, lddz, row_loss, loss_out);
+  } else {
+    const bool vec_ok = ldz % 4 == 0 && lddz % 4 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15u) == 0 && (reinterpret_cast<uintptr_t>(dz) & 15u) == 0;
+    const int width = ldz > lddz ? ldz : lddz;
+#define SPB_XENT(LANES, VECS)                                                                                                                       \
+  hipLaunchKernelGGL((softmax_xent_kernel<DZ, LANES, VECS>), dim3(LANES == 64 ? (rows + 3) / 4 : rows), dim3(LANES > 256 ? LANES : 256), 0, stream, \
+                     logits, ldz, labels, rows, classes, dz, lddz, row_loss)
+    if (!vec_ok || width > 512 * 16 * 4)
+      hipLaunchKernelGGL((softmax_xent_any_kernel<DZ>), dim3(rows), dim3(256), 0, stream, logits, ldz, labels, rows, classes, dz, lddz, row_loss);
+    else if (width <= 256) SPB_XENT(64, 1);
+    else if (width <= 1024) SPB_XENT(256, 1);
+    else if (width <= 2048) SPB_XENT(256, 2);
+    else if (width <= 4096) SPB_XENT(512, 2);
+    else if (width <= 8192) SPB_XENT(512, 4);
+    else if (width <= 16384) SPB_XENT(512, 8);
+    else SPB_XENT(512, 16);
+#undef SPB_XENT
+  }
+  hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, stream, row_loss, rows, loss_out);
+}
+
 hipError_t launch_softmax_xent(const float* logits, int ldz, const int32_t* labels, int rows, int classes,
                                void* dz, int lddz, DType dz_dtype, float* row_loss, float* loss_out,
                                hipStream_t stream) {
   if (!logits || !labels || !dz || !row_loss || !loss_out || rows <= 0 || classes <= 0 || ldz < classes || lddz < classes)
     return hipErrorInvalidValue;
-  if (classes <= 64 && rows <= 4096) {
-    int lpr = 1;
-    while (lpr < classes) lpr <<= 1;
-    if (dz_dtype == DType::F32)
-      hipLaunchKernelGGL((softmax_xent_one_block_kernel<float>), dim3(1), dim3(256), 0, stream, logits, ldz, labels, rows, classes, lpr, (float*)dz, lddz, row_loss, loss_out);
-    else
-      hipLaunchKernelGGL((softmax_xent_one_block_kernel<uint16_t>), dim3(1), dim3(256), 0, stream, logits, ldz, labels, rows, classes, lpr, (uint16_t*)dz, lddz, row_loss, loss_out);
-    return hipGetLastError();
-  }
-  const bool vec_ok = ldz % 4 == 0 && lddz % 4 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15u) == 0 && (reinterpret_cast<uintptr_t>(dz) & 15u) == 0;
-  if (classes > 2048 && vec_ok && (ldz > lddz ? ldz : lddz) <= kXentThreads * kXentVecs * 4) {
-    if (dz_dtype == DType::F32)
-      hipLaunchKernelGGL((softmax_xent_long_kernel<float>), dim3(rows), dim3(kXentThreads), 0, stream, logits, ldz, labels, rows, classes, (float*)dz, lddz, row_loss);
-    else
-      hipLaunchKernelGGL((softmax_xent_long_kernel<uint16_t>), dim3(rows), dim3(kXentThreads), 0, stream, logits, ldz, labels, rows, classes, (uint16_t*)dz, lddz, row_loss);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, stream, row_loss, rows, loss_out);
-    return hipGetLastError();
-  }
-  const bool wide = classes > 2048;
-  const int grid = wide ? rows : (rows + 3) / 4;
-  if (dz_dtype == DType::F32) {
-    if (wide) hipLaunchKernelGGL((softmax_xent_kernel<float, 4>), dim3(grid), dim3(256), 0, stream, logits, ldz, labels, rows, classes, (float*)dz, lddz, row_loss);
-    else hipLaunchKernelGGL((softmax_xent_kernel<float, 1>), dim3(grid), dim3(256), 0, stream, logits, ldz, labels, rows, classes, (float*)dz, lddz, row_loss);
-  } else {
-    if (wide) hipLaunchKernelGGL((softmax_xent_kernel<uint16_t, 4>), dim3(grid), dim3(256), 0, stream, logits, ldz, labels, rows, classes, (uint16_t*)dz, lddz, row_loss);
-    else hipLaunchKernelGGL((softmax_xent_kernel<uint16_t, 1>), dim3(grid), dim3(256), 0, stream, logits, ldz, labels, rows, classes, (uint16_t*)dz, lddz, row_loss);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, stream, row_loss, rows, loss_out);
+  if (dz_dtype == DType::F32) enqueue_softmax_xent(logits, ldz, labels, rows, classes, static_cast<float*>(dz), lddz, row_loss, loss_out, stream);
+  else enqueue_softmax_xent(logits, ldz, labels, rows, classes, static_cast<uint16_t*>(dz), lddz, row_loss, loss_out, stream);
   return hipGetLastError();
 }
 
