@@ -2,6 +2,7 @@
 #include <cstdlib>
 #include "model.h"
 
+#include <atomic>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -36,28 +37,29 @@ int Model::replay(const char* name, int count, hipStream_t s) {
 }
 
 Model::~Model() {
-  if (side_) (void)hipStreamDestroy(side_);
   if (fork_ev_) (void)hipEventDestroy(fork_ev_);
   if (join_ev_) (void)hipEventDestroy(join_ev_);
   for (auto e : mark_ev_) if (e) (void)hipEventDestroy(e);
 }
 
 void Model::ensure_side_stream(hipStream_t s) {
-  if (side_) return;
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) { (void)hipGetLastError(); return; }
-  hipStream_t q = nullptr;
-  hipEvent_t ev[2 + kMarks] = {};
-  bool ok = hipStreamCreateWithFlags(&q, hipStreamNonBlocking) == hipSuccess;
-  for (int i = 0; ok && i < 2 + kMarks; ++i) ok = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming) == hipSuccess;
-  if (ok) {
-    side_ = q; fork_ev_ = ev[0]; join_ev_ = ev[1];
+  if (!fork_ev_) {
+    static std::atomic<unsigned> models{0};
+    hipEvent_t ev[2 + kMarks] = {};
+    bool ok = true;
+    for (int i = 0; ok && i < 2 + kMarks; ++i) ok = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming) == hipSuccess;
+    if (!ok) {
+      (void)hipGetLastError();
+      for (auto e : ev) if (e) (void)hipEventDestroy(e);
+      return;
+    }
+    turn_ = models++;
+    fork_ev_ = ev[0]; join_ev_ = ev[1];
     for (int i = 0; i < kMarks; ++i) mark_ev_[i] = ev[2 + i];
-    return;
   }
-  (void)hipGetLastError();
-  if (q) (void)hipStreamDestroy(q);
-  for (auto e : ev) if (e) (void)hipEventDestroy(e);
+  if (!forked_) side_ = side_stream_beside(s, turn_);
 }
 
 int Model::mark() {

@@ -70,8 +70,8 @@ class Model {
   std::map<std::string, Product> last_product;  // per kernel class, the most recent product or pair (kept while timing is on)
   int replay(const char* name, int count, hipStream_t s);
 
-  // Creates the side stream (see fork) unless s is being captured into a graph right now; called by the C ABI
-  // before a forward pass, so a model built on a machine without a GPU never touches the runtime.
+  // Picks the side stream (see fork) that goes with s, unless s is being captured into a graph right now; called by the
+  // C ABI before a forward pass, so a model built on a machine without a GPU never touches the runtime.
   void ensure_side_stream(hipStream_t s);
   int finish(hipStream_t s) { return join(s); }   // after a backward pass: s waits for whatever is still on the side stream
 
@@ -94,11 +94,16 @@ class Model {
   int check(hipError_t e, const char* what);
 
  private:
-  hipStream_t side_ = nullptr;
+  hipStream_t side_ = nullptr;   // one of the device's (see streams.hip), not this model's to destroy
+  unsigned turn_ = 0;
   hipEvent_t fork_ev_ = nullptr, join_ev_ = nullptr, mark_ev_[kMarks] = {};
   int next_mark_ = 0;
   bool forked_ = false;
 };
+
+// One of the few streams the library keeps per device, on another hardware queue than s where that is known; models take
+// them in turn.  nullptr if none can be had.  See streams.hip.
+hipStream_t side_stream_beside(hipStream_t s, unsigned turn);
 
 std::unique_ptr<Model> make_mlp(const spb_model_desc& d);
 std::unique_ptr<Model> make_encoder(const spb_model_desc& d);
