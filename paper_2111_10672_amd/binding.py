@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(HERE, "libspb.so")
@@ -61,6 +62,10 @@ class spb_sched_job(C.Structure):
 class spb_sched_task(C.Structure):
     _fields_ = [("job", C.c_int32), ("iteration", C.c_int32), ("worker", C.c_int32), ("machine", C.c_int32),
                 ("moved", C.c_int32), ("start", C.c_double), ("end", C.c_double), ("held_until", C.c_double)]
+
+
+_TASK = struct.Struct("<4i?7x3d")     # spb_sched_task; `moved` is 0 or 1, so its lowest byte says it
+assert _TASK.size == C.sizeof(spb_sched_task)
 
 
 EXPORTS = {
@@ -291,8 +296,9 @@ def spb_schedule_tasks(jobs, n_machines: int, gamma: float = 0.0, capacity: floa
     n, makespan = C.c_int64(), C.c_double()
     _check(lib().spb_schedule_tasks(arr, len(jobs), int(n_machines), float(gamma), float(capacity), int(bool(gang)), out, total,
                                     C.byref(n), C.byref(makespan)))
-    return ([dict(job=t.job, iteration=t.iteration, worker=t.worker, machine=t.machine, start=t.start, end=t.end,
-                  held_until=t.held_until, moved=bool(t.moved)) for t in out[:n.value]], makespan.value)
+    # one record per task, unpacked in C (reading the fields through ctypes took 0.9 us a task, twice the placement itself)
+    return ([{"job": j, "iteration": i, "worker": w, "machine": m, "start": start, "end": end, "held_until": held, "moved": moved}
+             for j, i, w, m, moved, start, end, held in _TASK.iter_unpack(memoryview(out).cast("B")[:n.value * _TASK.size])], makespan.value)
 
 
 class SpbModel:
