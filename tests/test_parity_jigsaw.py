@@ -76,3 +76,22 @@ def test_argument_errors_are_reported():
         with pytest.raises(spb.SpbError) as e:
             spb.spb_schedule_tasks([bad], machines, **kw)
         assert e.value.code == -1 and "spb_schedule_tasks" in str(e.value)
+
+
+@pytest.mark.parametrize("gang", [False, True])
+@pytest.mark.parametrize("jobs,machines,workers", [(3, 1, 1), (70, 70, 2), (6, 130, 65), (9, 4, 4)])
+def test_equal_times_and_many_workers(jobs, machines, workers, gang):
+    """Ties everywhere (equal durations, arrivals and sizes, so tasks meet end to start and intervals join), and more ready
+    tasks than one word of the queue holds."""
+    mix_ = [dict(arrival=float(j % 2), iterations=3, model_size=float(j % 3), durations=[0.5] * workers, resources=[0.5] * workers) for j in range(jobs)]
+    for gamma in (0.0, 0.25):
+        assert spb.spb_schedule_tasks(mix_, machines, gamma=gamma, gang=gang) == jigsaw.schedule(mix_, machines, gamma=gamma, gang=gang)
+
+
+@pytest.mark.parametrize("gang", [False, True])
+def test_durations_below_the_resolution_of_the_times(gang):
+    """1e-18 s next to times around 1e3 s: an end can equal its start, and intervals are not joined."""
+    rng = random.Random(5)
+    jobs = [dict(arrival=rng.choice([0.0, 1e3]), iterations=4, model_size=1.0, durations=[rng.choice([1e-18, 0.5, 2.0]) for _ in range(w)],
+                 resources=[0.5] * w) for w in (1, 2, 3, 1, 2, 3)]
+    assert spb.spb_schedule_tasks(jobs, 3, gamma=0.25, gang=gang) == jigsaw.schedule(jobs, 3, gamma=0.25, gang=gang)
