@@ -59,6 +59,9 @@ DeviceStreams g_devices[kMaxDevices];
 
 void create(DeviceStreams& d) {
   d.tried = true;
+  // (an allocation would otherwise fail, and end the capture, while another thread captures a graph)
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
   bool ok = hipHostMalloc(reinterpret_cast<void**>(&d.result), kProbes * sizeof(int), hipHostMallocDefault) == hipSuccess;
   for (int c = 0; ok && c < kSide; ++c) ok = hipStreamCreateWithFlags(&d.side[c], hipStreamNonBlocking) == hipSuccess;
   if (ok) {
@@ -66,6 +69,7 @@ void create(DeviceStreams& d) {
     for (int c = 0; c < kSide; ++c) hipLaunchKernelGGL(probe_set_kernel, dim3(1), dim3(1), 0, d.side[c], 0, -1);   // a stream's first launch is slow
     ok = hipGetLastError() == hipSuccess;
   }
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
   d.ok = ok;
   if (ok) return;
   (void)hipGetLastError();
