@@ -67,12 +67,10 @@ class EncoderModel : public Model {
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes, 256); return o; };
     const size_t mh = (size_t)M * H * 2, mf = (size_t)M * F * 2, zss = (size_t)Z * S * S;
-    const Attention attn = attention();
-    const size_t row_values = attention_long_row_floats(Z, S) * 4;
     const int cut = num_units - k;  // units >= cut are backpropagated
     auto take_layer = [&]() {
       LayerBuf b;
-      b.u = take(mh); b.stats1 = take((size_t)M * 8); b.qkv = take(3 * mh); b.prob = take(attn == Attention::Long ? row_values : zss * 2); b.ctx = take(mh);
+      b.u = take(mh); b.stats1 = take((size_t)M * 8); b.qkv = take(3 * mh); b.prob = take(zss * 2); b.ctx = take(mh);
       b.h = take(mh); b.stats2 = take((size_t)M * 8); b.v = take(mh); b.z1 = take(mf); b.f = take(mf);
       return b;
     };
@@ -82,7 +80,7 @@ class EncoderModel : public Model {
     p.layer.assign(NL, scratch);
     for (int u = 0; u <= NL; ++u) p.xout[u] = (u + 1 >= cut) ? take(mh) : ping[u & 1];  // kept if the unit above reads it in its backward pass
     for (int i = 0; i < NL; ++i) if (i + 1 >= cut) p.layer[i] = take_layer();
-    p.scores = take(attn == Attention::Products ? zss * 4 : 0);
+    p.scores = take(zss * 4);
     p.y = take((size_t)R * H * 2); p.statsf = take((size_t)R * 8); p.logits = take((size_t)R * ldz() * 4);
     p.row_loss = take((size_t)R * 4); p.dlogits = take((size_t)R * ldv() * 2);
     p.dy = p.partial = p.partial_bytes = p.dx[0] = p.dx[1] = p.dF[0] = p.dF[1] = p.dv = p.dh[0] = p.dh[1] = p.dctx = p.dscore = p.dqkv[0] = p.dqkv[1] = p.du = 0;
@@ -95,18 +93,10 @@ class EncoderModel : public Model {
     if (k >= 2) {
       // dF, dh and dqkv are read by weight gradients on the second stream: two of each, used by alternate layers
       p.dx[0] = take(mh); p.dx[1] = take(mh); p.dF[0] = take(mf); p.dF[1] = take(mf); p.dv = take(mh); p.dh[0] = take(mh); p.dh[1] = take(mh);
-      p.dctx = take(mh); p.dscore = take(attn == Attention::Long ? row_values : attn == Attention::Products ? zss * 2 : 0); p.dqkv[0] = take(3 * mh); p.dqkv[1] = take(3 * mh); p.du = take(mh);
+      p.dctx = take(mh); p.dscore = take(zss * 2); p.dqkv[0] = take(3 * mh); p.dqkv[1] = take(3 * mh); p.du = take(mh);
     }
     p.total = off;
     return p;
-  }
-
-  enum class Attention { Short, Long, Products };
-  // One kernel that keeps P where the sequence fits a workgroup; beyond that the kernels that form P again; other head
-  // sizes as separate products and softmax passes.
-  Attention attention() const {
-    if (attention_fused_accepts(S, D, 3 * H, H)) return Attention::Short;
-    return attention_long_accepts(S, D, 3 * H, H) ? Attention::Long : Attention::Products;
   }
 
   size_t workspace_size(int k) const override { return plan(k).total; }
@@ -157,15 +147,11 @@ class EncoderModel : public Model {
       if (int rc = run("layernorm_fwd", 2 * mh, s, [&] {
             return launch_layernorm_fwd(xin, H, nullptr, M, H, P(LN1W), P(LN1B), w + b.u, H, reinterpret_cast<float*>(w + b.stats1), s); })) return rc;
       if (int rc = gemm(linear(w + b.u, H, M, P(QKVW), 3 * H, H, P(QKVB), w + b.qkv, 3 * H), s)) return rc;
-      if (attention() == Attention::Short) {
+      if (attention_fused_accepts(S, D, 3 * H, H)) {
         // one kernel per layer; P is written only where the backward pass will read it
         void* keep_prob = (i + 1 >= num_units - k) ? w + b.prob : nullptr;
         if (int rc = run("attention_fwd", (double)M * H * 2 * 4 + (keep_prob ? (double)Z * S * S * 2 : 0.0), s, [&] {
               return launch_attention_fwd(w + b.qkv, 3 * H, keep_prob, w + b.ctx, H, B, NH, S, D, inv_sqrt_d, s); })) return rc;
-      } else if (attention() == Attention::Long) {
-        float* keep_lse = (i + 1 >= num_units - k) ? reinterpret_cast<float*>(w + b.prob) : nullptr;
-        if (int rc = run("attention_fwd", (double)M * H * 2 * 4 + (keep_lse ? (double)Z * S * 4 : 0.0), s, [&] {
-              return launch_attention_long_fwd(w + b.qkv, 3 * H, keep_lse, w + b.ctx, H, B, NH, S, D, inv_sqrt_d, s); })) return rc;
       } else {
       {
         GemmProblem g;  // scores[z, s, s'] = Q[s, :] . K[s', :] / sqrt(d)
@@ -313,13 +299,9 @@ class EncoderModel : public Model {
         if (int rc = gemm(g, s)) return rc;
       }
       const char* qbase = w + b.qkv;
-      if (attention() == Attention::Short) {
+      if (attention_fused_accepts(S, D, 3 * H, H)) {
         if (int rc = run("attention_bwd", (double)M * H * 2 * 7 + (double)Z * S * S * 2, s, [&] {
               return launch_attention_bwd(qbase, 3 * H, w + b.prob, w + p.dctx, H, dqkv, B, NH, S, D, inv_sqrt_d, s); })) return rc;
-      } else if (attention() == Attention::Long) {
-        if (int rc = run("attention_bwd", (double)M * H * 2 * 8 + (double)Z * S * 4, s, [&] {
-              return launch_attention_long_bwd(qbase, 3 * H, reinterpret_cast<const float*>(w + b.prob), w + b.ctx, w + p.dctx, H, dqkv,
-                                               reinterpret_cast<float*>(w + p.dscore), B, NH, S, D, inv_sqrt_d, s); })) return rc;
       } else {
       {
         GemmProblem g;  // dP[s, s'] = dctx[s, :] . V[s', :]

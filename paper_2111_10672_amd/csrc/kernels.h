@@ -230,16 +230,6 @@ hipError_t launch_attention_fwd(const void* qkv, int ld_qkv, void* prob, void* c
 hipError_t launch_attention_bwd(const void* qkv, int ld_qkv, const void* prob, const void* dctx, int ld_ctx, void* dqkv, int batch,
                                 int heads, int seq, int head_dim, float scale, hipStream_t stream);
 
-// The same attention at any sequence length (attention_long.hip), heads of 64 features, without prob: the forward pass
-// writes lse (float32, optional) and the backward pass forms the probabilities again from it.  lse and dsum (scratch of the
-// backward pass) hold attention_long_row_floats(batch * heads, seq) floats.
-bool attention_long_accepts(int seq, int head_dim, int ld_qkv, int ld_ctx);
-size_t attention_long_row_floats(int heads_total, int seq);
-hipError_t launch_attention_long_fwd(const void* qkv, int ld_qkv, float* lse, void* ctx, int ld_ctx, int batch, int heads, int seq,
-                                     int head_dim, float scale, hipStream_t stream);
-hipError_t launch_attention_long_bwd(const void* qkv, int ld_qkv, const float* lse, const void* ctx, const void* dctx, int ld_ctx, void* dqkv,
-                                     float* dsum, int batch, int heads, int seq, int head_dim, float scale, hipStream_t stream);
-
 // Server-side aggregation and update (aggregate.hip): for each tensor, g = mean of `count` float32 worker
 // gradients (added in the order given), v = momentum * v + g + weight_decay * w, w = w - rate * v.  w is in
 // param_dtype (bfloat16 parameters are rounded to nearest-even after the float32 update), v is float32.
