@@ -16,74 +16,110 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ void store_dz(float* p, float v) { *p = v; }
 __device__ __forceinline__ void store_dz(uint16_t* p, float v) { *p = bf16_round(v); }
 
-// Sum or maximum over the LANES threads that share a row, in every one of them.  red: one slot per wave.
-template <int LANES, class Op>
-__device__ __forceinline__ float row_reduce(float v, float* red, Op op) {
+__device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o, 64));
-  if constexpr (LANES > 64) {
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    v = red[0];
-#pragma unroll
-    for (int w = 1; w < LANES / 64; ++w) v = op(v, red[w]);
-    __syncthreads();
-  }
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
 }
 
-// One row per LANES threads, the whole row in registers as VECS 16-byte vectors per thread: the logits are read from
-// memory exactly once, with every load of the row in flight together; the exponentials are kept and only scaled for
-// the gradient.  Columns between `classes` and the pitch count as minus infinity on the way in and come out as zero.
-// Bound by HBM (6 bytes per logit with a bfloat16 gradient) for large rows x classes, by latency below.  VECS is the
-// smallest that holds the row, because every vector costs its exponentials whether it holds columns or not
-// (1000 rows of 4999 classes: 27.5 us with room for 32768 columns, 10.2 us with room for 8192).
+// 65 to 2048 classes: one row per wave, the row in registers as VALS floats per lane (column = lane + 64 i), read once
+// with every load in flight.  A lane adds its exponentials in the order of i, the lanes are added as a tree, and the
+// gradient is exp(z - lse): the bits do not depend on VALS, and another order of the sum shows in where a bfloat16
+// gradient rounds.  Bound by latency (256 rows of 100 classes: a wave on each CU).
+template <typename DZ, int VALS>
+__global__ __launch_bounds__(256) void softmax_xent_wave_kernel(const float* __restrict__ logits, int ldz, const int32_t* __restrict__ labels,
+                                                                int rows, int classes, DZ* __restrict__ dz, int lddz,
+                                                                float* __restrict__ row_loss) {
+  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + ((int)threadIdx.x >> 6);
+  if (row >= rows) return;                           // whole waves, no barrier follows
+  const float* z = logits + (size_t)row * ldz;
+  const int y = labels[row];
+  float v[VALS], m = -INFINITY, s = 0.f;
+#pragma unroll
+  for (int i = 0; i < VALS; ++i) {
+    v[i] = -INFINITY;
+    if (lane + 64 * i < classes) v[i] = z[lane + 64 * i];
+  }
+#pragma unroll
+  for (int i = 0; i < VALS; ++i) m = fmaxf(m, v[i]);
+  m = wave_max(m);
+#pragma unroll
+  for (int i = 0; i < VALS; ++i)
+    if (lane + 64 * i < classes) s += expf(v[i] - m);
+  s = wave_sum(s);
+  const float lse = m + logf(s), inv_rows = 1.f / (float)rows;
+  DZ* out = dz + (size_t)row * lddz;
+#pragma unroll
+  for (int i = 0; i < VALS; ++i) {
+    const int c = lane + 64 * i;
+    if (c < classes) store_dz(out + c, (expf(v[i] - lse) - (c == y ? 1.f : 0.f)) * inv_rows);
+  }
+  for (int c = classes + lane; c < lddz; c += 64) store_dz(out + c, 0.f);  // keep the pitch padding zero
+  // a label outside [0, classes) contributes no target term instead of reading out of bounds
+  if (lane == 0) row_loss[row] = lse - ((unsigned)y < (unsigned)classes ? z[y] : 0.f);
+}
+
+// Longer rows: one workgroup of 512 threads per row, the whole row in registers as VECS 16-byte vectors per thread: the
+// logits are read from memory exactly once, with every load of the row in flight together; the exponentials are kept and
+// only scaled for the gradient.  Columns between `classes` and the pitch count as minus infinity on the way in and come
+// out as zero.  Bound by HBM (6 bytes per logit with a bfloat16 gradient) for large rows x classes, by latency below.
+// VECS is the smallest that holds the row, because every vector costs its exponentials whether it holds columns or not
+// (1000 rows of 4999 classes: 27.5 us with room for 32768 columns, 10.2 us with room for 8192; same bits).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kXentThreads = 512;
 __device__ __forceinline__ void store_dz4(float* p, const f32x4& v) { *reinterpret_cast<f32x4*>(p) = v; }
 __device__ __forceinline__ void store_dz4(uint16_t* p, const f32x4& v) {
   *reinterpret_cast<uint2*>(p) = make_uint2(bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]));
 }
-template <typename DZ, int LANES, int VECS>
-__global__ __launch_bounds__(LANES > 256 ? LANES : 256) void softmax_xent_kernel(const float* __restrict__ logits, int ldz,
-                                                                                const int32_t* __restrict__ labels, int rows, int classes,
-                                                                                DZ* __restrict__ dz, int lddz, float* __restrict__ row_loss) {
-  constexpr int kBlock = LANES > 256 ? LANES : 256, kRows = kBlock / LANES;
-  static_assert(LANES == 64 || kRows == 1, "rows share a workgroup only where a row is one wave");
-  __shared__ float red[kBlock / 64];
-  const int sub = threadIdx.x % LANES;
-  const int row = blockIdx.x * kRows + (int)threadIdx.x / LANES;
-  if (row >= rows) return;                           // whole waves, and only where no barrier follows
+template <typename DZ, int VECS>
+__global__ __launch_bounds__(kXentThreads) void softmax_xent_kernel(const float* __restrict__ logits, int ldz, const int32_t* __restrict__ labels,
+                                                                   int rows, int classes, DZ* __restrict__ dz, int lddz,
+                                                                   float* __restrict__ row_loss) {
+  __shared__ float red[kXentThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = blockIdx.x;
   const float* z = logits + (size_t)row * ldz;
   const int y = labels[row];
   f32x4 v[VECS];
   float m = -INFINITY;
 #pragma unroll
   for (int i = 0; i < VECS; ++i) {
-    const int c = 4 * (sub + LANES * i);
+    const int c = 4 * ((int)threadIdx.x + kXentThreads * i);
     v[i] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     if (c + 4 <= ldz) v[i] = *reinterpret_cast<const f32x4*>(z + c);
   }
 #pragma unroll
   for (int i = 0; i < VECS; ++i) {
-    const int c = 4 * (sub + LANES * i);
+    const int c = 4 * ((int)threadIdx.x + kXentThreads * i);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       if (c + e >= classes) v[i][e] = -INFINITY;
       m = fmaxf(m, v[i][e]);
     }
   }
-  m = row_reduce<LANES>(m, red, [](float a, float b) { return fmaxf(a, b); });
+  m = wave_max(m);
+  if (lane == 0) red[wave] = m;
+  __syncthreads();
+  m = red[0];
+#pragma unroll
+  for (int w = 1; w < kXentThreads / 64; ++w) m = fmaxf(m, red[w]);
+  __syncthreads();
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < VECS; ++i)
 #pragma unroll
     for (int e = 0; e < 4; ++e) { v[i][e] = expf(v[i][e] - m); s += v[i][e]; }
-  s = row_reduce<LANES>(s, red, [](float a, float b) { return a + b; });
+  s = wave_sum(s);
+  if (lane == 0) red[wave] = s;
+  __syncthreads();
+  s = red[0];
+#pragma unroll
+  for (int w = 1; w < kXentThreads / 64; ++w) s += red[w];
   const float scale = 1.f / (s * (float)rows), inv_rows = 1.f / (float)rows;
   DZ* out = dz + (size_t)row * lddz;
 #pragma unroll
   for (int i = 0; i < VECS; ++i) {
-    const int c = 4 * (sub + LANES * i);
+    const int c = 4 * ((int)threadIdx.x + kXentThreads * i);
     if (c + 4 <= lddz) {
       f32x4 g = v[i] * scale;
       // a label outside [0, classes) contributes no target term
@@ -93,7 +129,7 @@ __global__ __launch_bounds__(LANES > 256 ? LANES : 256) void softmax_xent_kernel
       store_dz4(out + c, g);
     }
   }
-  if (sub == 0) row_loss[row] = m + logf(s) - ((unsigned)y < (unsigned)classes ? z[y] : 0.f);
+  if (threadIdx.x == 0) row_loss[row] = m + logf(s) - ((unsigned)y < (unsigned)classes ? z[y] : 0.f);
 }
 
 // Rows longer than any of those (or pitches and pointers that are not whole 16-byte pieces): one workgroup per row,
@@ -102,14 +138,22 @@ template <typename DZ>
 __global__ __launch_bounds__(256) void softmax_xent_any_kernel(const float* __restrict__ logits, int ldz, const int32_t* __restrict__ labels,
                                                                int rows, int classes, DZ* __restrict__ dz, int lddz, float* __restrict__ row_loss) {
   __shared__ float red[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = blockIdx.x;
   const float* z = logits + (size_t)row * ldz;
   float m = -INFINITY;
   for (int c = threadIdx.x; c < classes; c += 256) m = fmaxf(m, z[c]);
-  m = row_reduce<256>(m, red, [](float a, float b) { return fmaxf(a, b); });
+  m = wave_max(m);
+  if (lane == 0) red[wave] = m;
+  __syncthreads();
+  m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  __syncthreads();
   float s = 0.f;
   for (int c = threadIdx.x; c < classes; c += 256) s += expf(z[c] - m);
-  s = row_reduce<256>(s, red, [](float a, float b) { return a + b; });
+  s = wave_sum(s);
+  if (lane == 0) red[wave] = s;
+  __syncthreads();
+  s = (red[0] + red[1]) + (red[2] + red[3]);
   const float lse = m + logf(s), inv_rows = 1.f / (float)rows;
   const int y = labels[row];
   DZ* out = dz + (size_t)row * lddz;
@@ -199,21 +243,28 @@ static void enqueue_softmax_xent(const float* logits, int ldz, const int32_t* la
     const int per_block = 256 / lpr;
     hipLaunchKernelGGL((softmax_xent_few_kernel<DZ, false>), dim3((rows + per_block - 1) / per_block), dim3(256), 0, stream, logits, ldz, labels, rows, classes, lpr,
                        dz, lddz, row_loss, loss_out);
+  } else if (classes <= 2048) {
+#define SPB_XENT(VALS)                                                                                                                           \
+  hipLaunchKernelGGL((softmax_xent_wave_kernel<DZ, VALS>), dim3((rows + 3) / 4), dim3(256), 0, stream, logits, ldz, labels, rows, classes, dz, \
+                     lddz, row_loss)
+    if (classes <= 128) SPB_XENT(2);
+    else if (classes <= 256) SPB_XENT(4);
+    else if (classes <= 512) SPB_XENT(8);
+    else if (classes <= 1024) SPB_XENT(16);
+    else SPB_XENT(32);
+#undef SPB_XENT
   } else {
     const bool vec_ok = ldz % 4 == 0 && lddz % 4 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15u) == 0 && (reinterpret_cast<uintptr_t>(dz) & 15u) == 0;
     const int width = ldz > lddz ? ldz : lddz;
-#define SPB_XENT(LANES, VECS)                                                                                                                       \
-  hipLaunchKernelGGL((softmax_xent_kernel<DZ, LANES, VECS>), dim3(LANES == 64 ? (rows + 3) / 4 : rows), dim3(LANES > 256 ? LANES : 256), 0, stream, \
-                     logits, ldz, labels, rows, classes, dz, lddz, row_loss)
-    if (!vec_ok || width > 512 * 16 * 4)
+#define SPB_XENT(VECS)                                                                                                                          \
+  hipLaunchKernelGGL((softmax_xent_kernel<DZ, VECS>), dim3(rows), dim3(kXentThreads), 0, stream, logits, ldz, labels, rows, classes, dz, lddz, \
+                     row_loss)
+    if (!vec_ok || width > kXentThreads * 16 * 4)
       hipLaunchKernelGGL((softmax_xent_any_kernel<DZ>), dim3(rows), dim3(256), 0, stream, logits, ldz, labels, rows, classes, dz, lddz, row_loss);
-    else if (width <= 256) SPB_XENT(64, 1);
-    else if (width <= 1024) SPB_XENT(256, 1);
-    else if (width <= 2048) SPB_XENT(256, 2);
-    else if (width <= 4096) SPB_XENT(512, 2);
-    else if (width <= 8192) SPB_XENT(512, 4);
-    else if (width <= 16384) SPB_XENT(512, 8);
-    else SPB_XENT(512, 16);
+    else if (width <= kXentThreads * 2 * 4) SPB_XENT(2);
+    else if (width <= kXentThreads * 4 * 4) SPB_XENT(4);
+    else if (width <= kXentThreads * 8 * 4) SPB_XENT(8);
+    else SPB_XENT(16);
 #undef SPB_XENT
   }
   hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, stream, row_loss, rows, loss_out);
