@@ -153,10 +153,11 @@ spb_sched_task* place_tasks(const spb_sched_job* jobs, int n_jobs, int n_machine
     int& prev = last[first[j] + w];
     // Earlier start wins; at the same start the previous device, then the lower index.  So the previous device is asked
     // first; the others start no sooner than `moved_ready`, and one of them has to be strictly earlier than the best so far.
+    // Without a previous device the first one always counts: an infinite or undefined time is earlier than nothing.
     const double release = prog[j].release, moved_ready = release + gamma * q.model_size;
     int best_m = prev;
     double best_start = prev >= 0 ? dev[prev].earliest(release, d) : std::numeric_limits<double>::infinity();
-    for (int m = 0; m < n_machines && best_start > moved_ready; ++m) {
+    for (int m = 0; m < n_machines && (best_m < 0 || best_start > moved_ready); ++m) {
       if (m == prev) continue;
       const double start = dev[m].earliest(moved_ready, d, best_start);
       if (start < best_start || best_m < 0) { best_m = m; best_start = start; }
@@ -164,7 +165,7 @@ spb_sched_task* place_tasks(const spb_sched_job* jobs, int n_jobs, int n_machine
     spb_sched_task& t = *out++;
     t.job = j; t.iteration = prog[j].iteration; t.worker = w; t.machine = best_m; t.moved = (prev >= 0 && best_m != prev) ? 1 : 0;
     t.start = best_start; t.end = best_start + d; t.held_until = t.end;
-    dev[best_m].take(t.start, t.end);
+    if (!std::isnan(t.start)) dev[best_m].take(t.start, t.end);   // (no time lies inside an interval that is not a number)
     prev = best_m;
     prog[j].latest_end = prog[j].pending == q.workers ? t.end : std::max(prog[j].latest_end, t.end);
     if (--prog[j].pending == 0 && prog[j].iteration + 1 < q.iterations) release_iteration(j, prog[j].iteration + 1, prog[j].latest_end);

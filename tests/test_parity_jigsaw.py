@@ -95,3 +95,26 @@ def test_durations_below_the_resolution_of_the_times(gang):
     jobs = [dict(arrival=rng.choice([0.0, 1e3]), iterations=4, model_size=1.0, durations=[rng.choice([1e-18, 0.5, 2.0]) for _ in range(w)],
                  resources=[0.5] * w) for w in (1, 2, 3, 1, 2, 3)]
     assert spb.spb_schedule_tasks(jobs, 3, gamma=0.25, gang=gang) == jigsaw.schedule(jobs, 3, gamma=0.25, gang=gang)
+
+
+INF = float("inf")
+
+
+def no_nan(placed):
+    """The same placements with None in the place of every time that is not a number (which equals nothing)."""
+    return [{k: None if v != v else v for k, v in t.items()} for t in placed]
+
+
+@pytest.mark.parametrize("arrival,size,gamma", [(INF, 1.0, 0.25), (INF, 0.0, 0.0), (1.0, INF, 0.25), (1.0, 1.0, INF), (1.0, 1e300, 1e10), (1e308, 1e308, 1.0),
+                                                (1.0, 0.0, INF), (1.0, INF, 0.0)])
+def test_tasks_at_times_that_are_not_finite(arrival, size, gamma):
+    """Infinite inputs, products that overflow and infinity times zero are all in the ranges the call accepts, and next to
+    them other jobs are placed as always."""
+    odd = dict(arrival=arrival, iterations=3, model_size=size, durations=[0.5, 1.0, 0.75], resources=[1.0, 0.5, 0.25])
+    ok = dict(odd, arrival=0.5, model_size=1.0)
+    for jobs in ([odd], [ok, odd, ok], [odd, dict(ok, resources=[0.1, 0.1, 0.1])]):
+        for machines in (1, 2, 4):
+            want, _ = jigsaw.schedule(jobs, machines, gamma=gamma)
+            got, makespan = spb.spb_schedule_tasks(jobs, machines, gamma=gamma)
+            assert no_nan(got) == no_nan(want)
+            assert makespan == max([t["end"] for t in want if t["end"] == t["end"]], default=0.0)
