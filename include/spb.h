@@ -280,6 +280,9 @@ int spb_replay_kernel(spb_model* m, const char* name, int32_t count, void* strea
  * devices, at the earliest time at which that many are free for the slowest worker's duration, and hold them
  * that long; a worker keeps its previous device when that one is free then, the others take the free devices of
  * lowest index and need the start-up delay; iterations are ordered by (sum of resources) * (slowest duration).
+ * Times may be infinite (an infinite arrival, model size or gamma, or a sum or product that overflows).  Infinity times
+ * zero is no number: the tasks of such a job get starts that are not numbers, on the device of lowest index, and take up
+ * no time there; a gang of such a job needs no start-up delay.
  * (The paper normalises resource and duration by cluster constants, which does not change the order; what it
  * leaves open - the tie rules, exclusive devices, the first iteration's delay - is as stated here.) */
 typedef struct spb_sched_job {

@@ -196,7 +196,9 @@ spb_sched_task* place_gangs(const spb_sched_job* jobs, int n_jobs, int n_machine
     ready.erase(ready.begin());
     const int j = std::get<1>(k), i = std::get<2>(k);
     const spb_sched_job& q = jobs[j];
-    const double rel = release[j], moved_ready = rel + gamma * q.model_size, hold = slowest[j];
+    const double rel = release[j], hold = slowest[j];
+    // (infinity times zero: nothing is known to be moved, and no start is too early for it)
+    const double delay = gamma * q.model_size, moved_ready = std::isnan(delay) ? rel : rel + delay;
     // A gang starts at the earliest time at which all previous devices are free for `hold`, or - not before the model
     // can have moved - at which as many devices as it has workers are.  Both are found by jumps: from a time t, no start
     // lies before the latest (the workers-th) of the devices' own next gaps, and when that is t itself, it is the start.

@@ -118,3 +118,24 @@ def test_tasks_at_times_that_are_not_finite(arrival, size, gamma):
             got, makespan = spb.spb_schedule_tasks(jobs, machines, gamma=gamma)
             assert no_nan(got) == no_nan(want)
             assert makespan == max([t["end"] for t in want if t["end"] == t["end"]], default=0.0)
+
+
+@pytest.mark.parametrize("arrival,size,gamma", [(INF, 1.0, 0.25), (INF, 0.0, 0.0), (1.0, INF, 0.25), (1.0, 1.0, INF), (1.0, 1e300, 1e10), (1e308, 1e308, 1.0)])
+def test_gangs_at_times_that_are_not_finite(arrival, size, gamma):
+    odd = dict(arrival=arrival, iterations=3, model_size=size, durations=[0.5, 1.0], resources=[1.0, 0.5])
+    ok = dict(odd, arrival=0.5, model_size=1.0)
+    for jobs in ([odd], [ok, odd, ok], [odd, dict(ok, resources=[0.1, 0.1])]):
+        for machines in (2, 3, 5):
+            assert spb.spb_schedule_tasks(jobs, machines, gamma=gamma, gang=True) == jigsaw.schedule(jobs, machines, gamma=gamma, gang=True)
+
+
+@pytest.mark.timeout(60)
+@pytest.mark.parametrize("size,gamma,others", [(0.0, INF, INF), (INF, 0.0, 0.0)])
+def test_gangs_with_a_delay_that_is_not_a_number(size, gamma, others):
+    """Infinity times zero: the plan ends, and is the one without a delay for these jobs.  `others`: the delay per size
+    of the jobs beside them."""
+    odd = dict(arrival=1.0, iterations=3, model_size=size, durations=[0.5, 1.0], resources=[1.0, 0.5])
+    for jobs in ([odd], [odd] * 3, [dict(odd, model_size=1.0, resources=[0.1, 0.1]), odd, odd]):
+        for machines in (2, 3, 5):
+            plain = [dict(j, model_size=0.0 if j is odd else others) for j in jobs]
+            assert spb.spb_schedule_tasks(jobs, machines, gamma=gamma, gang=True) == jigsaw.schedule(plain, machines, gamma=1.0, gang=True)
