@@ -25,8 +25,8 @@
  *   - Work is enqueued on the caller's stream (a hipStream_t passed as void*);
  *     calls return without waiting for the device and may be captured into a
  *     HIP graph.  Calls on one model must not overlap in time.
- *   - The library keeps four more HIP streams per GPU (no device memory), created
- *     by the first spb_forward outside a graph capture, and a model a few events,
+ *   - For residual CNNs and encoders the library keeps four more HIP streams per GPU
+ *     (no device memory), created by the first spb_forward outside a graph capture, and a model a few events,
  *     released by spb_model_destroy.  spb_backward_truncated runs weight-gradient
  *     kernels on one of those streams beside the input-gradient chain; it first
  *     makes that stream wait for the caller's and, before it returns, makes the

@@ -298,7 +298,7 @@ int spb_forward(spb_model* m, const void* x, const int32_t* labels, const int32_
   const size_t need = m->impl->workspace_size(k);
   SPB_REQUIRE(workspace && workspace_bytes >= need, SPB_ERR_WORKSPACE, "spb_forward: workspace of %zu bytes, depth %d needs %zu", workspace_bytes, k, need);
   SPB_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & 255u) == 0, SPB_ERR_WORKSPACE, "spb_forward: workspace is not 256-byte aligned");
-  m->impl->ensure_side_stream(static_cast<hipStream_t>(stream));
+  if (m->impl->forks) m->impl->ensure_side_stream(static_cast<hipStream_t>(stream));
   int rc = m->impl->forward(x, labels, loss_rows, k, workspace, loss_out, static_cast<hipStream_t>(stream));
   if (rc != SPB_OK) return rc;
   m->impl->stashed_k = k;

@@ -17,6 +17,7 @@ class MlpModel : public Model {
     dims_.assign(d.dims, d.dims + d.n_dims);
     num_units = d.n_dims - 1;
     per_ = dtype == DType::F32 ? 4 : 8;
+    forks = false;
     for (int u = 0; u < num_units; ++u) {
       ParamInfo w, b;
       w.name = "fc" + std::to_string(u) + ".weight"; w.unit = u; w.dtype = dtype; w.shape = {dims_[u + 1], dims_[u]};

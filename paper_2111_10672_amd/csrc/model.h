@@ -63,6 +63,7 @@ class Model {
   std::vector<void*> param_ptrs, grad_ptrs;
   bool params_bound = false, grads_bound = false;
   bool needs_loss_rows = false;
+  bool forks = true;   // whether a backward pass puts work on the side stream; a model that never does is not given one
   int stashed_k = -1;  // depth the last forward pass stashed for; -1 = no forward yet
   void* ws = nullptr;
   KernelTimer timer;

@@ -1,0 +1,76 @@
+"""The host side of the two-stream backward pass, without a GPU: libspb.so runs on a stand-in for the HIP runtime
+(fake_hip.cpp) that writes down every call and keeps streams on queues.  Each test is a short program of its own process."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = """
+import ctypes as C, re, sys
+sys.path.insert(0, {root!r})
+hip = C.CDLL("libamdhip64.so.7", mode=C.RTLD_GLOBAL)
+hip.fake_stream.restype, hip.fake_log.restype = C.c_void_p, C.c_char_p
+hip.fake_id.argtypes, hip.fake_capture.argtypes = [C.c_void_p], [C.c_void_p, C.c_int]
+hip.fake_busy.argtypes, hip.fake_pass.argtypes = [C.c_int, C.c_double], [C.c_double]
+import paper_2111_10672_amd as spb
+
+MLP = dict(family="mlp", dtype="bf16", batch=64, dims=[64, 128, 64, 10])
+ENCODER = dict(family="encoder", dtype="bf16", batch=2, seq=128, layers=2, hidden=128, heads=2, ffn=256, vocab=97, loss_rows=31)
+
+class Model:
+    def __init__(self, cfg):
+        self.h = spb.spb_model_create(spb.desc_from_config(cfg))
+        self.k = spb.spb_num_units(self.h)
+        n = spb.spb_param_count(self.h)
+        spb.spb_bind_params(self.h, [4096] * n)       # (addresses that nothing reads)
+        spb.spb_bind_grads(self.h, [4096] * n)
+    def forward(self, stream=None):
+        spb.spb_forward(self.h, 4096, 4096, 4096, self.k, 4096, 1 << 40, 4096, stream)
+    def step(self, stream=None):
+        '''The step's log, and the streams (by number) that kernels of its backward pass ran on.'''
+        hip.fake_clear()
+        self.forward(stream)
+        at = len(log())
+        spb.spb_backward_truncated(self.h, self.k, stream)
+        return log(), {{int(l.split()[-1]) for l in log()[at:] if l.startswith("launch")}}
+    def close(self):
+        spb.spb_model_destroy(self.h)
+
+def log():
+    return hip.fake_log().decode().splitlines()
+def stream(queue):
+    return hip.fake_stream(queue)
+"""
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    out = tmp_path_factory.mktemp("fake_hip")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-Wl,-soname,libamdhip64.so.7", os.path.join(HERE, "fake_hip.cpp"),
+                    "-o", str(out / "libamdhip64.so.7")], check=True)
+    return str(out)
+
+
+@pytest.fixture
+def run(runtime, repo_root):
+    def go(program):
+        env = dict(os.environ, LD_LIBRARY_PATH=runtime)
+        res = subprocess.run([sys.executable, "-c", PRELUDE.format(root=repo_root) + textwrap.dedent(program)], env=env, capture_output=True, text=True, timeout=120)
+        assert res.returncode == 0, res.stderr[-3000:]
+    return go
+
+
+def test_a_perceptron_asks_for_no_stream(run):
+    """It has nothing to put on one: its forward pass makes no call but its launches, whatever stream it is given."""
+    run("""
+    m = Model(MLP)
+    for s in (None, stream(1), stream(2)):
+        hip.fake_clear()
+        m.forward(s)
+        assert log() and all(l.startswith("launch") for l in log()), log()
+        assert m.step(s)[1] == {hip.fake_id(s)}
+    """)
