@@ -48,8 +48,18 @@ __global__ void probe_look_kernel(int slot, int* result) {
   __hip_atomic_store(result, seen | kDone, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Both say what became of this launch: the thread's last error may be an earlier call's, and is then its caller's to read.
+hipError_t set(int slot, int c, hipStream_t s) {
+  void* args[] = {&slot, &c};
+  return hipLaunchKernel(reinterpret_cast<const void*>(probe_set_kernel), dim3(1), dim3(1), args, 0, s);
+}
+hipError_t look(int slot, int* result, hipStream_t s) {
+  void* args[] = {&slot, &result};
+  return hipLaunchKernel(reinterpret_cast<const void*>(probe_look_kernel), dim3(1), dim3(1), args, 0, s);
+}
+
 struct DeviceStreams {
-  bool tried = false, ok = false;
+  bool ok = false;
   hipStream_t side[kSide] = {};
   int* result = nullptr;            // pinned, one word per probe
   std::vector<hipStream_t> seen;    // caller's streams, in slot order
@@ -58,7 +68,6 @@ std::mutex g_lock;
 DeviceStreams g_devices[kMaxDevices];
 
 void create(DeviceStreams& d) {
-  d.tried = true;
   // (an allocation would otherwise fail, and end the capture, while another thread captures a graph)
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   (void)hipThreadExchangeStreamCaptureMode(&mode);
@@ -66,8 +75,7 @@ void create(DeviceStreams& d) {
   for (int c = 0; ok && c < kSide; ++c) ok = hipStreamCreateWithFlags(&d.side[c], hipStreamNonBlocking) == hipSuccess;
   if (ok) {
     for (int i = 0; i < kProbes; ++i) d.result[i] = 0;
-    for (int c = 0; c < kSide; ++c) hipLaunchKernelGGL(probe_set_kernel, dim3(1), dim3(1), 0, d.side[c], 0, -1);   // a stream's first launch is slow
-    ok = hipGetLastError() == hipSuccess;
+    for (int c = 0; ok && c < kSide; ++c) ok = set(0, -1, d.side[c]) == hipSuccess;   // a stream's first launch is slow
   }
   (void)hipThreadExchangeStreamCaptureMode(&mode);
   d.ok = ok;
@@ -84,15 +92,15 @@ hipStream_t side_stream_beside(hipStream_t s, unsigned turn) {
   if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= kMaxDevices) { (void)hipGetLastError(); return nullptr; }
   std::lock_guard<std::mutex> guard(g_lock);
   DeviceStreams& d = g_devices[device];
-  if (!d.tried) create(d);
-  if (!d.ok) return nullptr;
+  if (!d.ok) create(d);
+  if (!d.ok) return nullptr;      // (the next forward pass tries again)
   size_t slot = 0;
   while (slot < d.seen.size() && d.seen[slot] != s) ++slot;
   if (slot == d.seen.size() && slot < (size_t)kProbes) {
+    if (look((int)slot, d.result + slot, s) != hipSuccess) { (void)hipGetLastError(); return d.side[turn % kSide]; }
     d.seen.push_back(s);
-    hipLaunchKernelGGL(probe_look_kernel, dim3(1), dim3(1), 0, s, (int)slot, d.result + slot);
-    for (int c = 0; c < kSide; ++c) hipLaunchKernelGGL(probe_set_kernel, dim3(1), dim3(1), 0, d.side[c], (int)slot, c);
-    (void)hipGetLastError();
+    for (int c = 0; c < kSide; ++c)
+      if (set((int)slot, c, d.side[c]) != hipSuccess) (void)hipGetLastError();
   }
   const int found = slot < (size_t)kProbes ? __atomic_load_n(d.result + slot, __ATOMIC_ACQUIRE) : 0;
   int good[kSide], n = 0;

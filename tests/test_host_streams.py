@@ -74,3 +74,23 @@ def test_a_perceptron_asks_for_no_stream(run):
         assert log() and all(l.startswith("launch") for l in log()), log()
         assert m.step(s)[1] == {hip.fake_id(s)}
     """)
+
+
+@pytest.mark.parametrize("spoil,mend", [("hip.fake_error(101)", "pass"), ("hip.fake_refuse_launches(1)", "hip.fake_refuse_launches(0)")])
+def test_an_earlier_error_costs_no_overlap(run, spoil, mend):
+    """An error that a call outside the library left behind is reported by the first step, which launches kernels, and no later
+    step suffers from it; the same after launches that failed while the streams were set up."""
+    run(f"""
+    m, s = Model(ENCODER), stream(1)
+    {spoil}
+    try:
+        m.forward(s)
+        raise SystemExit("not reported")
+    except spb.SpbError as e:
+        assert e.code == -5, e
+    {mend}
+    for _ in range(3):
+        used = m.step(s)[1]
+        assert hip.fake_id(s) in used and len(used) == 2, used
+        hip.fake_wait()
+    """)
