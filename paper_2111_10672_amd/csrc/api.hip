@@ -2,7 +2,6 @@
 #include <cstdlib>
 #include "model.h"
 
-#include <atomic>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -43,23 +42,20 @@ Model::~Model() {
 }
 
 void Model::ensure_side_stream(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) { (void)hipGetLastError(); return; }
-  if (!fork_ev_) {
-    static std::atomic<unsigned> models{0};
-    hipEvent_t ev[2 + kMarks] = {};
-    bool ok = true;
-    for (int i = 0; ok && i < 2 + kMarks; ++i) ok = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming) == hipSuccess;
-    if (!ok) {
-      (void)hipGetLastError();
-      for (auto e : ev) if (e) (void)hipEventDestroy(e);
-      return;
-    }
-    turn_ = models++;
-    fork_ev_ = ev[0]; join_ev_ = ev[1];
-    for (int i = 0; i < kMarks; ++i) mark_ev_[i] = ev[2 + i];
+  if (forked_) return;
+  side_ = streams_.beside(s);
+  if (!side_ || fork_ev_) return;
+  hipEvent_t ev[2 + kMarks] = {};
+  bool ok = true;
+  for (int i = 0; ok && i < 2 + kMarks; ++i) ok = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming) == hipSuccess;
+  if (!ok) {
+    (void)hipGetLastError();
+    for (auto e : ev) if (e) (void)hipEventDestroy(e);
+    side_ = nullptr;
+    return;
   }
-  if (!forked_) side_ = side_stream_beside(s, turn_);
+  fork_ev_ = ev[0]; join_ev_ = ev[1];
+  for (int i = 0; i < kMarks; ++i) mark_ev_[i] = ev[2 + i];
 }
 
 int Model::mark() {

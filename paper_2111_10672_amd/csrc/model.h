@@ -46,6 +46,29 @@ class KernelTimer {
   std::vector<hipEvent_t> pool_;
 };
 
+// The streams beside the caller's that a model's weight gradients may run on: its own, made when first asked for; see
+// streams.hip.
+class SideStreams {
+ public:
+  ~SideStreams();
+  // The one that is known to run beside s, or any of them; nullptr if there are none (none can be had, or s is being
+  // captured into a graph before they were made).
+  hipStream_t beside(hipStream_t s);
+
+ private:
+  static constexpr int kSide = 3;
+  bool create();
+  void release();
+  void ask(hipStream_t s);
+  void answer();
+  hipStream_t side_[kSide] = {};
+  hipEvent_t looked_ = nullptr, ran_[kSide] = {};
+  hipStream_t for_ = nullptr;      // the caller's stream that the rest is about
+  int pick_ = 0;
+  long calls_ = 0, next_ = 0, wait_ = 1;    // no question before call next_
+  bool known_ = false, asked_ = false, waiting_ = false;
+};
+
 class Model {
  public:
   virtual ~Model();
@@ -71,8 +94,8 @@ class Model {
   std::map<std::string, Product> last_product;  // per kernel class, the most recent product or pair (kept while timing is on)
   int replay(const char* name, int count, hipStream_t s);
 
-  // Picks the side stream (see fork) that goes with s, unless s is being captured into a graph right now; called by the
-  // C ABI before a forward pass, so a model built on a machine without a GPU never touches the runtime.
+  // Picks the side stream (see fork) that goes with s; called by the C ABI before a forward pass, so a model built on a
+  // machine without a GPU never touches the runtime.
   void ensure_side_stream(hipStream_t s);
   int finish(hipStream_t s) { return join(s); }   // after a backward pass: s waits for whatever is still on the side stream
 
@@ -95,16 +118,12 @@ class Model {
   int check(hipError_t e, const char* what);
 
  private:
-  hipStream_t side_ = nullptr;   // one of the device's (see streams.hip), not this model's to destroy
-  unsigned turn_ = 0;
+  SideStreams streams_;
+  hipStream_t side_ = nullptr;   // one of streams_
   hipEvent_t fork_ev_ = nullptr, join_ev_ = nullptr, mark_ev_[kMarks] = {};
   int next_mark_ = 0;
   bool forked_ = false;
 };
-
-// One of the few streams the library keeps per device, on another hardware queue than s where that is known; models take
-// them in turn.  nullptr if none can be had.  See streams.hip.
-hipStream_t side_stream_beside(hipStream_t s, unsigned turn);
 
 std::unique_ptr<Model> make_mlp(const spb_model_desc& d);
 std::unique_ptr<Model> make_encoder(const spb_model_desc& d);

@@ -94,3 +94,64 @@ def test_an_earlier_error_costs_no_overlap(run, spoil, mend):
         assert hip.fake_id(s) in used and len(used) == 2, used
         hip.fake_wait()
     """)
+
+
+def test_models_share_no_stream_and_give_theirs_back(run):
+    """Two workers on streams of their own: neither's weight gradients wait for the other's, and nothing stays behind."""
+    run("""
+    callers = [stream(0), stream(0), stream(2)]
+    streams, events = hip.fake_live_streams(), hip.fake_live_events()
+    models = [Model(ENCODER) for _ in range(9)]
+    for _ in range(4):
+        used = [m.step(callers[i % 3])[1] - {hip.fake_id(callers[i % 3])} for i, m in enumerate(models)]
+        assert all(len(u) == 1 for u in used) and len(set().union(*used)) == len(models), used
+        hip.fake_wait()
+    for m in models:
+        m.close()
+    assert (hip.fake_live_streams(), hip.fake_live_events()) == (streams, events)
+    """)
+
+
+@pytest.mark.parametrize("caller", range(4))
+@pytest.mark.parametrize("first", range(4))
+def test_the_stream_on_another_queue_is_found(run, caller, first):
+    """Wherever the caller's stream and the model's lie, from the step after the question was answered the weight gradients
+    run on another queue than the caller's."""
+    run(f"""
+    s = stream({caller})
+    hip.fake_next_queue({first})
+    m = Model(ENCODER)
+    for step in range(4):
+        lines, used = m.step(s)
+        if step == 0:
+            made = [int(l.split()[-1]) for l in lines if "hipStreamCreate" in l]
+        side, = used - {{hip.fake_id(s)}}
+        assert step == 0 or ({first} + made.index(side)) % 4 != {caller}, (step, side, made)
+        hip.fake_wait()
+    """)
+
+
+def test_questions_are_few_however_often_the_caller_changes(run):
+    run("""
+    m, callers = Model(ENCODER), [stream(q % 4) for q in range(70)]
+    asked = 0
+    for step in range(1000):
+        asked += sum("spin" in l for l in m.step(callers[step % 70])[0])
+        hip.fake_wait()
+    assert 0 < asked <= 11, asked
+    """)
+
+
+def test_nothing_is_set_up_while_the_caller_captures(run):
+    run("""
+    m, s = Model(ENCODER), stream(1)
+    hip.fake_capture(s, 1)
+    lines, used = m.step(s)
+    assert used == {hip.fake_id(s)} and all("Create" not in l and "spin" not in l for l in lines)
+    hip.fake_capture(s, 0)
+    assert len(m.step(s)[1]) == 2
+    hip.fake_wait()
+    hip.fake_capture(s, 1)
+    lines, used = m.step(s)
+    assert used == {hip.fake_id(s)} and all("spin" not in l and not l.startswith(("wait", "record")) for l in lines)
+    """)
