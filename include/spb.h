@@ -35,7 +35,8 @@
  *     the extra stream is not used.  Results are the same bits in every case.  To
  *     find out which of them runs beside the caller's stream, spb_forward puts a
  *     kernel of 100 us (that does nothing else) on a caller's stream that is new to
- *     the model.  Two models share nothing.
+ *     the model, and again, ever more rarely, while none was seen to and every 4096
+ *     calls.  Two models share nothing.
  *   - All matrices are row-major.  Activations of perceptrons are
  *     [batch, features].
  *   - A model needs a GPU; there is no host fallback.

@@ -51,7 +51,7 @@ class KernelTimer {
 class SideStreams {
  public:
   ~SideStreams();
-  // The one that is known to run beside s, or any of them; nullptr if there are none (none can be had, or s is being
+  // The one that was last seen to run beside s, or any of them; nullptr if there are none (none can be had, or s is being
   // captured into a graph before they were made).
   hipStream_t beside(hipStream_t s);
 
@@ -66,7 +66,8 @@ class SideStreams {
   hipStream_t for_ = nullptr;      // the caller's stream that the rest is about
   int pick_ = 0;
   long calls_ = 0, next_ = 0, wait_ = 1;    // no question before call next_
-  bool known_ = false, asked_ = false, waiting_ = false;
+  long until_ = 0;                          // what is known holds before call until_
+  bool known_ = false, waiting_ = false;
 };
 
 class Model {

@@ -7,14 +7,18 @@
 // model has three streams (of two, made one after the other, both were seen on one queue), and asks for a caller's stream: a
 // kernel there runs for 100 us, and an empty one goes to each of the three behind it.  One that ended well before the long
 // kernel did runs beside it; behind the same queue it could not have.  Nothing waits on the host: the events' times are
-// read by the first call that finds them there.
+// read by the first call that finds them there.  Where none was seen beside it (the other queues may have been busy with
+// another model's work) the question is asked again, ever more rarely; and an answer holds for a number of calls only,
+// because a handle says nothing about the stream behind it: one that was destroyed may come back on another queue.
 #include "model.h"
 
 namespace spb {
 namespace {
 
 constexpr float kBesideMs = 0.01f;   // ahead of the long kernel's end by this much: one queue's order never looks like it
-constexpr long kLongest = 4096;      // questions come at least 1, 2, 4, ... and then this many calls after one another, however often s changes
+// Questions come at least 1, 2, 4, ... and then this many calls after one another, however often s changes and whatever
+// was seen; an answer holds for as many calls (100 us in 4096 steps of 1 ms are 0.002 %).
+constexpr long kLongest = 4096;
 constexpr long long kTick = 100;     // wall_clock64 ticks per microsecond (100 MHz)
 
 // 100 us; the iteration count bounds it without a clock.
@@ -62,7 +66,7 @@ void SideStreams::ask(hipStream_t s) {
   bool ok = launch(spin_kernel, s) && hipEventRecord(looked_, s) == hipSuccess;
   for (int c = 0; ok && c < kSide; ++c) ok = launch(empty_kernel, side_[c]) && hipEventRecord(ran_[c], side_[c]) == hipSuccess;
   if (!ok) { (void)hipGetLastError(); return; }
-  asked_ = waiting_ = true;
+  waiting_ = true;
   next_ = calls_ + wait_;
   if (wait_ < kLongest) wait_ *= 2;
 }
@@ -76,22 +80,22 @@ void SideStreams::answer() {
     const int c = (pick_ + i) % kSide;
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, ran_[c], looked_) != hipSuccess) (void)hipGetLastError();   // still behind something: not known to run beside
-    else if (ms > kBesideMs) { pick_ = c; known_ = true; }
+    else if (ms > kBesideMs) { pick_ = c; known_ = true; until_ = calls_ + kLongest; }
   }
 }
 
 hipStream_t SideStreams::beside(hipStream_t s) {
   ++calls_;
-  if (known_ && s == for_) return side_[pick_];
+  if (known_ && s == for_ && calls_ < until_) return side_[pick_];
   const Uncaptured guard;
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &st) != hipSuccess) { (void)hipGetLastError(); return side_[pick_]; }
   if (st != hipStreamCaptureStatusNone) return side_[pick_];
   if (hipPeekAtLastError() != hipSuccess) return side_[pick_];      // an earlier call's error: neither ours to clear nor to be taken for ours
   if (!side_[0] && !create()) return nullptr;                       // (the next forward pass tries again)
-  if (s != for_) { for_ = s; known_ = asked_ = waiting_ = false; }
-  if (!asked_ && calls_ >= next_) ask(s);
-  else if (waiting_) answer();
+  if (known_ || s != for_) { for_ = s; known_ = waiting_ = false; }
+  if (waiting_) answer();
+  else if (calls_ >= next_) ask(s);
   return side_[pick_];
 }
 

@@ -108,6 +108,7 @@ void fake_next_queue(int q) { g_next_queue = q; }
 void fake_error(int e) { g_last_error = e; }
 void fake_refuse_launches(int on) { g_refuse_launches = on; }
 void fake_capture(void* s, int on) { of(s)->capturing = on; }
+void fake_move(void* s, int queue) { of(s)->queue = queue; }
 void fake_busy(int queue, double ms) { g_clock[queue] = (g_clock[queue] > g_now ? g_clock[queue] : g_now) + ms; }
 void fake_wait() { for (double t : g_clock) if (t > g_now) g_now = t; }      // the host waits for the device
 void fake_pass(double ms) { g_now += ms; }

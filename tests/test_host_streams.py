@@ -15,6 +15,7 @@ sys.path.insert(0, {root!r})
 hip = C.CDLL("libamdhip64.so.7", mode=C.RTLD_GLOBAL)
 hip.fake_stream.restype, hip.fake_log.restype = C.c_void_p, C.c_char_p
 hip.fake_id.argtypes, hip.fake_capture.argtypes = [C.c_void_p], [C.c_void_p, C.c_int]
+hip.fake_move.argtypes = [C.c_void_p, C.c_int]
 hip.fake_busy.argtypes, hip.fake_pass.argtypes = [C.c_int, C.c_double], [C.c_double]
 import paper_2111_10672_amd as spb
 
@@ -154,4 +155,49 @@ def test_nothing_is_set_up_while_the_caller_captures(run):
     hip.fake_capture(s, 1)
     lines, used = m.step(s)
     assert used == {hip.fake_id(s)} and all("spin" not in l and not l.startswith(("wait", "record")) for l in lines)
+    """)
+
+
+@pytest.mark.parametrize("caller", range(4))
+def test_a_question_met_by_busy_queues_is_asked_again(run, caller):
+    """While every other queue is busy with other work (another model's, say) no stream is seen beside the caller's, which
+    says nothing about the time after."""
+    run(f"""
+    s = stream({caller})
+    hip.fake_next_queue({caller})
+    m = Model(ENCODER)
+    for step in range(8):
+        if step < 2:
+            for q in range(4):
+                if q != {caller}:
+                    hip.fake_busy(q, 50.0)
+        lines, used = m.step(s)
+        if step == 0:
+            made = [int(l.split()[-1]) for l in lines if "hipStreamCreate" in l]
+        side, = used - {{hip.fake_id(s)}}
+        hip.fake_wait()
+    assert ({caller} + made.index(side)) % 4 != {caller}, (side, made)
+    """)
+
+
+def test_another_stream_behind_the_same_handle_is_noticed(run):
+    """A destroyed stream's handle may come back for a new stream on another queue: what was known of the old one does not
+    hold for good."""
+    run("""
+    s = stream(1)
+    hip.fake_next_queue(1)
+    m = Model(ENCODER)
+    where = {}
+    for step in range(5200):
+        if step == 20:
+            hip.fake_move(s, side)
+        lines, used = m.step(s)
+        for l in lines:
+            if "hipStreamCreate" in l:
+                where[int(l.split()[-1])] = (1 + len(where)) % 4
+        queue, = {where[u] for u in used - {hip.fake_id(s)}}
+        if step == 19:
+            side = queue
+        hip.fake_wait()
+    assert queue != side, (queue, side)
     """)
