@@ -25,18 +25,19 @@
  *   - Work is enqueued on the caller's stream (a hipStream_t passed as void*);
  *     calls return without waiting for the device and may be captured into a
  *     HIP graph.  Calls on one model must not overlap in time.
- *   - A residual CNN or encoder owns three more HIP streams and a few events (no device
- *     memory), created by its first spb_forward outside a graph capture and released
+ *   - A residual CNN or encoder owns one to three more HIP streams and a few events (no
+ *     device memory), created by its forward passes outside a graph capture and released
  *     by spb_model_destroy.  spb_backward_truncated runs weight-gradient kernels on
  *     one of those streams beside the input-gradient chain; it first makes that
  *     stream wait for the caller's and, before it returns, makes the caller's stream
  *     wait for it, so to the caller everything is ordered on the stream that was
  *     passed.  While that stream is being captured, and while kernel timing is on,
- *     the extra stream is not used.  Results are the same bits in every case.  To
- *     find out which of them runs beside the caller's stream, spb_forward puts a
- *     kernel of 100 us (that does nothing else) on a caller's stream that is new to
- *     the model, and again, ever more rarely, while none was seen to and every 4096
- *     calls.  Two models share nothing.
+ *     the extra stream is not used.  Results are the same bits in every case.  To find
+ *     out whether it runs beside the caller's stream, spb_forward puts a kernel of
+ *     100 us (that does nothing else) on it and an empty one on the caller's, which ends
+ *     behind the first if the two streams share a hardware queue: for a caller's stream
+ *     that is new to the model, again, ever more rarely, while the two were not seen to
+ *     run side by side, and every 4096 calls.  Two models share nothing.
  *   - All matrices are row-major.  Activations of perceptrons are
  *     [batch, features].
  *   - A model needs a GPU; there is no host fallback.

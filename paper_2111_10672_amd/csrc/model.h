@@ -57,14 +57,13 @@ class SideStreams {
 
  private:
   static constexpr int kSide = 3;
-  bool create();
-  void release();
+  bool make();
   void ask(hipStream_t s);
   void answer();
-  hipStream_t side_[kSide] = {};
-  hipEvent_t looked_ = nullptr, ran_[kSide] = {};
+  struct Side { hipStream_t stream = nullptr; hipEvent_t asked = nullptr, ran = nullptr, passed = nullptr; };
+  Side side_[kSide];
   hipStream_t for_ = nullptr;      // the caller's stream that the rest is about
-  int pick_ = 0;
+  int made_ = 0, pick_ = 0;
   long calls_ = 0, next_ = 0, wait_ = 1;    // no question before call next_
   long until_ = 0;                          // what is known holds before call until_
   bool known_ = false, waiting_ = false;

@@ -3,19 +3,21 @@
 // HIP maps the streams of a process onto a few hardware queues (four by default), and two streams on one queue run one
 // after the other.  A model with one stream of its own therefore shares its queue with the caller's stream one time in
 // four, and loses all overlap (encoder of 32 x 128 tokens, everything but the embedding: 4.30 ms with the two streams on
-// different queues, 5.80 ms on the same one).  The runtime does not say which queue a stream is on, so it is found out: a
-// model has three streams (of two, made one after the other, both were seen on one queue), and asks for a caller's stream: a
-// kernel there runs for 100 us, and an empty one goes to each of the three behind it.  One that ended well before the long
-// kernel did runs beside it; behind the same queue it could not have.  Nothing waits on the host: the events' times are
-// read by the first call that finds them there.  Where none was seen beside it (the other queues may have been busy with
-// another model's work) the question is asked again, ever more rarely; and an answer holds for a number of calls only,
-// because a handle says nothing about the stream behind it: one that was destroyed may come back on another queue.
+// different queues, 5.80 ms on the same one).  The runtime does not say which queue a stream is on, so it is found out:
+// a stream of the model's waits for the caller's and runs a kernel of 100 us, and the caller's runs an empty kernel that
+// was enqueued behind that one.  If the empty one ended well before the long one did, the two run beside each other; on
+// one queue it could not have.  Nothing waits on the host: the events' times are read by the first call that finds them
+// there.  A model has one stream at first and makes another (up to three) when none it has was seen beside the caller's: a
+// stream takes 35 us to make and as long to destroy, and of two, made one after the other, both were seen on one queue.
+// Then the question is asked again, ever more rarely, since the caller's queue may only have been busy with another
+// model's work.  An answer holds for a number of calls only, because a handle says nothing about the stream behind it:
+// one that was destroyed may come back on another queue.
 #include "model.h"
 
 namespace spb {
 namespace {
 
-constexpr float kBesideMs = 0.01f;   // ahead of the long kernel's end by this much: one queue's order never looks like it
+constexpr float kBesideMs = 0.01f;   // ended ahead of the long kernel by this much: one queue's order never looks like it
 // Questions come at least 1, 2, 4, ... and then this many calls after one another, however often s changes and whatever
 // was seen; an answer holds for as many calls (100 us in 4096 steps of 1 ms are 0.002 %).
 constexpr long kLongest = 4096;
@@ -43,60 +45,64 @@ struct Uncaptured {
 
 }  // namespace
 
-SideStreams::~SideStreams() { release(); }
-
-void SideStreams::release() {
-  for (auto& q : side_) if (q) { (void)hipStreamDestroy(q); q = nullptr; }
-  for (auto& e : ran_) if (e) { (void)hipEventDestroy(e); e = nullptr; }
-  if (looked_) { (void)hipEventDestroy(looked_); looked_ = nullptr; }
+SideStreams::~SideStreams() {
+  for (auto& x : side_) {
+    if (x.stream) (void)hipStreamDestroy(x.stream);
+    for (auto e : {x.asked, x.ran, x.passed}) if (e) (void)hipEventDestroy(e);
+  }
 }
 
-bool SideStreams::create() {
-  bool ok = hipEventCreate(&looked_) == hipSuccess;
-  for (int c = 0; ok && c < kSide; ++c)
-    ok = hipStreamCreateWithFlags(&side_[c], hipStreamNonBlocking) == hipSuccess && hipEventCreate(&ran_[c]) == hipSuccess &&
-         launch(empty_kernel, side_[c]);     // a stream's first launch is slow
-  if (ok) return true;
+// One more stream, if there may be and can be.
+bool SideStreams::make() {
+  if (made_ == kSide) return false;
+  Side& x = side_[made_];
+  if ((x.asked || hipEventCreateWithFlags(&x.asked, hipEventDisableTiming) == hipSuccess) && (x.ran || hipEventCreate(&x.ran) == hipSuccess) &&
+      (x.passed || hipEventCreate(&x.passed) == hipSuccess) && hipStreamCreateWithFlags(&x.stream, hipStreamNonBlocking) == hipSuccess) {
+    pick_ = made_++;
+    return true;
+  }
   (void)hipGetLastError();
-  release();
   return false;
 }
 
 void SideStreams::ask(hipStream_t s) {
-  bool ok = launch(spin_kernel, s) && hipEventRecord(looked_, s) == hipSuccess;
-  for (int c = 0; ok && c < kSide; ++c) ok = launch(empty_kernel, side_[c]) && hipEventRecord(ran_[c], side_[c]) == hipSuccess;
-  if (!ok) { (void)hipGetLastError(); return; }
-  waiting_ = true;
   next_ = calls_ + wait_;
   if (wait_ < kLongest) wait_ *= 2;
+  waiting_ = true;
+  for (int c = 0; c < made_ && waiting_; ++c) {       // one after the other: on s's queue one holds up s
+    const Side& x = side_[c];
+    waiting_ = hipEventRecord(x.asked, s) == hipSuccess && hipStreamWaitEvent(x.stream, x.asked, 0) == hipSuccess && launch(spin_kernel, x.stream) &&
+               hipEventRecord(x.ran, x.stream) == hipSuccess && launch(empty_kernel, s) && hipEventRecord(x.passed, s) == hipSuccess;
+  }
+  if (!waiting_) (void)hipGetLastError();
 }
 
 void SideStreams::answer() {
-  const hipError_t e = hipEventQuery(looked_);
-  if (e != hipSuccess) (void)hipGetLastError();
-  if (e == hipErrorNotReady) return;
-  waiting_ = false;
-  for (int i = 0; i < kSide && !known_; ++i) {
-    const int c = (pick_ + i) % kSide;
+  for (int i = 0; i < made_; ++i) {
+    const int c = (pick_ + i) % made_;
     float ms = 0.f;
-    if (hipEventElapsedTime(&ms, ran_[c], looked_) != hipSuccess) (void)hipGetLastError();   // still behind something: not known to run beside
-    else if (ms > kBesideMs) { pick_ = c; known_ = true; until_ = calls_ + kLongest; }
+    const hipError_t e = hipEventElapsedTime(&ms, side_[c].passed, side_[c].ran);
+    if (e != hipSuccess) (void)hipGetLastError();
+    if (e == hipErrorNotReady) return;
+    if (e == hipSuccess && ms > kBesideMs) { pick_ = c; known_ = true; until_ = calls_ + kLongest; return; }
   }
+  waiting_ = false;
+  (void)make();
 }
 
 hipStream_t SideStreams::beside(hipStream_t s) {
   ++calls_;
-  if (known_ && s == for_ && calls_ < until_) return side_[pick_];
+  if (known_ && s == for_ && calls_ < until_) return side_[pick_].stream;
   const Uncaptured guard;
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) != hipSuccess) { (void)hipGetLastError(); return side_[pick_]; }
-  if (st != hipStreamCaptureStatusNone) return side_[pick_];
-  if (hipPeekAtLastError() != hipSuccess) return side_[pick_];      // an earlier call's error: neither ours to clear nor to be taken for ours
-  if (!side_[0] && !create()) return nullptr;                       // (the next forward pass tries again)
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) { (void)hipGetLastError(); return side_[pick_].stream; }
+  if (st != hipStreamCaptureStatusNone) return side_[pick_].stream;
+  if (hipPeekAtLastError() != hipSuccess) return side_[pick_].stream;      // an earlier call's error: neither ours to clear nor to be taken for ours
+  if (!made_ && !make()) return nullptr;                            // (the next forward pass tries again)
   if (known_ || s != for_) { for_ = s; known_ = waiting_ = false; }
   if (waiting_) answer();
-  else if (calls_ >= next_) ask(s);
-  return side_[pick_];
+  if (!waiting_ && !known_ && calls_ >= next_) ask(s);
+  return side_[pick_].stream;
 }
 
 }  // namespace spb

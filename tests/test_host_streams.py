@@ -121,14 +121,30 @@ def test_the_stream_on_another_queue_is_found(run, caller, first):
     run(f"""
     s = stream({caller})
     hip.fake_next_queue({first})
-    m = Model(ENCODER)
+    m, made = Model(ENCODER), []
     for step in range(4):
         lines, used = m.step(s)
-        if step == 0:
-            made = [int(l.split()[-1]) for l in lines if "hipStreamCreate" in l]
+        made += [int(l.split()[-1]) for l in lines if "hipStreamCreate" in l]
         side, = used - {{hip.fake_id(s)}}
         assert step == 0 or ({first} + made.index(side)) % 4 != {caller}, (step, side, made)
         hip.fake_wait()
+    """)
+
+
+@pytest.mark.parametrize("caller", range(4))
+def test_a_first_step_makes_one_stream_and_the_caller_runs_nothing_long(run, caller):
+    """A new model's first step pays for what it sets up: one stream, and further ones only if that is on the caller's queue."""
+    run(f"""
+    s = stream({caller})
+    hip.fake_next_queue(1)
+    m, made = Model(ENCODER), []
+    for step in range(20):
+        lines, _ = m.step(s)
+        made.append(sum("hipStreamCreate" in l for l in lines))
+        spun = [int(l.split()[-1]) for l in lines if "spin" in l]
+        assert len(spun) <= sum(made) and hip.fake_id(s) not in spun, spun
+        hip.fake_wait()
+    assert made == [1, {int(caller == 1)}] + [0] * 18, made
     """)
 
 
@@ -165,15 +181,14 @@ def test_a_question_met_by_busy_queues_is_asked_again(run, caller):
     run(f"""
     s = stream({caller})
     hip.fake_next_queue({caller})
-    m = Model(ENCODER)
+    m, made = Model(ENCODER), []
     for step in range(8):
         if step < 2:
             for q in range(4):
                 if q != {caller}:
                     hip.fake_busy(q, 50.0)
         lines, used = m.step(s)
-        if step == 0:
-            made = [int(l.split()[-1]) for l in lines if "hipStreamCreate" in l]
+        made += [int(l.split()[-1]) for l in lines if "hipStreamCreate" in l]
         side, = used - {{hip.fake_id(s)}}
         hip.fake_wait()
     assert ({caller} + made.index(side)) % 4 != {caller}, (side, made)
