@@ -1,6 +1,8 @@
 """The backward pass launched eagerly runs weight gradients on a second stream of the library's own.  Every
 kernel sums in a fixed order, so the gradients must come out bit for bit as in the single-stream order, which
 the library keeps while kernels are being timed and while the caller's stream is being captured into a graph."""
+import threading
+
 import pytest
 import torch
 
@@ -74,3 +76,43 @@ def test_two_stream_backward_at_full_size(name):
                 assert torch.equal(serial[n], eager[n]), f"{name} k={k} repetition {rep}: {n} differs"
     finally:
         model.close()
+
+
+def test_models_stepped_from_two_threads_on_two_streams():
+    """Two workers in one process, each with a caller's stream and a thread of its own, their steps in flight together: the
+    gradients are those of each model alone."""
+    names = ["fused_attention_encoder_bf16", "small_resnet_bottleneck_bf16"]
+    models, devs, want, threads, wrong = [], [], [], [], []
+    try:
+        for i, name in enumerate(names):
+            cfg = wl.get_config(name)
+            models.append(spb.SpbModel(cfg, wl.make_params(cfg, i, True)))
+            devs.append({n: t.cuda() for n, t in wl.make_batch(cfg, i).items()})
+            want.append(_grads(models[i], devs[i], models[i].n_units, "timed"))
+
+        def work(i):
+            try:
+                streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+                for step in range(12):
+                    with torch.cuda.stream(streams[step // 3 % 2]):
+                        for g in models[i].grads:
+                            g.fill_(float("nan"))
+                        models[i].step(devs[i], models[i].n_units)
+                        torch.cuda.current_stream().synchronize()
+                        if models[i].loss.item() != want[i][0]:
+                            wrong.append((names[i], step, "loss"))
+                        wrong.extend((names[i], step, n) for n, g in models[i].grad_dict(models[i].n_units).items() if not torch.equal(g, want[i][1][n]))
+            except Exception as e:      # (a thread's exception reaches no one by itself)
+                wrong.append((names[i], repr(e)))
+
+        print(f"case {names} on two threads", flush=True)
+        torch.cuda.synchronize()
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not wrong, wrong
+    finally:
+        for m in models:
+            m.close()
