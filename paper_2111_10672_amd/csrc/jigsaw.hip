@@ -22,8 +22,10 @@ namespace {
 // duration d of the plan (the caller checks): no task then fits between an end and an equal start.
 struct Device {
   std::vector<double> start, end;
-  bool join = true;
+  bool join;
   mutable size_t near = 0;          // where the last lookup ended; a job's chain asks for ascending times, so the next is close
+
+  explicit Device(bool joins) : join(joins) {}
 
   // index of the first interval that ends after t: everything before it lies wholly before t
   size_t first_after(double t) const {
@@ -126,8 +128,7 @@ int validate(const spb_sched_job* jobs, int n_jobs, int n_machines, double gamma
 }
 
 spb_sched_task* place_tasks(const spb_sched_job* jobs, int n_jobs, int n_machines, double gamma, spb_sched_task* out) {
-  std::vector<Device> dev(n_machines);
-  for (Device& dv : dev) dv.join = may_join(jobs, n_jobs, gamma);
+  std::vector<Device> dev(n_machines, Device(may_join(jobs, n_jobs, gamma)));
   std::vector<Progress> prog(n_jobs);
   struct Slot { double key; int job, worker; };                // key: -resource * duration
   std::vector<Slot> order;
@@ -174,8 +175,7 @@ spb_sched_task* place_tasks(const spb_sched_job* jobs, int n_jobs, int n_machine
 }
 
 spb_sched_task* place_gangs(const spb_sched_job* jobs, int n_jobs, int n_machines, double gamma, spb_sched_task* out) {
-  std::vector<Device> dev(n_machines);
-  for (Device& dv : dev) dv.join = may_join(jobs, n_jobs, gamma);
+  std::vector<Device> dev(n_machines, Device(may_join(jobs, n_jobs, gamma)));
   std::vector<std::vector<int>> last(n_jobs);
   std::vector<double> weight(n_jobs), slowest(n_jobs);
   using Key = std::tuple<double, int, int>;                    // (-(sum of resources) * slowest duration, job, iteration)
