@@ -25,19 +25,21 @@
  *   - Work is enqueued on the caller's stream (a hipStream_t passed as void*);
  *     calls return without waiting for the device and may be captured into a
  *     HIP graph.  Calls on one model must not overlap in time.
- *   - A residual CNN or encoder owns one to three more HIP streams and a few events (no
- *     device memory), created by its forward passes outside a graph capture and released
- *     by spb_model_destroy.  spb_backward_truncated runs weight-gradient kernels on
- *     one of those streams beside the input-gradient chain; it first makes that
- *     stream wait for the caller's and, before it returns, makes the caller's stream
- *     wait for it, so to the caller everything is ordered on the stream that was
- *     passed.  While that stream is being captured, and while kernel timing is on,
- *     the extra stream is not used.  Results are the same bits in every case.  To find
+ *   - Beside a caller's stream on which residual CNNs or encoders step, the library
+ *     keeps one to three more HIP streams (no device memory), created by spb_forward
+ *     outside a graph capture.  A model holds on to those of the four caller's streams
+ *     it was last called with and owns a few events; what no model holds on to is
+ *     released, at the latest by spb_model_destroy.  spb_backward_truncated runs
+ *     weight-gradient kernels on one of those streams beside the input-gradient chain;
+ *     it first makes that stream wait for the caller's and, before it returns, makes the
+ *     caller's stream wait for it, so to the caller everything is ordered on the stream
+ *     that was passed.  While that stream is being captured, and while kernel timing is
+ *     on, the extra stream is not used.  Results are the same bits in every case.  To find
  *     out whether it runs beside the caller's stream, spb_forward puts a kernel of
  *     100 us (that does nothing else) on it and an empty one on the caller's, which ends
  *     behind the first if the two streams share a hardware queue: for a caller's stream
- *     that is new to the model, again, ever more rarely, while the two were not seen to
- *     run side by side, and every 4096 calls.  Two models share nothing.
+ *     that is new, again, ever more rarely, while the two were not seen to run side by
+ *     side, and every 4096 calls.  Steps on different caller's streams share nothing.
  *   - All matrices are row-major.  Activations of perceptrons are
  *     [batch, features].
  *   - A model needs a GPU; there is no host fallback.
@@ -174,7 +176,7 @@ int spb_forward(spb_model* m, const void* x, const int32_t* labels, const int32_
  *   - a depth whose spb_workspace_size exceeds SPB_STATIC_WORKSPACE_BYTES is refused with SPB_ERR_WORKSPACE
  *     before anything is enqueued (the two perceptron workloads fit at every depth; the CNN and encoder
  *     workloads at full size do not);
- *   - the model's further streams are not created here, so unless an earlier spb_forward created them the backward
+ *   - no further stream is created here, so unless an earlier spb_forward of the model did that the backward
  *     pass stays on the caller's stream (same bits either way);
  *   - all models and all calls on one GPU share the one array, which keeps the last call's contents: a step
  *     (this call up to the end of its backward pass) must have completed on the device before the next

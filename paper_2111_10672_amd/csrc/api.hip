@@ -43,7 +43,7 @@ Model::~Model() {
 
 void Model::ensure_side_stream(hipStream_t s) {
   if (forked_) return;
-  side_ = streams_.beside(s);
+  side_ = sides_.of(s).beside(s);
   if (!side_ || fork_ev_) return;
   hipEvent_t ev[2 + kMarks] = {};
   bool ok = true;

@@ -7,6 +7,7 @@
 #include <functional>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -46,14 +47,14 @@ class KernelTimer {
   std::vector<hipEvent_t> pool_;
 };
 
-// The streams beside the caller's that a model's weight gradients may run on: its own, made when first asked for; see
-// streams.hip.
+// The streams beside one caller's stream that weight gradients may run on, made when first asked for; see streams.hip.
 class SideStreams {
  public:
   ~SideStreams();
   // The one that was last seen to run beside s, or any of them; nullptr if there are none (none can be had, or s is being
-  // captured into a graph before they were made).
+  // captured into a graph before they were made).  Always asked about the same s, until `forget`.
   hipStream_t beside(hipStream_t s);
+  void forget();
 
  private:
   static constexpr int kSide = 3;
@@ -61,12 +62,23 @@ class SideStreams {
   void ask(hipStream_t s);
   void answer();
   struct Side { hipStream_t stream = nullptr; hipEvent_t asked = nullptr, ran = nullptr, passed = nullptr; };
+  std::mutex lock_;                         // models on one caller's stream may be on several threads
   Side side_[kSide];
-  hipStream_t for_ = nullptr;      // the caller's stream that the rest is about
   int made_ = 0, pick_ = 0;
   long calls_ = 0, next_ = 0, wait_ = 1;    // no question before call next_
   long until_ = 0;                          // what is known holds before call until_
   bool known_ = false, waiting_ = false;
+};
+
+// Those of the caller's streams that a model was last called with.
+class CallersSides {
+ public:
+  SideStreams& of(hipStream_t s);
+
+ private:
+  static constexpr size_t kKept = 4;
+  struct Use { hipStream_t caller; int device; std::shared_ptr<SideStreams> sides; };
+  std::vector<Use> uses_;                   // the latest first
 };
 
 class Model {
@@ -118,8 +130,8 @@ class Model {
   int check(hipError_t e, const char* what);
 
  private:
-  SideStreams streams_;
-  hipStream_t side_ = nullptr;   // one of streams_
+  CallersSides sides_;
+  hipStream_t side_ = nullptr;   // one of sides_
   hipEvent_t fork_ev_ = nullptr, join_ev_ = nullptr, mark_ev_[kMarks] = {};
   int next_mark_ = 0;
   bool forked_ = false;
