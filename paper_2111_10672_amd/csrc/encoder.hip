@@ -152,6 +152,10 @@ class EncoderModel : public Model {
         void* keep_prob = (i + 1 >= num_units - k) ? w + b.prob : nullptr;
         if (int rc = run("attention_fwd", (double)M * H * 2 * 4 + (keep_prob ? (double)Z * S * S * 2 : 0.0), s, [&] {
               return launch_attention_fwd(w + b.qkv, 3 * H, keep_prob, w + b.ctx, H, B, NH, S, D, inv_sqrt_d, s); })) return rc;
+      } else if (attention_rows_accepts(S, D, 3 * H, H)) {
+        void* keep_prob = (i + 1 >= num_units - k) ? w + b.prob : nullptr;
+        if (int rc = run("attention_rows_fwd", (double)M * H * 2 * 4 + (keep_prob ? (double)Z * S * S * 2 : 0.0), s, [&] {
+              return launch_attention_rows_fwd(w + b.qkv, 3 * H, keep_prob, w + b.ctx, H, B, NH, S, D, inv_sqrt_d, s); })) return rc;
       } else {
       {
         GemmProblem g;  // scores[z, s, s'] = Q[s, :] . K[s', :] / sqrt(d)
@@ -303,6 +307,11 @@ class EncoderModel : public Model {
         if (int rc = run("attention_bwd", (double)M * H * 2 * 7 + (double)Z * S * S * 2, s, [&] {
               return launch_attention_bwd(qbase, 3 * H, w + b.prob, w + p.dctx, H, dqkv, B, NH, S, D, inv_sqrt_d, s); })) return rc;
       } else {
+      const bool by_rows = attention_rows_accepts(S, D, 3 * H, H);   // dS and dQ in one kernel
+      if (by_rows) {
+        if (int rc = run("attention_rows_bwd", (double)M * H * 2 * 5 + (double)Z * S * S * 4, s, [&] {
+              return launch_attention_rows_bwd(qbase, 3 * H, w + b.prob, w + p.dctx, H, w + p.dscore, dqkv, B, NH, S, D, inv_sqrt_d, s); })) return rc;
+      } else {
       {
         GemmProblem g;  // dP[s, s'] = dctx[s, :] . V[s', :]
         g.dtype = dtype; g.a_layout = Layout::RowK; g.b_layout = Layout::RowK; g.epilogue = Epilogue::StoreF32;
@@ -314,6 +323,7 @@ class EncoderModel : public Model {
       }
       if (int rc = run("softmax_bwd", (double)Z * S * S * 8, s, [&] {
             return launch_softmax_bwd(reinterpret_cast<const float*>(w + p.scores), w + b.prob, w + p.dscore, (long long)Z * S, S, inv_sqrt_d, s); })) return rc;
+      }
       auto attn_out = [&](const char* name, Layout la, const void* a, int lda, BatchStride ab, const void* bsrc, int col_block) {
         GemmProblem g;  // [S, D] per head, written into the q, k or v third of dqkv
         g.dtype = dtype; g.a_layout = la; g.b_layout = Layout::KRow; g.epilogue = Epilogue::BiasAct;
@@ -326,7 +336,8 @@ class EncoderModel : public Model {
       };
       // dV = P^T dctx;  dQ = dS K;  dK = dS^T Q
       if (int rc = attn_out("attn_bwd_dv", Layout::KRow, w + b.prob, S, per_matrix(), w + p.dctx, 2)) return rc;
-      if (int rc = attn_out("attn_bwd_dq", Layout::RowK, w + p.dscore, S, per_matrix(), bf(qbase, (size_t)H), 0)) return rc;
+      if (!by_rows)
+        if (int rc = attn_out("attn_bwd_dq", Layout::RowK, w + p.dscore, S, per_matrix(), bf(qbase, (size_t)H), 0)) return rc;
       if (int rc = attn_out("attn_bwd_dk", Layout::KRow, w + p.dscore, S, per_matrix(), qbase, 1)) return rc;
       }
       {

@@ -230,6 +230,14 @@ hipError_t launch_attention_fwd(const void* qkv, int ld_qkv, void* prob, void* c
 hipError_t launch_attention_bwd(const void* qkv, int ld_qkv, const void* prob, const void* dctx, int ld_ctx, void* dqkv, int batch,
                                 int heads, int seq, int head_dim, float scale, hipStream_t stream);
 
+// The same for 129 to 512 positions (attention_rows.hip); the backward half forms dS (dscore [batch * heads, seq, seq],
+// bfloat16) and dQ (into dqkv), and leaves dK = dS^T Q and dV = P^T dctx to batched products.
+bool attention_rows_accepts(int seq, int head_dim, int ld_qkv, int ld_ctx);
+hipError_t launch_attention_rows_fwd(const void* qkv, int ld_qkv, void* prob, void* ctx, int ld_ctx, int batch, int heads, int seq,
+                                     int head_dim, float scale, hipStream_t stream);
+hipError_t launch_attention_rows_bwd(const void* qkv, int ld_qkv, const void* prob, const void* dctx, int ld_ctx, void* dscore, void* dqkv,
+                                     int batch, int heads, int seq, int head_dim, float scale, hipStream_t stream);
+
 // Server-side aggregation and update (aggregate.hip): for each tensor, g = mean of `count` float32 worker
 // gradients (added in the order given), v = momentum * v + g + weight_decay * w, w = w - rate * v.  w is in
 // param_dtype (bfloat16 parameters are rounded to nearest-even after the float32 update), v is float32.

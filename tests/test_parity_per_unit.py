@@ -142,6 +142,12 @@ def test_every_unit_of_the_small_encoders(name):
     _teacher_forced(name)
 
 
+@pytest.mark.parametrize("name", ["rows_attention_136_bf16", "rows_attention_256_bf16", "rows_attention_328_bf16", "rows_attention_512_bf16",
+                                  "rows_attention_chain_bf16", "rows_attention_chain2_bf16", "long_attention_520_bf16"])
+def test_encoder_layers_of_more_than_128_positions(name):
+    _teacher_forced(name, units_to_run=[1])
+
+
 # Full size: the classifier, the top units, and one unit of every kind of shape further down (a stride-2 block with a
 # projection, the first block behind the stem, the stem itself / the embedding).
 @pytest.mark.parametrize("name,units", [("cfg3", [9, 8, 7, 5, 3, 1, 0]), ("cfg4", [17, 16, 14, 10]), ("cfg5", [13, 12, 11, 1, 0])])

@@ -72,6 +72,17 @@ CONFIGS = {
     "wide_encoder_1024_bf16": dict(family="encoder", dtype="bf16", batch=1, seq=40, layers=1, hidden=1024, heads=16,
                                    ffn=128, vocab=37, loss_rows=9, depths=[0, 1, 2, 3]),
     # a vocabulary large enough for the head's input gradient to be cut into k-slices and for the long-row loss kernel
+    # attention over more than 128 positions, by rows of 32 queries whose keys four waves divide: one 64-key tile a wave and
+    # three waves at work, four whole tiles, two tiles a wave with a ragged last one and an idle wave, four times two
+    "rows_attention_136_bf16": dict(family="encoder", dtype="bf16", batch=3, seq=136, layers=2, hidden=128, heads=2, ffn=128, vocab=97, loss_rows=41),
+    "rows_attention_256_bf16": dict(family="encoder", dtype="bf16", batch=2, seq=256, layers=1, hidden=64, heads=1, ffn=64, vocab=97, loss_rows=60),
+    "rows_attention_328_bf16": dict(family="encoder", dtype="bf16", batch=2, seq=328, layers=1, hidden=128, heads=2, ffn=128, vocab=97, loss_rows=60),
+    "rows_attention_512_bf16": dict(family="encoder", dtype="bf16", batch=2, seq=512, layers=1, hidden=128, heads=2, ffn=128, vocab=97, loss_rows=60),
+    # so many heads that the sums over the keys run in one chain over the waves; one tile a wave, two tiles a wave
+    "rows_attention_chain_bf16": dict(family="encoder", dtype="bf16", batch=32, seq=152, layers=1, hidden=512, heads=8, ffn=64, vocab=97, loss_rows=60),
+    "rows_attention_chain2_bf16": dict(family="encoder", dtype="bf16", batch=16, seq=264, layers=1, hidden=512, heads=8, ffn=64, vocab=97, loss_rows=60),
+    # longer than those rows: batched products and softmax passes
+    "long_attention_520_bf16": dict(family="encoder", dtype="bf16", batch=1, seq=520, layers=1, hidden=64, heads=1, ffn=64, vocab=97, loss_rows=60),
     "big_vocab_encoder_bf16": dict(family="encoder", dtype="bf16", batch=2, seq=16, layers=1, hidden=64, heads=1,
                                    ffn=72, vocab=2311, loss_rows=9, depths=[0, 1, 2, 3]),
     "tiny_resnet_basic": dict(family="resnet_basic", dtype="bf16", batch=2, image=[6, 6, 3],
