@@ -384,6 +384,20 @@ __global__ __launch_bounds__(256, 2) void attention_rows_bwd_kernel(const bf16_t
   keys_product<TPW>(frag, tiles, wave, last_wave, n_tiles, in_quarters != 0, dqkv + ((size_t)rb.b * seq + rb.q0) * ld_qkv + rb.h * kHeadDim, ld_qkv, rows, lane);
 }
 
+// dV = P^T dctx and dK = dS^T Q where their sums run in quarters: the tiles of the small-product kernel for all heads and both
+// products in one launch.  On their own these were two launches of 768 workgroups (8 x 512 tokens, 12 heads) whose rings, 128 KB,
+// leave a CU to one of them, and the tiles of a head lay on eight XCDs: 36 us each in the step.  A ring of one tile per wave lets two share a
+// CU, and a head's tiles, which read the same P or dS columns and the same Q or dctx, lie on one XCD: 49 us for both (the step
+// 5812 -> 5609 us).
+__global__ __launch_bounds__(256) void attention_rows_keys_kernel(GemmParams dv, GemmParams dk) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int tiles = dv.tiles_m * dv.tiles_n;
+  const int run = xcd_tile(blockIdx.x, gridDim.x);
+  const int z2 = run / tiles, tile = run - z2 * tiles;
+  if (z2 & 1) small_product<64, 64, 1, Layout::KRow, Layout::KRow>(dk, tile, z2 >> 1, lds);
+  else small_product<64, 64, 1, Layout::KRow, Layout::KRow>(dv, tile, z2 >> 1, lds);
+}
+
 bool aligned16(const void* a, const void* b, const void* c, const void* d = nullptr, const void* e = nullptr) {
   return ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) | reinterpret_cast<uintptr_t>(c) | reinterpret_cast<uintptr_t>(d) |
            reinterpret_cast<uintptr_t>(e)) & 15) == 0;
@@ -436,6 +450,20 @@ hipError_t launch_attention_rows_bwd(const void* qkv, int ld_qkv, const void* pr
     return hipGetLastError();
   };
   return seq <= 256 ? go(attention_rows_bwd_kernel<1>, rows_lds(1)) : go(attention_rows_bwd_kernel<2>, rows_lds(2));
+}
+
+bool attention_rows_keys_accepts(const GemmProblem& dv, const GemmProblem& dk) {
+  return small_product_fits(dv) && small_product_fits(dk) && gemm_dma_accepts(dv) && gemm_dma_accepts(dk) && dv.M == dk.M && dv.N == kHeadDim &&
+         dk.N == kHeadDim && dv.batch == dk.batch && dv.batch <= 65535 && (long long)2 * dv.batch * ((dv.M + 63) / 64) <= 0x7FFFFFFF;
+}
+
+hipError_t launch_attention_rows_keys(const GemmProblem& dv, const GemmProblem& dk, hipStream_t stream) {
+  if (!attention_rows_keys_accepts(dv, dk)) return hipErrorInvalidValue;
+  const GemmParams pv = make_params(dv, 64, 64), pk = make_params(dk, 64, 64);
+  constexpr size_t lds_bytes = small_product_lds(64, 64, 1);
+  if (hipError_t e = prepare_rows(attention_rows_keys_kernel, lds_bytes); e != hipSuccess) return e;
+  hipLaunchKernelGGL(attention_rows_keys_kernel, dim3(2 * dv.batch * pv.tiles_m * pv.tiles_n), dim3(256), lds_bytes, stream, pv, pk);
+  return hipGetLastError();
 }
 
 }  // namespace spb

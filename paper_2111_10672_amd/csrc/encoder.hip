@@ -332,13 +332,19 @@ class EncoderModel : public Model {
         g.b_batch = per_head(g.ldb);
         g.C = bf(dqkv, (size_t)col_block * H); g.ldc = 3 * H; g.c_batch = per_head(3 * H);
         g.batch = Z; g.name = name;
-        return gemm(g, s);
+        return g;
       };
       // dV = P^T dctx;  dQ = dS K;  dK = dS^T Q
-      if (int rc = attn_out("attn_bwd_dv", Layout::KRow, w + b.prob, S, per_matrix(), w + p.dctx, 2)) return rc;
+      const GemmProblem dv = attn_out("attn_bwd_dv", Layout::KRow, w + b.prob, S, per_matrix(), w + p.dctx, 2);
+      const GemmProblem dk = attn_out("attn_bwd_dk", Layout::KRow, w + p.dscore, S, per_matrix(), qbase, 1);
       if (!by_rows)
-        if (int rc = attn_out("attn_bwd_dq", Layout::RowK, w + p.dscore, S, per_matrix(), bf(qbase, (size_t)H), 0)) return rc;
-      if (int rc = attn_out("attn_bwd_dk", Layout::KRow, w + p.dscore, S, per_matrix(), qbase, 1)) return rc;
+        if (int rc = gemm(attn_out("attn_bwd_dq", Layout::RowK, w + p.dscore, S, per_matrix(), bf(qbase, (size_t)H), 0), s)) return rc;
+      if (by_rows && attention_rows_keys_accepts(dv, dk)) {
+        if (int rc = run("attention_rows_keys", (double)M * H * 2 * 4 + (double)Z * S * S * 4, s, [&] { return launch_attention_rows_keys(dv, dk, s); })) return rc;
+      } else {
+        if (int rc = gemm(dv, s)) return rc;
+        if (int rc = gemm(dk, s)) return rc;
+      }
       }
       {
         hipStream_t side = fork(s);   // and one for the attention half

@@ -238,6 +238,10 @@ hipError_t launch_attention_rows_fwd(const void* qkv, int ld_qkv, void* prob, vo
 hipError_t launch_attention_rows_bwd(const void* qkv, int ld_qkv, const void* prob, const void* dctx, int ld_ctx, void* dscore, void* dqkv,
                                      int batch, int heads, int seq, int head_dim, float scale, hipStream_t stream);
 
+// dV = P^T dctx and dK = dS^T Q of all heads in one launch, where the small-product kernel would take both.
+bool attention_rows_keys_accepts(const GemmProblem& dv, const GemmProblem& dk);
+hipError_t launch_attention_rows_keys(const GemmProblem& dv, const GemmProblem& dk, hipStream_t stream);
+
 // Server-side aggregation and update (aggregate.hip): for each tensor, g = mean of `count` float32 worker
 // gradients (added in the order given), v = momentum * v + g + weight_decay * w, w = w - rate * v.  w is in
 // param_dtype (bfloat16 parameters are rounded to nearest-even after the float32 update), v is float32.
