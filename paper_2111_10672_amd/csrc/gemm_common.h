@@ -59,6 +59,7 @@ struct GemmParams {
   int slice_in_x;
   ConvGeom conv;
   int tiles_m, tiles_n;
+  int touch_blocks;       // the first workgroups touch the weights they will read (see touch_lines); later ones find them in L2
   BatchStride a_batch, b_batch, c_batch;
 };
 
@@ -138,6 +139,8 @@ inline GemmParams make_params(const GemmProblem& q, int bm, int bn) {
   p.affine_y = q.affine_y; p.ldy = q.ldaffine_y; p.col_partial = q.col_partial;
   if (q.col_partial_rows) *q.col_partial_rows = (q.M + bm - 1) / bm;
   p.k_tiles_per_split = 0; p.slice_in_x = 0;
+  // a forward product: both operands RowK, B the weights.  (Input gradients find theirs near: touching cost them 0 to 2 us.)
+  p.touch_blocks = q.a_layout == Layout::RowK && q.b_layout == Layout::RowK && q.batch == 1 && q.k_splits == 1 ? 512 : 0;
   p.a_batch = q.a_batch; p.b_batch = q.b_batch; p.c_batch = q.c_batch;
   p.tiles_m = (q.M + bm - 1) / bm;
   p.tiles_n = (q.N + bn - 1) / bn;

@@ -16,7 +16,7 @@
 //     of row j, which is the MFMA operand layout.
 // Tile loop: wait for tile t (s_waitcnt vmcnt leaves the younger tiles' loads in flight), one barrier,
 // issue tile t + STAGES - 1 into the buffer tile t - 1 used, multiply tile t.
-#include "gemm_common.h"
+#include "conv3_impl.h"
 
 namespace spb {
 
@@ -26,6 +26,8 @@ hipError_t launch_gemm_dma_kk(const GemmProblem& p, hipStream_t stream);
 hipError_t launch_gemm_dma_conv_fwd(const GemmProblem& p, hipStream_t stream);
 hipError_t launch_gemm_dma_conv_dgrad(const GemmProblem& p, hipStream_t stream);
 hipError_t launch_gemm_dma_conv_wgrad(const GemmProblem& p, hipStream_t stream);
+hipError_t launch_conv3_fwd(const GemmProblem& p, hipStream_t stream);
+hipError_t launch_conv3_dgrad(const GemmProblem& p, hipStream_t stream);
 
 bool gemm_dma_accepts(const GemmProblem& p) {
   if (p.dtype != DType::BF16) return false;
@@ -61,6 +63,7 @@ bool gemm_dma_accepts(const GemmProblem& p) {
 }
 
 hipError_t launch_gemm_dma(const GemmProblem& p, hipStream_t stream) {
+  if (gemm_dma_detail::conv3_accepts(p)) return p.b_gather == Gather::ConvWeightT ? launch_conv3_dgrad(p, stream) : launch_conv3_fwd(p, stream);
   if (p.a_gather == Gather::ConvRows && p.b_gather == Gather::None && p.b_layout == Layout::RowK) return launch_gemm_dma_conv_fwd(p, stream);
   if (p.a_gather == Gather::ConvRows && p.b_gather == Gather::ConvWeightT) return launch_gemm_dma_conv_dgrad(p, stream);
   if (p.a_gather == Gather::None && p.a_layout == Layout::KRow && p.b_gather == Gather::ConvPatchT) return launch_gemm_dma_conv_wgrad(p, stream);

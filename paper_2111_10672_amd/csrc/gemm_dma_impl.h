@@ -150,6 +150,16 @@ struct TileSource {
     }
   }
 
+  // Plain operands: instruction i of the whole tile whose first k-row (or column of k) of this workgroup's panel is at pt.
+  __device__ __forceinline__ void load_whole(int i, const char* pt, char* tile, int wave) const {
+    const uint32_t dst = (uint32_t)(uintptr_t)(lds_ptr_t)(tile + (i * NW + wave) * 1024);
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff[i]), "s"(pt), "s"(dst) : "m0");
+  }
+  __device__ __forceinline__ void issue_at(const char* pt, char* tile, int wave) const {
+#pragma unroll
+    for (int i = 0; i < kInstr; ++i) load_whole(i, pt, tile, wave);
+  }
+
   // Issue tile t (tiles must be issued in increasing order, one after the other).  PARTS > 1: only the
   // instructions i with i % PARTS == part, and the parts of a tile in increasing order.
   template <int PARTS = 1>
@@ -184,8 +194,7 @@ struct TileSource {
 #pragma unroll
         for (int i = 0; i < kInstr; ++i) {
           if (PARTS > 1 && i % PARTS != part) continue;
-          const uint32_t dst = (uint32_t)(uintptr_t)(lds_ptr_t)(tile + (i * NW + wave) * 1024);
-          asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff[i]), "s"(pt), "s"(dst) : "m0");
+          load_whole(i, pt, tile, wave);
         }
       } else {                                                         // the last tile of a k range that ends inside it
 #pragma unroll
@@ -238,6 +247,36 @@ struct TileSource {
   }
 
 };
+
+// Weights on their way from HBM.  A step reads its weights once, and by the next step the cache holds something else, so a forward
+// product finds them in HBM, some 2 us away; a ring that looks one to three tiles ahead then waits for memory at every tile
+// (4096 x 256 x 2304 in 64 x 64 tiles: 12 us with the weights in L2, 24 us in the step).  So before anything else the
+// workgroups that share a panel of B rows and an XCD touch its 128-byte lines, each its part, one word of a line per lane: all
+// of the panel is requested within the first microsecond.  The words go to a corner of LDS that nobody reads; touches return in
+// order with the tile loads behind them, so waiting for those covers them.
+//   base: the panel's first row at the k of line 0; lines from..to of ROWS rows, of which `valid` exist.
+constexpr int kTouchBytes = 256;
+template <int ROWS, int NW>
+__device__ __forceinline__ void touch_lines(const bf16_t* base, int ld, int valid, int from, int to, int share, int sharers, char* corner, int wave, int lane) {
+  const uint32_t dst = (uint32_t)(uintptr_t)(lds_ptr_t)corner;
+#pragma unroll 1
+  for (int l = from * ROWS + (share * NW + wave) * 64; l < to * ROWS; l += sharers * NW * 64) {
+    const int row = (l + lane) % ROWS, line = min((l + lane) / ROWS, to - 1);
+    const uint32_t voff = (uint32_t)min(row, valid - 1) * (uint32_t)ld * 2u + (uint32_t)line * 128u;
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(voff), "s"(base), "s"(dst) : "m0");
+  }
+}
+// The tiles of a panel of B rows that run on one XCD are those of a group of tile rows, or, where the tiles do not divide by the
+// XCDs, one tile row of every group (xcd_tile_grouped).
+template <int BN, int NW>
+__device__ __forceinline__ void touch_panel(const GemmParams& p, int tile_m, int n0, int from, char* corner, int wave, int lane) {
+  if ((int)blockIdx.x >= p.touch_blocks) return;
+  const int group = tile_m / kTileGroupM;
+  const bool runs = p.tiles_m * p.tiles_n % 8 == 0;
+  const int share = runs ? tile_m - group * kTileGroupM : group;
+  const int sharers = runs ? min(p.tiles_m - group * kTileGroupM, kTileGroupM) : (p.tiles_m + kTileGroupM - 1) / kTileGroupM;
+  touch_lines<BN, NW>(static_cast<const bf16_t*>(p.B) + (size_t)n0 * p.ldb, p.ldb, p.N - n0, from, (p.K + kTileK - 1) / kTileK, share, sharers, corner, wave, lane);
+}
 
 // Fetch the MFMA operand of one 32-row fragment for k-group kg (16 values of k): 8 bfloat16 per lane.
 // A KRow fragment is read in assembly and is valid only after fragments_ready().

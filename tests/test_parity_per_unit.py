@@ -142,6 +142,11 @@ def test_every_unit_of_the_small_encoders(name):
     _teacher_forced(name)
 
 
+@pytest.mark.parametrize("name", ["odd_resnet_basic_bf16", "pixel_resnet_basic_bf16"])
+def test_every_unit_of_the_cnns_on_odd_images(name):
+    _teacher_forced(name)
+
+
 @pytest.mark.parametrize("name", ["rows_attention_136_bf16", "rows_attention_256_bf16", "rows_attention_328_bf16", "rows_attention_512_bf16",
                                   "rows_attention_chain_bf16", "rows_attention_chain2_bf16", "long_attention_520_bf16"])
 def test_encoder_layers_of_more_than_128_positions(name):
