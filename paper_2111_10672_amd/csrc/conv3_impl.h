@@ -230,7 +230,7 @@ hipError_t launch_conv3_tile(const GemmProblem& q, hipStream_t stream) {
 // Whether a product is such a convolution, with a patch that leaves room for the smallest tile's ring.
 inline bool conv3_accepts(const GemmProblem& q) {
   const ConvGeom& c = q.conv;
-  return q.a_gather == Gather::ConvRows && c.r == 3 && c.s == 3 && c.stride == 1 && c.pad == 1 && c.sh == c.rh && c.sw == c.rw && c.sc % kTileK == 0 &&
+  return q.a_gather == Gather::ConvRows && c.r == 3 && c.s == 3 && c.stride == 1 && c.pad == 1 && c.pad_w == 1 && c.sh == c.rh && c.sw == c.rw && c.sc % kTileK == 0 &&
          q.K == 9 * c.sc && q.k_splits == 1 && q.batch == 1 && q.M == c.n * c.rh * c.rw &&
          (q.b_gather == Gather::ConvWeightT ? c.w_cout == c.sc && c.w_cin == q.N && q.ldb == q.N : q.b_layout == Layout::RowK && q.b_gather == Gather::None) &&
          conv3_lds(64, 64, 4, c.rw, c.sc) <= 160 * 1024;

@@ -28,6 +28,8 @@ hipError_t launch_gemm_dma_conv_dgrad(const GemmProblem& p, hipStream_t stream);
 hipError_t launch_gemm_dma_conv_wgrad(const GemmProblem& p, hipStream_t stream);
 hipError_t launch_conv3_fwd(const GemmProblem& p, hipStream_t stream);
 hipError_t launch_conv3_dgrad(const GemmProblem& p, hipStream_t stream);
+bool conv_stride2_dgrad_accepts(const GemmProblem& p);
+hipError_t launch_conv_stride2_dgrad(const GemmProblem& p, hipStream_t stream);
 
 bool gemm_dma_accepts(const GemmProblem& p) {
   if (p.dtype != DType::BF16) return false;
@@ -64,6 +66,7 @@ bool gemm_dma_accepts(const GemmProblem& p) {
 
 hipError_t launch_gemm_dma(const GemmProblem& p, hipStream_t stream) {
   if (gemm_dma_detail::conv3_accepts(p)) return p.b_gather == Gather::ConvWeightT ? launch_conv3_dgrad(p, stream) : launch_conv3_fwd(p, stream);
+  if (conv_stride2_dgrad_accepts(p)) return launch_conv_stride2_dgrad(p, stream);
   if (p.a_gather == Gather::ConvRows && p.b_gather == Gather::None && p.b_layout == Layout::RowK) return launch_gemm_dma_conv_fwd(p, stream);
   if (p.a_gather == Gather::ConvRows && p.b_gather == Gather::ConvWeightT) return launch_gemm_dma_conv_dgrad(p, stream);
   if (p.a_gather == Gather::None && p.a_layout == Layout::KRow && p.b_gather == Gather::ConvPatchT) return launch_gemm_dma_conv_wgrad(p, stream);

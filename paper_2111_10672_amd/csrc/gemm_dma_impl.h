@@ -136,7 +136,7 @@ struct TileSource {
           const int a = rem / cg.rw, b = rem - a * cg.rw;
           g0[i] = n * cg.sh * cg.sw;
           g1[i] = cg.transposed ? a + cg.pad : a * cg.stride - cg.pad;
-          g2[i] = cg.transposed ? b + cg.pad : b * cg.stride - cg.pad;
+          g2[i] = cg.transposed ? b + cg.pad_w : b * cg.stride - cg.pad_w;
           tap[i] = k_abs / cg.sc; chan[i] = k_abs - tap[i] * cg.sc;
           if (one_tap) ptr[i] += ((long long)(g0[i] + g1[i] * cg.sw + g2[i]) * cg.sc + k) * 2;
         } else if constexpr (G == Gather::ConvWeightT) {  // row gr = ci; k = (tap, co)
@@ -235,7 +235,7 @@ struct TileSource {
       } else {
         const int r = (tap[i] * (65536 / cg.s + 1)) >> 16, c = tap[i] - r * cg.s;
         const int oh = __float2int_rz(((float)g1[i] + 0.5f) * (1.0f / (float)cg.rw)), ow = g1[i] - oh * cg.rw;
-        const int hi = oh * cg.stride + r - cg.pad, wi = ow * cg.stride + c - cg.pad;
+        const int hi = oh * cg.stride + r - cg.pad, wi = ow * cg.stride + c - cg.pad_w;
         if (in_rows[i] && g0[i] < cg.n && (unsigned)hi < (unsigned)cg.sh && (unsigned)wi < (unsigned)cg.sw)
           src = ptr[i] + ((size_t)((g0[i] * cg.sh + hi) * cg.sw + wi) * cg.sc + chan[i]) * 2;
         const int per_image = cg.rh * cg.rw;
@@ -631,9 +631,11 @@ __device__ __forceinline__ void store_rows_bf16(const GemmParams& p, const float
 // them never waits for a store.  The arithmetic per element is that of store_rows_bf16.
 // wm, tile_m: the wave's place among the WAVES_M waves that share its columns and the tile's row of tiles (the fused
 // affine backward adds its column sums up over those waves and files them under that row).
-template <int WM, int WN, int WAVES_M>
+// MAPPED: the wave's rows are not consecutive rows of the result; rows[r] says which one row r is, -1 that there is none (whole
+// 16-byte pieces of columns and bfloat16 results only).
+template <int WM, int WN, int WAVES_M, bool MAPPED = false>
 __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&acc)[WM / 32][WN / 32], float* stage, int row_base, int col_base, int lane, long long c_offset,
-                                                int wm, int tile_m) {
+                                                int wm, int tile_m, const int* rows = nullptr) {
   constexpr int TM = WM / 32, TN = WN / 32;
   constexpr int kPitch = WN + 4;  // floats; the 16-byte pad staggers the banks of consecutive rows
   float* park_at = stage + (lane & 31) * kPitch + 4 * (lane >> 5);
@@ -644,7 +646,7 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
       for (int g = 0; g < 4; ++g)
         *reinterpret_cast<f32x4*>(park_at + j * 32 + 8 * g) = f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
   };
-  if (p.epilogue == (int)Epilogue::StoreF32) {
+  if (!MAPPED && p.epilogue == (int)Epilogue::StoreF32) {
     constexpr int kPerRow = WN / 4, kRowStep = 64 / kPerRow, kIters = (32 + kRowStep - 1) / kRowStep;
     const int c = (lane % kPerRow) * 4, n = col_base + c, row0 = lane / kPerRow;
     const bool active = n < p.N && lane < kPerRow * kRowStep, whole = n + 4 <= p.N;
@@ -682,11 +684,15 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
   const int last_row = p.M - 1;
   const bool scaled = p.alpha != 1.f;
   const float* from = stage + row0 * kPitch + c;
+  // row r of the wave's tile: does it exist; which row of the result it is; the same, clamped to one that exists
+  auto exists = [&](int r) { return MAPPED ? rows[r] >= 0 : row_base + r < p.M; };
+  auto row_at = [&](int r) { return (size_t)(MAPPED ? rows[r] : row_base + r); };
+  auto near_row = [&](int r) { return MAPPED ? max(rows[r], 0) : min(row_base + r, last_row); };
   auto request = [&](int i, u32x4 (&dst)[kIters]) {
     if (xsrc == nullptr || !active || !whole) return;
 #pragma unroll
     for (int it = 0; it < kIters; ++it)  // from a clamped, always valid row
-      dst[it] = *reinterpret_cast<const u32x4*>(xsrc + (size_t)min(row_base + i * 32 + row0 + it * kRowStep, last_row) * ldx + n);
+      dst[it] = *reinterpret_cast<const u32x4*>(xsrc + (size_t)near_row(i * 32 + row0 + it * kRowStep) * ldx + n);
   };
   // math(v, x, pre): v = alpha * acc on entry and the result on return; x = the per-element tensor's 8 values (only
   // with has_x); pre = what the auxiliary output stores (only worked out with has_aux).  Both flags are template
@@ -702,7 +708,7 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
       park(i);
       if constexpr (kX) { if (i + 1 < TM) request(i + 1, xs[(i + 1) & 1]); }
       if (!active) continue;
-      if (!whole) {  // ragged right edge: element by element
+      if (!MAPPED && !whole) {  // ragged right edge: element by element
 #pragma unroll 1
         for (int row = row0; row < 32 && row_base + i * 32 + row < p.M; row += kRowStep)
           store_ragged(p, stage + row * kPitch + c, 8, row_base + i * 32 + row, n, c_offset);
@@ -714,7 +720,7 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
 #pragma unroll
       for (int it = 0; it < kIters; ++it) {
         const int row = row0 + it * kRowStep;
-        if (row >= 32 || row_base + i * 32 + row >= p.M) break;
+        if (row >= 32 || !exists(i * 32 + row)) break;
         const f32x4 v0 = *reinterpret_cast<const f32x4*>(from + it * kRowStep * kPitch);
         const f32x4 v1 = *reinterpret_cast<const f32x4*>(from + it * kRowStep * kPitch + 4);
         float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]}, x[8], pre[8];
@@ -724,8 +730,14 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
         }
         if constexpr (kX) unpack_bf16x8(xs[i & 1][it], x);
         math(has_x, has_aux, v, x, pre);
-        if constexpr (kAux) *reinterpret_cast<u32x4*>(to_aux + (size_t)it * kRowStep * p.ldaux) = pack_bf16x8(pre);
-        *reinterpret_cast<u32x4*>(to + (size_t)it * kRowStep * p.ldc) = pack_bf16x8(v);
+        if constexpr (MAPPED) {
+          const size_t m = row_at(i * 32 + row);
+          if constexpr (kAux) *reinterpret_cast<u32x4*>(aux + m * p.ldaux + n) = pack_bf16x8(pre);
+          *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(p.C) + c_offset + m * p.ldc + n) = pack_bf16x8(v);
+        } else {
+          if constexpr (kAux) *reinterpret_cast<u32x4*>(to_aux + (size_t)it * kRowStep * p.ldaux) = pack_bf16x8(pre);
+          *reinterpret_cast<u32x4*>(to + (size_t)it * kRowStep * p.ldc) = pack_bf16x8(v);
+        }
       }
     }
   };
@@ -747,7 +759,7 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
     // of unit u + 2 are requested before unit u is worked out and stored: three sets of registers in rotation, and
     // waiting for a chunk never waits for a store issued after it.
     constexpr int kUnits = TM * kIters;
-    auto unit_row = [&](int u) { return row_base + (u / kIters) * 32 + row0 + (u % kIters) * kRowStep; };
+    auto unit_row = [&](int u) { return (u / kIters) * 32 + row0 + (u % kIters) * kRowStep; };
     // Optional: a second gradient that joins the product before the rounding (the shortcut's, where the product is a
     // unit's last input gradient) and a copy of dz itself (what that unit hands down its own shortcut).
     const bf16_t* rsrc = static_cast<const bf16_t*>(p.residual);
@@ -755,7 +767,7 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
     u32x4 ab[3], yb[3], rb[3];
     auto request2 = [&](int u, u32x4& a, u32x4& y, u32x4& r) {
       if (!active) return;
-      const size_t row = (size_t)min(unit_row(u), last_row);   // a clamped, always valid row
+      const size_t row = (size_t)near_row(min(unit_row(u), WM - 1));   // a clamped, always valid row
       a = *reinterpret_cast<const u32x4*>(xsrc + row * ldx + n);
       y = *reinterpret_cast<const u32x4*>(ysrc + row * p.ldy + n);
       if (rsrc) r = *reinterpret_cast<const u32x4*>(rsrc + row * p.ldres + n);
@@ -767,7 +779,7 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
       if constexpr (it == 0) park(i);
       if constexpr (u + 2 < kUnits) request2(u + 2, ab[(u + 2) % 3], yb[(u + 2) % 3], rb[(u + 2) % 3]);
       const int row = row0 + it * kRowStep;
-      if (active && row < 32 && row_base + i * 32 + row < p.M) {
+      if (active && row < 32 && exists(i * 32 + row)) {
         const f32x4 v0 = *reinterpret_cast<const f32x4*>(from + it * kRowStep * kPitch);
         const f32x4 v1 = *reinterpret_cast<const f32x4*>(from + it * kRowStep * kPitch + 4);
         float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]}, a[8], y[8], d[8], o[8];
@@ -791,7 +803,7 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
           s_dz[e] += d[e];
           o[e] = sc[e] * d[e];
         }
-        const size_t m = (size_t)(row_base + i * 32 + row);
+        const size_t m = row_at(i * 32 + row);
         if (dz_out) *reinterpret_cast<u32x4*>(dz_out + m * p.ldaux + n) = pack_bf16x8(d);   // exact: d is bfloat16 already
         *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(p.C) + c_offset + m * p.ldc + n) = pack_bf16x8(o);
       }

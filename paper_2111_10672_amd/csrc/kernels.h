@@ -48,7 +48,7 @@ enum class Gather : int {
 struct ConvGeom {
   int n = 0, sh = 0, sw = 0, sc = 0;  // the gathered tensor: [n, sh, sw, sc], NHWC
   int rh = 0, rw = 0;                 // spatial size of the grid the implicit matrix's pixel index runs over
-  int r = 1, s = 1, stride = 1, pad = 0;
+  int r = 1, s = 1, stride = 1, pad = 0, pad_w = 0;   // pad: above (rows), pad_w: to the left (columns)
   int transposed = 0;                 // 0: source = grid * stride + tap - pad; 1: source = (grid + pad - tap) / stride if divisible
   int w_cin = 0, w_cout = 0;          // ConvWeightT: the weight tensor is [w_cout][r * s][w_cin]
 };
@@ -92,7 +92,7 @@ struct GemmProblem {
   bool share_cu = false;
   float* a_row_sum = nullptr;     // optional [M]: sum_k A(m, k), written once by the tiles of column block 0
   // AffineBwdStore: the affine's input (pre-affine convolution output), the partial column sums [tile rows][2][N]
-  // (room for (M + 63) / 64 tile rows) and where the launcher reports how many tile rows it wrote
+  // (room for (M + 63) / 64 + 3 tile rows: four classes of pixels may each end in a tile of their own) and where the launcher reports how many tile rows it wrote
   const void* affine_y = nullptr;
   int ldaffine_y = 0;
   float* col_partial = nullptr;

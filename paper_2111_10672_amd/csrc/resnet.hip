@@ -211,7 +211,7 @@ class ResnetModel : public Model {
       size_t ap = 0, wp = 0;
       auto see = [&](const Conv& c) {
         ap = std::max(ap, affine_partial_floats(c.out_rows(batch_), c.cout) * 4);
-        ap = std::max(ap, (size_t)((c.out_rows(batch_) + 63) / 64) * 2 * c.cout * 4);   // the fused form: one row of sums per tile row
+        ap = std::max(ap, (size_t)((c.out_rows(batch_) + 63) / 64 + 3) * 2 * c.cout * 4);   // the fused form: one row of sums per tile row
         wp = std::max(wp, (size_t)wgrad_splits(c) * c.cout * c.k_total() * 4);
       };
       see(stem_);
@@ -230,7 +230,7 @@ class ResnetModel : public Model {
   ConvGeom geom(const Conv& c) const {
     ConvGeom g;
     g.n = batch_; g.sh = c.in_h; g.sw = c.in_w; g.sc = c.cin_eff; g.rh = c.out_h; g.rw = c.out_w;
-    g.r = c.k; g.s = c.k; g.stride = c.stride; g.pad = c.pad; g.transposed = 0;
+    g.r = c.k; g.s = c.k; g.stride = c.stride; g.pad = g.pad_w = c.pad; g.transposed = 0;
     return g;
   }
 
@@ -258,7 +258,7 @@ class ResnetModel : public Model {
     if (!pointwise(c)) {
       g.a_gather = Gather::ConvRows; g.b_gather = Gather::ConvWeightT;
       g.conv.n = batch_; g.conv.sh = c.out_h; g.conv.sw = c.out_w; g.conv.sc = c.cout; g.conv.rh = c.in_h; g.conv.rw = c.in_w;
-      g.conv.r = c.k; g.conv.s = c.k; g.conv.stride = c.stride; g.conv.pad = c.pad; g.conv.transposed = 1;
+      g.conv.r = c.k; g.conv.s = c.k; g.conv.stride = c.stride; g.conv.pad = g.conv.pad_w = c.pad; g.conv.transposed = 1;
       g.conv.w_cin = c.cin_eff; g.conv.w_cout = c.cout;
     }
     g.M = (int)c.in_rows(batch_); g.N = c.cin_eff; g.K = c.k * c.k * c.cout;
@@ -289,7 +289,7 @@ class ResnetModel : public Model {
     if (!pointwise(c)) {
       g.a_gather = Gather::ConvRows; g.b_gather = Gather::ConvWeightT;
       g.conv.n = batch_; g.conv.sh = c.out_h; g.conv.sw = c.out_w; g.conv.sc = c.cout; g.conv.rh = c.in_h; g.conv.rw = c.in_w;
-      g.conv.r = c.k; g.conv.s = c.k; g.conv.stride = c.stride; g.conv.pad = c.pad; g.conv.transposed = 1;
+      g.conv.r = c.k; g.conv.s = c.k; g.conv.stride = c.stride; g.conv.pad = g.conv.pad_w = c.pad; g.conv.transposed = 1;
       g.conv.w_cin = c.cin_eff; g.conv.w_cout = c.cout;
     }
     g.M = (int)c.in_rows(batch_); g.N = c.cin_eff; g.K = c.k * c.k * c.cout;
