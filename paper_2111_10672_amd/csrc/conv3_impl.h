@@ -211,6 +211,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv3_kernel(GemmParam
       if (t + 1 < n_tiles) static_for<4>([&](auto q) { step(t, std::integral_constant<int, decltype(q)::value + 4>{}); });
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  // the reads behind the last tile have come in too: until here their registers belong to nobody else
+#pragma unroll
+  for (int q = 0; q < kSets; ++q) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(fa[q][i]));
+#pragma unroll
+    for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(fb[q][j]));
+  }
   __syncthreads();   // every wave has its last fragments in registers: patch and ring are dead
   float* stage = reinterpret_cast<float*>(lds) + wave * (32 * (WN + 4));
   store_wave_tile<WM, WN, WAVES_M>(p, acc, stage, m0 + wm * WM, n0 + wn * WN, lane, 0, wm, tile_m);
