@@ -154,9 +154,9 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t stream);
 size_t affine_partial_floats(long long rows, int channels);
 // One small fixed-order reduction: kPairs = the column sums of an affine backward pass (partial [count][2][width] ->
 // out [width], out_b [width]); kSlices / kSlices4 = the k-slices of a weight gradient (see launch_splitk_reduce;
-// kSlices4 counts in groups of four floats).  blocks = workgroups it takes.
+// kSlices4 and, for many slices, kSlices4Wide count in groups of four floats).  blocks = workgroups it takes.
 struct ReduceTask {
-  enum Kind { kPairs = 0, kSlices4 = 1, kSlices = 2 };
+  enum Kind { kPairs = 0, kSlices4 = 1, kSlices = 2, kSlices4Wide = 3 };
   int kind = kPairs;
   const float* partial = nullptr;
   int count = 0, width = 0;
