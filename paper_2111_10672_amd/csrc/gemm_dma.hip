@@ -67,6 +67,7 @@ bool gemm_dma_accepts(const GemmProblem& p) {
 hipError_t launch_gemm_dma(const GemmProblem& p, hipStream_t stream) {
   if (gemm_dma_detail::conv3_accepts(p)) return p.b_gather == Gather::ConvWeightT ? launch_conv3_dgrad(p, stream) : launch_conv3_fwd(p, stream);
   if (conv_stride2_dgrad_accepts(p)) return launch_conv_stride2_dgrad(p, stream);
+  if (conv3_wgrad_accepts(p)) return launch_conv3_wgrad(p, stream);
   if (p.a_gather == Gather::ConvRows && p.b_gather == Gather::None && p.b_layout == Layout::RowK) return launch_gemm_dma_conv_fwd(p, stream);
   if (p.a_gather == Gather::ConvRows && p.b_gather == Gather::ConvWeightT) return launch_gemm_dma_conv_dgrad(p, stream);
   if (p.a_gather == Gather::None && p.a_layout == Layout::KRow && p.b_gather == Gather::ConvPatchT) return launch_gemm_dma_conv_wgrad(p, stream);

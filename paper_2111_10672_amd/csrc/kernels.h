@@ -122,6 +122,11 @@ inline hipError_t raise_lds_limit(const void* kernel, size_t lds_bytes) {
 hipError_t launch_gemm(const GemmProblem& p, hipStream_t stream);
 bool gemm_dma_accepts(const GemmProblem& p);
 hipError_t launch_gemm_dma(const GemmProblem& p, hipStream_t stream);
+// The weight gradient of a 3 x 3 convolution of stride 1 with all taps in one workgroup (conv3_wgrad.hip): into how many slices it cuts the
+// pixels, 0 where the convolution is not one it takes (channels not whole 64-groups, another kernel size or stride, rows too wide).
+int conv3_wgrad_splits(const ConvGeom& c, int c_out);
+bool conv3_wgrad_accepts(const GemmProblem& p);
+hipError_t launch_conv3_wgrad(const GemmProblem& p, hipStream_t stream);
 // float32 products of small dense layers (latency-bound): see gemm_f32_small.hip
 bool gemm_f32_small_accepts(const GemmProblem& p);
 hipError_t launch_gemm_f32_small(const GemmProblem& p, hipStream_t stream);

@@ -139,6 +139,7 @@ class ResnetModel : public Model {
     return m;
   }
   int wgrad_splits(const Conv& c) const {
+    if (const int s = conv3_wgrad_splits(geom(c), c.cout)) return s;
     const long tiles = (long)((c.cout + 127) / 128) * ((c.k_total() + 127) / 128);
     const long k_tiles = (long)((c.out_rows(batch_) + 63) / 64);
     // k-slices for about 192 workgroups, not one per CU: the weight gradients run beside the input-gradient chain of the
