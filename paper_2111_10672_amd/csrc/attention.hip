@@ -190,29 +190,29 @@ __global__ __launch_bounds__(256) void attention_fwd_kernel(const bf16_t* __rest
 //   dP = dctx V^T;  dS = P * (dP - rowsum(dP * P)) * scale (rounded to bfloat16, as the unfused path stores it);
 //   dQ = dS K;  dK = dS^T Q;  dV = P^T dctx.
 // Phase 1 is row-wise: wave w forms dP and dS of its 32 queries in the accumulators (P comes straight from HBM in
-// that layout) and writes dS once, into a workgroup-wide KRow tile (k = query) that dK reads; its own dQ product
-// takes dS from the registers.  After one barrier, phase 2: wave w produces rows 32 w .. of dQ, dK and dV, three
-// products of 16 MFMAs each, with K, Q and dctx read through transposing LDS reads and P as a KRow tile that came
-// in by direct-to-LDS loads.  LDS: dctx twice (RowK for dP, KRow for dV), V (RowK), K, Q (KRow), P (KRow), the KRow dS
-// tile, which takes over the space of dctx-RowK and V once dP is done, and 8 KB per wave through which results leave.
-constexpr int kDsK = kSeqMax * 2 * kSeqMax;  // dS as KRow tiles: two k tiles of 64 queries x 128 key rows
-constexpr int kBwdLds = kQBytes /*dctx RowK*/ + kQBytes /*V RowK*/ + 3 * kVBytes /*dctx, K, Q as KRow*/ + kDsK /*P KRow*/ + 4 * kPWave;
+// that layout); its own dQ product takes dS from the registers.  dK and dV read dS and P as KRow tiles (k = query) that the waves write
+// from their registers, one after the other into the same 32 KB that dctx and V filled before; dctx comes in a second time, as a
+// KRow tile, into the place of K once dQ is done.  What leaves is rounded before it is parked, 4 KB per wave.  That makes 80 KB, so
+// two workgroups share a CU (with every tile in a place of its own it was 144 KB and a CU held one).  Alone, 12 heads of 128 positions: 32
+// sequences 19.9 -> 16.1 us, 64 sequences 32.4 -> 27.2; up to 256 workgroups level (16 sequences 9.4).
+constexpr int kDsK = kSeqMax * 2 * kSeqMax;  // dS or P as KRow tiles: two k tiles of 64 queries x 128 key rows
+constexpr int kOutWave = 32 * kRowBytes;     // a wave's 32 rows x 64 bfloat16 on their way out
+constexpr int kBwdLds = kDsK /*dctx and V RowK, then dS, then P*/ + 2 * kVBytes /*K, then dctx; Q; KRow*/ + 4 * kOutWave;
 static_assert(2 * kQBytes == kDsK, "the KRow dS tile reuses the dctx and V tiles of phase 1");
+static_assert(2 * kBwdLds <= 160 * 1024, "two workgroups share a CU");
 
-__global__ __launch_bounds__(256) void attention_bwd_kernel(const bf16_t* __restrict__ qkv, int ld_qkv, const bf16_t* __restrict__ prob,
-                                                            const bf16_t* __restrict__ dctx, int ld_ctx, bf16_t* __restrict__ dqkv,
-                                                            int heads, int seq, float scale) {
+__global__ __launch_bounds__(256, 2) void attention_bwd_kernel(const bf16_t* __restrict__ qkv, int ld_qkv, const bf16_t* __restrict__ prob,
+                                                               const bf16_t* __restrict__ dctx, int ld_ctx, bf16_t* __restrict__ dqkv,
+                                                               int heads, int seq, float scale) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  char* dctx_r = lds;                           // phase 1; then, with v_r, the KRow dS tile
+  char* dctx_r = lds;                           // phase 1; then, with v_r, the KRow tile of dS, then of P
   char* v_r = lds + kQBytes;
-  char* ds_k = lds;
-  char* dctx_k = lds + 2 * kQBytes;
-  char* k_k = dctx_k + kVBytes;
+  char* krow = lds;
+  char* k_k = lds + 2 * kQBytes;                // K, then dctx
   char* q_k = k_k + kVBytes;
-  char* p_k = q_k + kVBytes;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  char* out_stage = p_k + kDsK + wave * kPWave;   // this wave's 32 x 64 floats on their way out
+  char* out_stage = q_k + kVBytes + wave * kOutWave;
   const int z = blockIdx.x, b = z / heads, h = z - b * heads;
   const int hidden = heads * kHeadDim;
   const bf16_t* base = qkv + (size_t)b * seq * ld_qkv + h * kHeadDim;
@@ -222,22 +222,17 @@ __global__ __launch_bounds__(256) void attention_bwd_kernel(const bf16_t* __rest
 
   {
     TileSource<kSeqMax, Layout::RowK, Gather::None, 4> src_dc, src_v;
-    TileSource<kHeadDim, Layout::KRow, Gather::None, 4> src_dck, src_k, src_q;
-    TileSource<kSeqMax, Layout::KRow, Gather::None, 4> src_p;
+    TileSource<kHeadDim, Layout::KRow, Gather::None, 4> src_k, src_q;
     src_dc.init(dc, ld_ctx, 0, seq, wave, lane, 0, none);
     src_v.init(base + 2 * hidden, ld_qkv, 0, seq, wave, lane, 0, none);
-    src_dck.init(dc, ld_ctx, 0, kHeadDim, wave, lane, 0, none);
     src_k.init(base + hidden, ld_qkv, 0, kHeadDim, wave, lane, 0, none);
     src_q.init(base, ld_qkv, 0, kHeadDim, wave, lane, 0, none);
-    src_p.init(pz, seq, 0, seq, wave, lane, 0, none);
     src_dc.issue(0, kHeadDim, dctx_r, wave, ld_ctx, none);
     src_v.issue(0, kHeadDim, v_r, wave, ld_qkv, none);
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      src_dck.issue(t, seq, dctx_k + t * (kHeadDim * kRowBytes), wave, ld_ctx, none);
       src_k.issue(t, seq, k_k + t * (kHeadDim * kRowBytes), wave, ld_qkv, none);
       src_q.issue(t, seq, q_k + t * (kHeadDim * kRowBytes), wave, ld_qkv, none);
-      src_p.issue(t, seq, p_k + t * (kSeqMax * kRowBytes), wave, seq, none);
     }
   }
   // P of this wave's queries, four consecutive keys at a time, straight from HBM while the tiles are in flight.
@@ -303,49 +298,40 @@ __global__ __launch_bounds__(256) void attention_bwd_kernel(const bf16_t* __rest
       for (int e = 0; e < 8; ++e)
         ds[j][e] = pack_bf16(pv[j][2 * e] * (dp[j][2 * e] - dot) * scale, pv[j][2 * e + 1] * (dp[j][2 * e + 1] - dot) * scale);
   }
-  __syncthreads();  // all waves have read dctx_r and v_r: their space becomes the KRow dS tile
-  // dS as KRow tiles (k = query, rows = keys) for dK = dS^T Q: two k tiles of 64 queries, 128 key rows of 2 bytes per
+  __syncthreads();  // all waves have read dctx_r and v_r: their space becomes the KRow tile
+  // dS, and later P, as KRow tiles (k = query, rows = keys): two k tiles of 64 queries, 128 key rows of 2 bytes per
   // k-row, the 16-byte chunks of k-row kk rotated by 2 (kk % 8), which keeps these 8-byte writes (32 k-rows at once)
   // and the transposing reads below (4 k-rows at once) off each other's banks.
+  auto write_krow = [&](auto&& words) {   // words(j, g): keys 32 j + 8 g + 4 hh + (0..3)
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int key = 32 * j + 8 * g + 4 * hh, kk = q & 63;
-      const int pc = ((key >> 3) + dsk_rot(kk)) & (kSeqMax / 8 - 1);
-      *reinterpret_cast<uint2*>(ds_k + (q >> 6) * (kSeqMax * kRowBytes) + kk * (kSeqMax * 2) + pc * 16 + (key & 7) * 2) = uint2{ds[j][2 * g], ds[j][2 * g + 1]};
-    }
-  __syncthreads();
+      for (int g = 0; g < 4; ++g) {
+        const int key = 32 * j + 8 * g + 4 * hh, kk = q & 63;
+        const int pc = ((key >> 3) + dsk_rot(kk)) & (kSeqMax / 8 - 1);
+        *reinterpret_cast<uint2*>(krow + (q >> 6) * (kSeqMax * kRowBytes) + kk * (kSeqMax * 2) + pc * 16 + (key & 7) * 2) = words(j, g);
+      }
+  };
+  write_krow([&](int j, int g) { return uint2{ds[j][2 * g], ds[j][2 * g + 1]}; });
 
   // phase 2: three [32 x 64] outputs per wave, multiplied with the operands exchanged so that four consecutive
-  // accumulators are four consecutive features of one row: a result parks in the wave's staging rows with 16-byte
-  // writes (the 16 chunks of a 256-byte row permuted by row % 16, which keeps both the writes, 32 rows at once, and
-  // the row-wise reads off each other's banks) and leaves as whole 128-byte rows.
-  float* stage = reinterpret_cast<float*>(out_stage);
-  constexpr int kPitch = kHeadDim;
+  // accumulators are four consecutive features of one row: a result parks in the wave's staging rows with 8-byte
+  // writes and leaves as whole 128-byte rows.
   auto write_out = [&](f32x16 (&o)[2], int col_block) {
     asm volatile("" ::: "memory");
     const int prow = lane & 31;
 #pragma unroll
     for (int n = 0; n < 2; ++n)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int chunk = (8 * n + 2 * g + hh) ^ (prow & 15);
-        *reinterpret_cast<f32x4*>(stage + prow * kPitch + chunk * 4) = f32x4{o[n][4 * g], o[n][4 * g + 1], o[n][4 * g + 2], o[n][4 * g + 3]};
-      }
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<uint2*>(out_stage + lds_offset(prow, 4 * n + g) + hh * 8) = uint2{pack_bf16(o[n][4 * g], o[n][4 * g + 1]), pack_bf16(o[n][4 * g + 2], o[n][4 * g + 3])};
     asm volatile("" ::: "memory");
     bf16_t* out = dqkv + (size_t)b * seq * ld_qkv + col_block * hidden + h * kHeadDim;
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
-      const int row = it * 8 + (lane >> 3), c = (lane & 7) * 2;
-      if (q0 + row < seq) {
-        float v[8];
-        const f32x4 v0 = *reinterpret_cast<const f32x4*>(stage + row * kPitch + (c ^ (row & 15)) * 4);
-        const f32x4 v1 = *reinterpret_cast<const f32x4*>(stage + row * kPitch + ((c + 1) ^ (row & 15)) * 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { v[e] = v0[e]; v[4 + e] = v1[e]; }
-        *reinterpret_cast<u32x4*>(out + (size_t)(q0 + row) * ld_qkv + c * 4) = pack_bf16x8(v);
-      }
+      const int row = it * 8 + (lane >> 3), c = lane & 7;
+      if (q0 + row < seq)
+        *reinterpret_cast<u32x4*>(out + (size_t)(q0 + row) * ld_qkv + c * 8) = *reinterpret_cast<const u32x4*>(out_stage + lds_offset(row, c));
     }
     asm volatile("" ::: "memory");
   };
@@ -374,20 +360,23 @@ __global__ __launch_bounds__(256) void attention_bwd_kernel(const bf16_t* __rest
       for (int n = 0; n < 2; ++n)
         acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bb[n]), __builtin_bit_cast(bf16x8, a[0]), acc[n], 0, 0, 0);
     }
-  write_out(acc, 0);
-  // dK[key, d] = sum_q dS[q, key] Q[q, d]   and   dV[key, d] = sum_q P[q, key] dctx[q, d]: rows = this wave's 32 keys
+  __syncthreads();   // dS is whole, and every wave is done with K: dctx comes into its place
+  {
+    TileSource<kHeadDim, Layout::KRow, Gather::None, 4> src_dck;
+    src_dck.init(dc, ld_ctx, 0, kHeadDim, wave, lane, 0, none);
 #pragma unroll
-  for (int which = 0; which < 2; ++which) {
-    const char* a_tile = which == 0 ? ds_k : p_k;
-    const char* b_tile = which == 0 ? q_k : dctx_k;
+    for (int t = 0; t < 2; ++t) src_dck.issue(t, seq, k_k + t * (kHeadDim * kRowBytes), wave, ld_ctx, none);
+  }
+  write_out(acc, 0);
+  // out[key, d] = sum_q tile[q, key] b[q, d]: rows = this wave's 32 keys
+  auto key_product = [&](const char* b_tile) {
     zero(acc);
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         u32x4 a[1], bb[2];
-        a[0] = which == 0 ? read_krow<kSeqMax, true, false>(a_tile + kt * (kSeqMax * kRowBytes), q0, g, lane)
-                          : read_fragment<kSeqMax, Layout::KRow>(a_tile + kt * (kSeqMax * kRowBytes), q0, g, lane);
+        a[0] = read_krow<kSeqMax, true, false>(krow + kt * (kSeqMax * kRowBytes), q0, g, lane);
         bb[0] = read_fragment<kHeadDim, Layout::KRow>(b_tile + kt * (kHeadDim * kRowBytes), 0, g, lane);
         bb[1] = read_fragment<kHeadDim, Layout::KRow>(b_tile + kt * (kHeadDim * kRowBytes), 32, g, lane);
         fragments_ready(a, bb);
@@ -395,8 +384,14 @@ __global__ __launch_bounds__(256) void attention_bwd_kernel(const bf16_t* __rest
         for (int j = 0; j < 2; ++j)
           acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bb[j]), __builtin_bit_cast(bf16x8, a[0]), acc[j], 0, 0, 0);
       }
-    write_out(acc, 1 + which);
-  }
+  };
+  key_product(q_k);   // dK[key, d] = sum_q dS[q, key] Q[q, d]
+  __syncthreads();    // every wave is done with dS: P comes into its place
+  write_krow([&](int j, int g) { return pw[j][g]; });
+  write_out(acc, 1);
+  wait_loads_and_barrier<0>();   // P and dctx are whole
+  key_product(k_k);   // dV[key, d] = sum_q P[q, key] dctx[q, d]
+  write_out(acc, 2);
 }
 
 }  // namespace
