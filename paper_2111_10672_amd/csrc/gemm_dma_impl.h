@@ -1397,9 +1397,9 @@ __device__ __forceinline__ void small_product(const GemmParams& p, int block, in
   else store_rows_bf16<BN, NW>(p, stage, m0 + row_base, n0, lane, batch_offset_z(p.c_batch, z), kRows, BM * kPitch, &cols, xpre);
 }
 
-// Ring depth per wave: alone on its CU a workgroup's rings fill 128 KiB; the workgroups of a pair launch take
+// Ring depth per wave: alone on its CU a workgroup's rings fill up to 150 KiB; the workgroups of a pair launch take
 // half, so that one of each product fits on a CU and their fixed latencies overlap.
-constexpr int small_ring_depth(int bm, int bn, bool paired) { return (int)((paired ? 64 : 128) * 1024 / (4 * (bm + bn) * kRowBytes)); }
+constexpr int small_ring_depth(int bm, int bn, bool paired) { return (int)((paired ? 64 : 150) * 1024 / (4 * (bm + bn) * kRowBytes)); }
 
 template <int BM, int BN, Layout LA, Layout LB>
 __global__ __launch_bounds__(256) void gemm_bf16_small_kernel(GemmParams p) {
@@ -1505,7 +1505,13 @@ hipError_t launch_layouts(const GemmProblem& q, hipStream_t stream) {
   auto tiles = [&](int tm, int tn) { return tile_count(q, tm, tn); };
   if constexpr (GA == Gather::None && GB == Gather::None) {
     if (small_product_fits(q) && q.epilogue != Epilogue::AffineBwdStore) {   // (the small kernel's epilogue has no column sums)
-      if (small_product_tile64(q)) return launch_small<64, 64, LA, LB>(q, stream);
+      if (small_product_tile64(q)) {
+        // 64 x 64 tiles that would leave a quarter of the chip or more idle: 32 x 64, if those make one round.  A CU then pulls three
+        // quarters of the bytes, and the ring holds three tiles of a wave's quarter instead of two (504 rows, 768 columns, in the encoder
+        // step of 7 x 72 tokens, 42 such products: 1442 -> 1358 us the step).
+        if (tiles(64, 64) < 192 && tiles(32, 64) <= 256) return launch_small<32, 64, LA, LB>(q, stream);
+        return launch_small<64, 64, LA, LB>(q, stream);
+      }
       return launch_small<32, 32, LA, LB>(q, stream);
     }
   }
