@@ -389,7 +389,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) { return bf16_
 
 // Epilogue.  Each wave parks 32 rows of its WM x WN accumulator tile at a time in its own LDS region (the tile
 // ring is dead by then) and reads them back row by row, so that bias, mask and result move in 16-byte pieces
-// along n.  LDS operations of one wave complete in order, so the pieces need no barrier between them.
+// along n.  LDS operations of one wave complete in order, so the pieces need no wait between them.
 // The row loops are deliberately not unrolled: an unrolled epilogue is tens of thousands of instructions,
 // which no longer fit the instruction cache and cost more time than the tile loop itself.
 
@@ -623,7 +623,7 @@ __device__ __forceinline__ void store_rows_bf16(const GemmParams& p, const float
 // 16-byte write per four accumulators, and reads them back so that consecutive lanes hold consecutive 16-byte
 // pieces of a row: loads of the per-element tensor and stores of the result are whole 64-byte segments per four
 // lanes (stores scattered one lane per row were measured 2-3 x slower: every lane becomes a request of its own at the
-// L2).  LDS operations of one wave complete in order, so no barrier separates the pieces.  A wave issues about 1.7 k
+// L2).  LDS operations of one wave complete in order, so no wait separates the pieces (only the lanes are kept together).  A wave issues about 1.7 k
 // instructions at 4 cycles each if this is written as a loop over rows with the mode tested per element (8 us per
 // product, as much as 12 k-tiles of the tile loop); hence: the row loop is unrolled with the mode decided outside
 // it, a lane's column and its per-column operands never change, a row's address is the previous one plus a constant,
@@ -645,7 +645,12 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         *reinterpret_cast<f32x4*>(park_at + j * 32 + 8 * g) = f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+    // All lanes park a piece together, after all have read the one before: without a convergent operation here the compiler may
+    // run the pieces of the lanes that store nothing (a wave partly beyond the last column) in a branch of their own ahead of
+    // the others', and the first piece's rows parked by those lanes were then read with the second piece's values.
+    if constexpr (TM > 1) __builtin_amdgcn_wave_barrier();
   };
+  auto piece_done = [&]() { if constexpr (TM > 1) __builtin_amdgcn_wave_barrier(); };
   if (!MAPPED && p.epilogue == (int)Epilogue::StoreF32) {
     constexpr int kPerRow = WN / 4, kRowStep = 64 / kPerRow, kIters = (32 + kRowStep - 1) / kRowStep;
     const int c = (lane % kPerRow) * 4, n = col_base + c, row0 = lane / kPerRow;
@@ -659,13 +664,13 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
     const float* from = stage + row0 * kPitch + c;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
+      if (i > 0) piece_done();
       park(i);
-      if (!active) continue;
       float* to = static_cast<float*>(p.C) + c_offset + (size_t)(row_base + i * 32 + row0) * p.ldc + n;
 #pragma unroll
       for (int it = 0; it < kIters; ++it) {
         const int row = row0 + it * kRowStep, m = row_base + i * 32 + row;
-        if (row >= 32 || m >= p.M) break;
+        if (!active || row >= 32 || m >= p.M) break;
         const f32x4 v = *reinterpret_cast<const f32x4*>(from + it * kRowStep * kPitch);
         if (whole) *reinterpret_cast<f32x4*>(to + (size_t)it * kRowStep * p.ldc) = v * p.alpha + b;
         else store_ragged(p, from + it * kRowStep * kPitch, 4, m, n, c_offset);   // straight from the parked row (a copy would live in scratch memory)
@@ -705,6 +710,7 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
     if constexpr (kX) request(0, xs[0]);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
+      if (i > 0) piece_done();
       park(i);
       if constexpr (kX) { if (i + 1 < TM) request(i + 1, xs[(i + 1) & 1]); }
       if (!active) continue;
@@ -776,7 +782,10 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
     if constexpr (kUnits > 1) request2(1, ab[1], yb[1], rb[1]);
     static_for<kUnits>([&](auto u_c) {
       constexpr int u = decltype(u_c)::value, i = u / kIters, it = u % kIters;
-      if constexpr (it == 0) park(i);
+      if constexpr (it == 0) {
+        if constexpr (i > 0) piece_done();
+        park(i);
+      }
       if constexpr (u + 2 < kUnits) request2(u + 2, ab[(u + 2) % 3], yb[(u + 2) % 3], rb[(u + 2) % 3]);
       const int row = row0 + it * kRowStep;
       if (active && row < 32 && exists(i * 32 + row)) {

@@ -125,7 +125,8 @@ def _teacher_forced(name, units_to_run=None, seed=0, perturbed=True, check_hande
     return report
 
 
-@pytest.mark.parametrize("name", ["cfg1", "cfg2", "ragged_mlp_bf16", "ragged_mlp_f32", "many_class_mlp_bf16", "tall_mlp_bf16"])
+@pytest.mark.parametrize("name", ["cfg1", "cfg2", "ragged_mlp_bf16", "ragged_mlp_f32", "many_class_mlp_bf16", "tall_mlp_bf16",
+                                  "part_wave_mlp_bf16"])
 def test_every_unit_of_the_perceptrons(name):
     _teacher_forced(name, perturbed=(name != "cfg2"))
     if name == "cfg2":

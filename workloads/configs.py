@@ -56,6 +56,8 @@ CONFIGS = {
     "big_tile_mlp_bf16": dict(family="mlp", dtype="bf16", batch=8192, dims=[512, 4096, 512, 16], depths=[2, 3]),
     # 333 rows: forward, input-gradient and weight-gradient products in 32 x 64 tiles of the small-product kernel
     "tall_mlp_bf16": dict(family="mlp", dtype="bf16", batch=333, dims=[768, 512, 1096, 1104, 13], depths=[2, 4]),
+    # 3072 x 1000 logits in 128 x 128 tiles of eight waves: the last wave of the columns holds 8 of its 32
+    "part_wave_mlp_bf16": dict(family="mlp", dtype="bf16", batch=3072, dims=[72, 1000], depths=[0, 1]),
     # several thousand classes: the loss kernel that keeps a whole row of logits in the registers of one workgroup
     "many_class_mlp_bf16": dict(family="mlp", dtype="bf16", batch=37, dims=[72, 40, 4999], depths=[0, 1, 2]),
     "many_class_mlp_f32": dict(family="mlp", dtype="f32", batch=21, dims=[36, 2050], depths=[0, 1]),
