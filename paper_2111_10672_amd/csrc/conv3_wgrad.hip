@@ -248,15 +248,20 @@ __global__ __launch_bounds__(512) void conv3_wgrad_kernel(GemmParams p, int x_ro
 
 using namespace gemm_dma_detail;
 
-// Slices of the pixel range for about kWgradBlocks workgroups (beside the input-gradient chain of the other stream), at least 4 steps each, at
-// most 48 (the table); 0: not this kernel's convolution.
+// Slices of the pixel range for about kWgradBlocks workgroups (beside the input-gradient chain of the other stream), at least 256 pixels each
+// (the zeros not counted: no more slices than the gathering product takes of a model small enough for the library's own workspace), and
+// so many that one has at most 48 steps (the table).  0: not this kernel's convolution, or so many pixels that the table asks for more than
+// kWgradMostBlocks workgroups: the partial results of each are 147 KB, in twelve buffers (128 channels of 1.6 million pixels: 321 MB a
+// buffer).  256 images of 64 x 64 pixels and 64 channels take 352.
+constexpr int kWgradMostBlocks = 512;
 int conv3_wgrad_splits(const ConvGeom& c, int c_out) {
   if (c.r != 3 || c.s != 3 || c.stride != 1 || c.pad != 1 || c.pad_w != 1 || c.transposed || c.sh != c.rh || c.sw != c.rw || c.sc % 64 || c_out % 64) return 0;
   if ((long long)c.n * (c.rh + 1) * (c.rw + 1) > 0x7FFFFFFFLL - 4096 || kTileK + wgrad_x_rows(c.rw) > 64 * kWgradLoads || wgrad_lds(c, 48) > 160 * 1024) return 0;
-  const int tiles = wgrad_tiles(c), blocks = c.sc / 64 * (c_out / 64);
-  int s = std::min((kWgradBlocks + blocks - 1) / blocks, std::max(tiles / 4, 1));
-  s = std::max(s, (tiles + 47) / 48);
-  return std::min(s, 65535);
+  const int tiles = wgrad_tiles(c), blocks = c.sc / 64 * (c_out / 64), least = (tiles + 47) / 48;
+  const int pixel_tiles = (int)(((long long)c.n * c.rh * c.rw + kTileK - 1) / kTileK);
+  const int s = std::min((kWgradBlocks + blocks - 1) / blocks, std::max(pixel_tiles / 4, 1));
+  if (least <= s) return s;
+  return (long long)least * blocks <= kWgradMostBlocks ? least : 0;
 }
 
 bool conv3_wgrad_accepts(const GemmProblem& q) {

@@ -149,6 +149,26 @@ def test_static_workspace_entry_point_checks_its_arguments_on_the_host():
         spb.spb_model_destroy(big)
 
 
+def _plain_cnn(batch, image, stem, stage_blocks, stage_widths):
+    stem = dict(kernel=3, stride=1, pad=1, pool=False) if stem == 3 else dict(kernel=7, stride=2, pad=3, pool=True)
+    return dict(family="resnet_basic", dtype="bf16", batch=batch, image=[image, image, 3], stem=dict(stem, width=stage_widths[0]),
+                stage_blocks=stage_blocks, stage_widths=stage_widths, classes=10)
+
+
+# A weight gradient's slices are partial results in the workspace: they leave a small model in the library's own one, and do not grow with
+# the pixels of a large one (its activations are 9 tenths of it).
+@pytest.mark.parametrize("cfg,most", [
+    (_plain_cnn(30, 8, 3, [1, 2], [32, 64]), spb.SPB_STATIC_WORKSPACE_BYTES),
+    (_plain_cnn(395, 253, 7, [2, 3, 3, 2], [128, 256, 512, 1024]), 58_200_000_000),
+])
+def test_weight_gradient_slices_are_bounded(cfg, most):
+    m = spb.spb_model_create(spb.desc_from_config(cfg))
+    try:
+        assert spb.spb_workspace_size(m, spb.spb_num_units(m)) <= most
+    finally:
+        spb.spb_model_destroy(m)
+
+
 @pytest.mark.parametrize("name", ["cfg2", "cfg3", "cfg5", "small_resnet_bottleneck_bf16"])
 def test_unit_views_lie_inside_the_workspace_and_have_the_units_shapes(name):
     cfg = wl.get_config(name)
