@@ -166,12 +166,13 @@ hipError_t launch_stride2(const GemmProblem& q, hipStream_t stream) {
 }  // namespace
 }  // namespace gemm_dma_detail
 
-// Whole 64-channel groups of the gradient (a tile of k lies on one tap) and whole 16-byte pieces of columns.
+// Whole 64-channel groups of the gradient (a tile of k lies on one tap) and whole 16-byte pieces of columns; column sums need room for
+// the classes' own last tiles.
 bool conv_stride2_dgrad_accepts(const GemmProblem& q) {
   const ConvGeom& c = q.conv;
   return q.a_gather == Gather::ConvRows && q.b_gather == Gather::ConvWeightT && c.transposed && c.stride == 2 && c.sc % gemm_dma_detail::kTileK == 0 &&
          c.w_cout == c.sc && c.w_cin == q.N && q.ldb == q.N && q.N % 8 == 0 && q.M == c.n * c.rh * c.rw && q.k_splits == 1 && q.batch == 1 &&
-         (q.epilogue == Epilogue::BiasAct || q.epilogue == Epilogue::AffineBwdStore);
+         (q.epilogue == Epilogue::BiasAct || (q.epilogue == Epilogue::AffineBwdStore && q.col_partial_spare >= 3));
 }
 
 // As for the other gathering products: 64-wide tiles for 64 columns; 128 x 128 while that fills the chip; else 64 x 64.

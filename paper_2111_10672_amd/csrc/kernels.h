@@ -92,10 +92,12 @@ struct GemmProblem {
   bool share_cu = false;
   float* a_row_sum = nullptr;     // optional [M]: sum_k A(m, k), written once by the tiles of column block 0
   // AffineBwdStore: the affine's input (pre-affine convolution output), the partial column sums [tile rows][2][N]
-  // (room for (M + 63) / 64 + 3 tile rows: four classes of pixels may each end in a tile of their own) and where the launcher reports how many tile rows it wrote
+  // (room for (M + 63) / 64 tile rows and col_partial_spare more: taken by parity, four classes of pixels may each end in a tile of
+  // their own) and where the launcher reports how many tile rows it wrote
   const void* affine_y = nullptr;
   int ldaffine_y = 0;
   float* col_partial = nullptr;
+  int col_partial_spare = 0;
   int* col_partial_rows = nullptr;
   const char* name = "gemm";
 };

@@ -126,9 +126,10 @@ class ResnetModel : public Model {
     size_t g[kSetBase + kSets * kPerSet];
     static constexpr int kReduceSlots = 4;   // a unit has at most three convolutions and a projection
     size_t affine_partial[kSets][kReduceSlots], wgrad_partial[kSets][kReduceSlots];   // per set of units
+    int spare_rows;   // of column sums, beside one per 64 rows: for input gradients by pixel parity
     size_t total;
   };
-  static constexpr int kFwdPool = 8;
+  static constexpr int kFwdPool = 8, kSpareRows = 3;
 
   size_t act_bytes(long long rows, int c) const { return (size_t)rows * c * 2; }
   size_t max_act_bytes() const {
@@ -150,8 +151,18 @@ class ResnetModel : public Model {
     return (int)std::max(1L, std::min(s, 1024L));
   }
 
+  // A model that fits the library's own workspace only without the spare rows does without them (its stride-2 input gradients are then
+  // the gathering product's).  They are at most 48 KB of each of the buffers: 2048 channels.
   Plan plan(int k) const {
+    const Plan p = plan(k, kSpareRows);
+    constexpr size_t kMost = (size_t)Plan::kSets * Plan::kReduceSlots * (kSpareRows * 2 * 2048 * 4);
+    if (p.total <= (size_t)SPB_STATIC_WORKSPACE_BYTES || p.total > (size_t)SPB_STATIC_WORKSPACE_BYTES + kMost) return p;
+    const Plan q = plan(k, 0);
+    return q.total <= (size_t)SPB_STATIC_WORKSPACE_BYTES ? q : p;
+  }
+  Plan plan(int k, int spare_rows) const {
     Plan p;
+    p.spare_rows = spare_rows;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes, 256); return o; };
     const int cut = num_units - k;
@@ -212,7 +223,7 @@ class ResnetModel : public Model {
       size_t ap = 0, wp = 0;
       auto see = [&](const Conv& c) {
         ap = std::max(ap, affine_partial_floats(c.out_rows(batch_), c.cout) * 4);
-        ap = std::max(ap, (size_t)((c.out_rows(batch_) + 63) / 64 + 3) * 2 * c.cout * 4);   // the fused form: one row of sums per tile row
+        ap = std::max(ap, (size_t)((c.out_rows(batch_) + 63) / 64 + spare_rows) * 2 * c.cout * 4);   // the fused form: one row of sums per tile row
         wp = std::max(wp, (size_t)wgrad_splits(c) * c.cout * c.k_total() * 4);
       };
       see(stem_);
@@ -284,7 +295,7 @@ class ResnetModel : public Model {
   // and dz_out (optional) receives that masked sum: the form for a unit's LAST input gradient, which then also does
   // the affine pass at the output of the unit below.
   int conv_dgrad_affine(const Conv& c, const void* dy, const void* w, const Conv& below, const void* act, const void* y, void* dy_below,
-                        float* partial, hipStream_t s, const void* residual = nullptr, void* dz_out = nullptr) {
+                        float* partial, int spare_rows, hipStream_t s, const void* residual = nullptr, void* dz_out = nullptr) {
     GemmProblem g;
     g.dtype = dtype; g.a_layout = Layout::RowK; g.b_layout = Layout::KRow; g.epilogue = Epilogue::AffineBwdStore;
     if (!pointwise(c)) {
@@ -296,7 +307,7 @@ class ResnetModel : public Model {
     g.M = (int)c.in_rows(batch_); g.N = c.cin_eff; g.K = c.k * c.k * c.cout;
     g.A = dy; g.lda = g.K; g.B = w; g.ldb = c.cin_eff; g.C = dy_below; g.ldc = c.cin_eff;
     g.mask = act; g.ldmask = c.cin_eff; g.affine_y = y; g.ldaffine_y = c.cin_eff; g.col_scale = param_ptrs[below.scale];
-    g.col_partial = partial;
+    g.col_partial = partial; g.col_partial_spare = spare_rows;
     g.residual = residual; g.ldres = c.cin_eff; g.aux_out = dz_out; g.ldaux = c.cin_eff;
     g.col_partial_rows = &fused_tile_rows_;   // (a member: the product may be replayed later from its recorded description)
     g.name = "conv_dgrad_affine";
@@ -482,7 +493,7 @@ class ResnetModel : public Model {
         if (int rc = wait_mark(s, reader[next_slot])) return rc;   // whoever read that slot is done with it
         reader[next_slot] = -1;
         // the gradient at convolution j's input only feeds the affine + ReLU below: one pass where the product can take it
-        const int fused = conv_dgrad_affine(b.convs[j], dy, param_ptrs[b.convs[j].w], b.convs[j - 1], in_j, w + u.conv[j - 1].y, dy_next, apart(j - 1), s);
+        const int fused = conv_dgrad_affine(b.convs[j], dy, param_ptrs[b.convs[j].w], b.convs[j - 1], in_j, w + u.conv[j - 1].y, dy_next, apart(j - 1), p.spare_rows, s);
         if (fused < 0) return fused;
         if (fused > 0) {
           if (int rc = conv_dgrad(b.convs[j], dy, param_ptrs[b.convs[j].w], nullptr, da, s)) return rc;
@@ -521,7 +532,7 @@ class ResnetModel : public Model {
         if (i + 2 < (int)blocks_.size())
           if (int rc = wait_mark(s, unit_done[i + 2])) return rc;   // the unit that last used that set
         const int fused = conv_dgrad_affine(b.convs[0], dy, param_ptrs[b.convs[0].w], below.convs[last_below], x_in, w + p.unit[i].conv[last_below].y,
-                                            G(set_below, 0), apart_of(set_below, last_below), s, shortcut_grad, G(set_below, 4));
+                                            G(set_below, 0), apart_of(set_below, last_below), p.spare_rows, s, shortcut_grad, G(set_below, 4));
         if (fused < 0) return fused;
         if (fused > 0) { set_error("resnet: the last input gradient of unit %d cannot carry the affine pass below it", i + 1); return SPB_ERR_INVALID_ARG; }
         incoming_fused = true;

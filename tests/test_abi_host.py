@@ -169,6 +169,15 @@ def test_weight_gradient_slices_are_bounded(cfg, most):
         spb.spb_model_destroy(m)
 
 
+# Column sums of input gradients by pixel parity take three rows more: a model that fits the library's own workspace only without them does so.
+def test_a_model_at_the_library_workspaces_limit_fits():
+    m = spb.spb_model_create(spb.desc_from_config(_plain_cnn(5, 8, 3, [1, 1], [64, 128])))
+    try:
+        assert spb.SPB_STATIC_WORKSPACE_BYTES - 40_000 < spb.spb_workspace_size(m, 2) <= spb.SPB_STATIC_WORKSPACE_BYTES
+    finally:
+        spb.spb_model_destroy(m)
+
+
 @pytest.mark.parametrize("name", ["cfg2", "cfg3", "cfg5", "small_resnet_bottleneck_bf16"])
 def test_unit_views_lie_inside_the_workspace_and_have_the_units_shapes(name):
     cfg = wl.get_config(name)
