@@ -154,6 +154,32 @@ def test_encoder_layers_of_more_than_128_positions(name):
     _teacher_forced(name, units_to_run=[1])
 
 
+# The logits of a wave that holds 26 of its 32 columns: their weights are scaled up until they take most of the
+# softmax, so that a few rows of that wave stored in each other's place show in the gradients of those columns.
+@pytest.mark.parametrize("name", ["part_wave_encoder_bf16"])
+def test_vocabulary_columns_of_a_part_filled_wave(name):
+    cfg = wl.get_config(name)
+    whole = cfg["vocab"] // 32 * 32
+    params, batch = wl.make_params(cfg, 0, True), wl.make_batch(cfg, 0)
+    batch["labels"] = batch["labels"] % whole
+    params["head.vocab.weight"][whole:] *= 64.0
+    model = spb.SpbModel(cfg, params)
+    u = model.n_units - 1
+    try:
+        model.step({n: t.cuda() for n, t in batch.items()}, 1)
+        torch.cuda.synchronize()
+        x_u = model.read_view(spb.spb_unit_io(model.handle, 1, u)[0], batch).numpy()
+        got = {n: g.double().cpu().numpy() for n, g in model.grad_dict(1).items()}
+    finally:
+        model.close()
+    p64 = {n: oracle_step._as_f64(v) for n, v in params.items()}
+    unit = oracle_step.build_units(cfg)[u]
+    unit.forward(x_u, p64, oracle.round_to_bf16, {n: oracle_step._as_f64(v) for n, v in batch.items()})
+    ref, _ = unit.backward(None, p64, oracle.round_to_bf16, need_input_grad=False)
+    for n in ("head.vocab.weight", "head.vocab.bias"):
+        _check(f"{name} {n}, columns from {whole}", got[n][whole:], ref[n][whole:], TOL["bf16"], [])
+
+
 # Full size: the classifier, the top units, and one unit of every kind of shape further down (a stride-2 block with a
 # projection, the first block behind the stem, the stem itself / the embedding).
 @pytest.mark.parametrize("name,units", [("cfg3", [9, 8, 7, 5, 3, 1, 0]), ("cfg4", [17, 16, 14, 10]), ("cfg5", [13, 12, 11, 1, 0])])

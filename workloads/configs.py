@@ -58,6 +58,9 @@ CONFIGS = {
     "tall_mlp_bf16": dict(family="mlp", dtype="bf16", batch=333, dims=[768, 512, 1096, 1104, 13], depths=[2, 4]),
     # 3072 x 1000 logits in 128 x 128 tiles of eight waves: the last wave of the columns holds 8 of its 32
     "part_wave_mlp_bf16": dict(family="mlp", dtype="bf16", batch=3072, dims=[72, 1000], depths=[0, 1]),
+    # 75 x 24634 logits in 193 tiles of 128 x 128: the last wave of the columns holds 26 of its 32
+    "part_wave_encoder_bf16": dict(family="encoder", dtype="bf16", batch=2, seq=40, layers=1, hidden=64, heads=1, ffn=64, vocab=24634, loss_rows=75,
+                                   depths=[0, 1]),
     # several thousand classes: the loss kernel that keeps a whole row of logits in the registers of one workgroup
     "many_class_mlp_bf16": dict(family="mlp", dtype="bf16", batch=37, dims=[72, 40, 4999], depths=[0, 1, 2]),
     "many_class_mlp_f32": dict(family="mlp", dtype="f32", batch=21, dims=[36, 2050], depths=[0, 1]),
@@ -75,7 +78,6 @@ CONFIGS = {
                                   ffn=192, vocab=61, loss_rows=13, depths=[0, 1, 2, 3]),
     "wide_encoder_1024_bf16": dict(family="encoder", dtype="bf16", batch=1, seq=40, layers=1, hidden=1024, heads=16,
                                    ffn=128, vocab=37, loss_rows=9, depths=[0, 1, 2, 3]),
-    # a vocabulary large enough for the head's input gradient to be cut into k-slices and for the long-row loss kernel
     # 3x3 convolutions of whole 64-channel groups on odd images, down to single pixels: rows resident in LDS
     "odd_resnet_basic_bf16": dict(family="resnet_basic", dtype="bf16", batch=5, image=[13, 13, 3],
                                   stem=dict(kernel=3, stride=1, pad=1, pool=False, width=64), stage_blocks=[1, 1, 1, 1], stage_widths=[64, 128, 192, 256], classes=7),
@@ -92,6 +94,7 @@ CONFIGS = {
     "rows_attention_chain2_bf16": dict(family="encoder", dtype="bf16", batch=16, seq=264, layers=1, hidden=512, heads=8, ffn=64, vocab=97, loss_rows=60),
     # longer than those rows: batched products and softmax passes
     "long_attention_520_bf16": dict(family="encoder", dtype="bf16", batch=1, seq=520, layers=1, hidden=64, heads=1, ffn=64, vocab=97, loss_rows=60),
+    # a vocabulary large enough for the head's input gradient to be cut into k-slices and for the long-row loss kernel
     "big_vocab_encoder_bf16": dict(family="encoder", dtype="bf16", batch=2, seq=16, layers=1, hidden=64, heads=1,
                                    ffn=72, vocab=2311, loss_rows=9, depths=[0, 1, 2, 3]),
     "tiny_resnet_basic": dict(family="resnet_basic", dtype="bf16", batch=2, image=[6, 6, 3],
