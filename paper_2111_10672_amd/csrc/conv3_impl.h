@@ -235,29 +235,67 @@ hipError_t launch_conv3_tile(const GemmProblem& q, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Whether a product is such a convolution, with a patch that leaves room for the smallest tile's ring.
-inline bool conv3_accepts(const GemmProblem& q) {
-  const ConvGeom& c = q.conv;
-  return q.a_gather == Gather::ConvRows && c.r == 3 && c.s == 3 && c.stride == 1 && c.pad == 1 && c.pad_w == 1 && c.sh == c.rh && c.sw == c.rw && c.sc % kTileK == 0 &&
-         q.K == 9 * c.sc && q.k_splits == 1 && q.batch == 1 && q.M == c.n * c.rh * c.rw &&
-         (q.b_gather == Gather::ConvWeightT ? c.w_cout == c.sc && c.w_cin == q.N && q.ldb == q.N : q.b_layout == Layout::RowK && q.b_gather == Gather::None) &&
-         conv3_lds(64, 64, 4, c.rw, c.sc) <= 160 * 1024;
-}
-
 // Tile choice, from every tile timed on the shapes of 32- and 224-pixel networks (us, forward; the gathering kernel's time in
 // front):  one nearly full round of 128 x 128 (12544 x 256 x 2304: 34 -> 19, 128 x 64 26), with eight waves, since a workgroup is alone
 // on its CU (four waves of 64 x 64: 20);  for 64 columns 256 x 64, two workgroups a CU (131072 x 64 x 576: 26 -> 16, 128 x 64 18);
 // 128 x 64 while that fills the chip (8192 x 256 x 2304: 25 -> 14, 64 x 64 15);  64 x 128 where the patch of 128 pixels does not
 // fit (3136 x 512 x 4608: 46 -> 24, 64 x 64 36);  else 64 x 64 (4096 x 256 x 2304: 21 -> 12, 2048 x 512 x 4608: 37 -> 18).
 // A ring of three 64-k tiles of weights does where it leaves room for another workgroup; lone small tiles take four.
-template <Layout LB>
-hipError_t launch_conv3(const GemmProblem& q, hipStream_t stream) {
+struct Conv3Tile { int bm, bn, stages; };
+inline Conv3Tile conv3_tile(const GemmProblem& q) {
   auto tiles = [&](int tm, int tn) { return tile_count(q, tm, tn); };
   auto fits = [&](int bm, int bn, int stages) { return conv3_lds(bm, bn, stages, q.conv.rw, q.conv.sc) <= 160 * 1024; };
-  if (q.N > 64 && tiles(128, 128) >= 160 && tiles(128, 128) <= 256 && fits(128, 128, 3)) return launch_conv3_tile<128, 128, 3, 4, 2, 3, LB>(q, stream);
-  if (q.N <= 64 && tiles(256, 64) >= 448 && fits(256, 64, 3)) return launch_conv3_tile<256, 64, 3, 8, 1, 3, LB>(q, stream);
-  if (tiles(128, 64) >= 160 && fits(128, 64, 3)) return launch_conv3_tile<128, 64, 3, 4, 1, 3, LB>(q, stream);
-  if (q.N > 64 && tiles(64, 128) >= 160 && fits(64, 128, 4)) return launch_conv3_tile<64, 128, 4, 2, 2, 3, LB>(q, stream);
+  if (q.N > 64 && tiles(128, 128) >= 160 && tiles(128, 128) <= 256 && fits(128, 128, 3)) return {128, 128, 3};
+  if (q.N <= 64 && tiles(256, 64) >= 448 && fits(256, 64, 3)) return {256, 64, 3};
+  if (tiles(128, 64) >= 160 && fits(128, 64, 3)) return {128, 64, 3};
+  if (q.N > 64 && tiles(64, 128) >= 160 && fits(64, 128, 4)) return {64, 128, 4};
+  return {64, 64, 4};
+}
+
+// Whether that is faster than the gathering kernels.  The resident rows leave a CU to one workgroup from 192 channels on (128 where
+// the image is wide), and from the third round of such workgroups on the gathering kernels' larger tiles catch up: alone, forward,
+// gathering kernel against resident rows, 12032 x 256 x 2304 (one round) 37 and 24 us, 20480 x 256 x 2304 (three) 49 and 45, 25088 (four) 50 and
+// 57, 65024 (eight, where 256 x 256 tiles make one) 79 and 112; 16384 x 512 x 4608 in 64 x 64 tiles (eight) 88 and 217.  Two workgroups a CU cover
+// each other: 399840 x 128 x 1152 174 and 149, 524288 x 64 x 576 96 and 60.  So: where a round or two is all there is, where two share a
+// CU, and for up to 64 columns, which the gathering kernels take in narrow tiles (256000 x 64 x 2304: 137 and 123); but not where the patch is
+// more than four times the tile (10000 x 128 x 1152, 100 pixels a row: 19 and 21; 80000 x 64 x 576, 200 a row: 25 and 30).  For the rest by the time
+// both should take, from lines through 180 timed shapes: per round a fixed part and one per 64 of k, for the tile that launch_layouts
+// would choose; wrong by at most 6 % on those shapes.
+inline bool conv3_pays(const GemmProblem& q) {
+  const Conv3Tile t = conv3_tile(q);
+  const int width = q.conv.rw, channels = q.conv.sc;
+  const bool lone = 2 * conv3_lds(t.bm, t.bn, t.stages, width, channels) > 160 * 1024;
+  auto rounds = [&](int tm, int tn, int at_once) { return (double)((tile_count(q, tm, tn) + at_once - 1) / at_once); };
+  const double own_rounds = rounds(t.bm, t.bn, lone ? 256 : 512);
+  if (own_rounds <= 1) return true;
+  if (lone && patch_rows(t.bm, width) > 4 * t.bm) return false;
+  if (own_rounds <= 2 || q.N <= 64 || (!lone && (q.N <= 128 || channels <= 64))) return true;
+  const double k = q.K / (double)kTileK;
+  const double own = own_rounds * ((lone ? 1.8 + 0.38 * k : 0.75 * k) + 0.02 * std::max(patch_rows(t.bm, width) - 160, 0));
+  const long t192 = tile_count(q, 256, 192), t256 = tile_count(q, 256, 256), t128 = tile_count(q, 128, 128);
+  if (q.M >= 256 && t192 >= 176 && t192 <= 256 && (long)((q.N + 191) / 192) * 192 * 20 <= (long)q.N * 21) return own <= 25 + 1.07 * k;
+  if (q.M >= 256 && q.N >= 256 && t256 >= 176 && (t256 <= 256 || t256 >= 448)) return own <= rounds(256, 256, 256) * (25 + 1.45 * k);
+  if (t128 > 256) return own <= (rounds(128, 128, 512) + 0.15) * (12 + 0.83 * k);
+  if (t128 >= 192) return own <= 12 + 0.74 * k;
+  return own_rounds <= (q.b_gather == Gather::ConvWeightT ? 3 : 2);   // 64 x 64 gathered: 5120 x 512 x 4608 forward 63 and 74, input gradient 72 and 64
+}
+
+// Whether a product is such a convolution, with a patch that leaves room for the smallest tile's ring.
+inline bool conv3_accepts(const GemmProblem& q) {
+  const ConvGeom& c = q.conv;
+  return q.a_gather == Gather::ConvRows && c.r == 3 && c.s == 3 && c.stride == 1 && c.pad == 1 && c.pad_w == 1 && c.sh == c.rh && c.sw == c.rw && c.sc % kTileK == 0 &&
+         q.K == 9 * c.sc && q.k_splits == 1 && q.batch == 1 && q.M == c.n * c.rh * c.rw &&
+         (q.b_gather == Gather::ConvWeightT ? c.w_cout == c.sc && c.w_cin == q.N && q.ldb == q.N : q.b_layout == Layout::RowK && q.b_gather == Gather::None) &&
+         conv3_lds(64, 64, 4, c.rw, c.sc) <= 160 * 1024 && conv3_pays(q);
+}
+
+template <Layout LB>
+hipError_t launch_conv3(const GemmProblem& q, hipStream_t stream) {
+  const Conv3Tile t = conv3_tile(q);
+  if (t.bm == 256) return launch_conv3_tile<256, 64, 3, 8, 1, 3, LB>(q, stream);
+  if (t.bm == 128 && t.bn == 128) return launch_conv3_tile<128, 128, 3, 4, 2, 3, LB>(q, stream);
+  if (t.bm == 128) return launch_conv3_tile<128, 64, 3, 4, 1, 3, LB>(q, stream);
+  if (t.bn == 128) return launch_conv3_tile<64, 128, 4, 2, 2, 3, LB>(q, stream);
   return launch_conv3_tile<64, 64, 4, 2, 2, LB == Layout::RowK ? 7 : 3, LB>(q, stream);
 }
 
