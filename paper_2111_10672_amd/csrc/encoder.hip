@@ -80,7 +80,7 @@ class EncoderModel : public Model {
     p.layer.assign(NL, scratch);
     for (int u = 0; u <= NL; ++u) p.xout[u] = (u + 1 >= cut) ? take(mh) : ping[u & 1];  // kept if the unit above reads it in its backward pass
     for (int i = 0; i < NL; ++i) if (i + 1 >= cut) p.layer[i] = take_layer();
-    p.scores = take(zss * 4);
+    p.scores = scores_in_memory() ? take(zss * 4) : 0;
     p.y = take((size_t)R * H * 2); p.statsf = take((size_t)R * 8); p.logits = take((size_t)R * ldz() * 4);
     p.row_loss = take((size_t)R * 4); p.dlogits = take((size_t)R * ldv() * 2);
     p.dy = p.partial = p.partial_bytes = p.dx[0] = p.dx[1] = p.dF[0] = p.dF[1] = p.dv = p.dh[0] = p.dh[1] = p.dctx = p.dscore = p.dqkv[0] = p.dqkv[1] = p.du = 0;
@@ -100,6 +100,8 @@ class EncoderModel : public Model {
   }
 
   size_t workspace_size(int k) const override { return plan(k).total; }
+  // Attention as products and softmax passes: only then do the float32 scores go to memory.
+  bool scores_in_memory() const { return !attention_fused_accepts(S, D, 3 * H, H) && !attention_rows_accepts(S, D, 3 * H, H); }
 
   // ---- product helpers -------------------------------------------------------------------------
   GemmProblem linear(const void* a, int lda, int rows, const void* w, int n_out, int n_in, const void* bias, void* c, int ldc) const {

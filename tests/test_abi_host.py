@@ -178,6 +178,22 @@ def test_a_model_at_the_library_workspaces_limit_fits():
         spb.spb_model_destroy(m)
 
 
+# Heads of 64 features and up to 512 positions keep their scores on chip: the float32 scores (4 bytes for each of the probabilities, which
+# take 2) have no place in the workspace.  Longer rows, and other head sizes, have them there.
+@pytest.mark.parametrize("seq,heads,in_memory", [(512, 1, False), (256, 1, False), (128, 1, False), (520, 1, True), (256, 2, True)])
+def test_scores_take_memory_only_where_they_are_written(seq, heads, in_memory):
+    rows, hidden, batch = 8 * seq, 64, 8
+    cfg = dict(family="encoder", dtype="bf16", batch=batch, seq=seq, layers=1, hidden=hidden, heads=heads, ffn=64, vocab=16, loss_rows=1)
+    m = spb.spb_model_create(spb.desc_from_config(cfg))
+    try:
+        prob = 2 * batch * heads * seq * seq
+        others = rows * hidden * 2 * 12 + 100_000     # two outputs in turn, and u, qkv (3), ctx, h, v, z1, f of a layer, and the small ones
+        assert spb.spb_workspace_size(m, 0) <= prob + others + (2 * prob if in_memory else 0)
+        assert spb.spb_workspace_size(m, 0) >= prob + (2 * prob if in_memory else 0)
+    finally:
+        spb.spb_model_destroy(m)
+
+
 @pytest.mark.parametrize("name", ["cfg2", "cfg3", "cfg5", "small_resnet_bottleneck_bf16"])
 def test_unit_views_lie_inside_the_workspace_and_have_the_units_shapes(name):
     cfg = wl.get_config(name)
