@@ -44,6 +44,7 @@ class EncoderModel : public Model {
     }
     add("head.ln.weight", NL + 1, {H}); add("head.ln.bias", NL + 1, {H});
     add("head.vocab.weight", NL + 1, {V, H}); add("head.vocab.bias", NL + 1, {V});
+    for (const ParamInfo& p : params) param_bytes_ += (size_t)p.numel() * dtype_size(p.dtype);
     param_ptrs.assign(params.size(), nullptr);
     grad_ptrs.assign(params.size(), nullptr);
   }
@@ -108,6 +109,7 @@ class EncoderModel : public Model {
     GemmProblem g;  // C[rows, n_out] = a[rows, n_in] * w[n_out, n_in]^T + bias
     g.dtype = dtype; g.a_layout = Layout::RowK; g.b_layout = Layout::RowK; g.epilogue = Epilogue::BiasAct;
     g.M = rows; g.N = n_out; g.K = n_in; g.A = a; g.lda = lda; g.B = w; g.ldb = n_in; g.bias = bias; g.C = c; g.ldc = ldc;
+    g.b_in_hbm = weights_in_hbm_;
     g.name = "gemm_bf16_fwd";
     return g;
   }
@@ -138,6 +140,7 @@ class EncoderModel : public Model {
     char* w = static_cast<char*>(wsp);
     ids_ = static_cast<const int32_t*>(x);
     rows_ = loss_rows;
+    weights_in_hbm_ = weights_driven_out(param_bytes_, p.total);
     const float inv_sqrt_d = 1.f / std::sqrt((float)D);
     const double mh = (double)M * H * 2;
     if (int rc = run("embedding_fwd", 2 * mh, s, [&] {
@@ -402,6 +405,8 @@ class EncoderModel : public Model {
   int B = 0, S = 0, NL = 0, H = 0, NH = 0, D = 0, F = 0, V = 0, R = 0, M = 0, Z = 0;
   const int32_t* ids_ = nullptr;
   const int32_t* rows_ = nullptr;
+  size_t param_bytes_ = 0;
+  bool weights_in_hbm_ = false;   // by the time the step that is being enqueued reads them
 };
 
 }  // namespace

@@ -140,7 +140,7 @@ inline GemmParams make_params(const GemmProblem& q, int bm, int bn) {
   if (q.col_partial_rows) *q.col_partial_rows = (q.M + bm - 1) / bm;
   p.k_tiles_per_split = 0; p.slice_in_x = 0;
   // a forward product: both operands RowK, B the weights.  (Input gradients find theirs near: touching cost them 0 to 2 us.)
-  p.touch_blocks = q.a_layout == Layout::RowK && q.b_layout == Layout::RowK && q.batch == 1 && q.k_splits == 1 ? 512 : 0;
+  p.touch_blocks = q.b_in_hbm && q.a_layout == Layout::RowK && q.b_layout == Layout::RowK && q.batch == 1 && q.k_splits == 1 ? 512 : 0;
   p.a_batch = q.a_batch; p.b_batch = q.b_batch; p.c_batch = q.c_batch;
   p.tiles_m = (q.M + bm - 1) / bm;
   p.tiles_n = (q.N + bn - 1) / bn;

@@ -250,10 +250,13 @@ struct TileSource {
 
 // Weights on their way from HBM.  A step reads its weights once, and by the next step the cache holds something else, so a forward
 // product finds them in HBM, some 2 us away; a ring that looks one to three tiles ahead then waits for memory at every tile
-// (4096 x 256 x 2304 in 64 x 64 tiles: 12 us with the weights in L2, 24 us in the step).  So before anything else the
+// (4096 x 256 x 2304 in 64 x 64 tiles: 12 us with the weights in L2, 24 us in the step).  So the
 // workgroups that share a panel of B rows and an XCD touch its 128-byte lines, each its part, one word of a line per lane: all
-// of the panel is requested within the first microsecond.  The words go to a corner of LDS that nobody reads; touches return in
-// order with the tile loads behind them, so waiting for those covers them.
+// of the panel is requested within the first microsecond.  The words go to a corner of LDS that nobody reads.  The resident-row
+// kernel touches first and waits for everything before its loop; the ring kernels touch behind the loads of their first tiles.  Loads
+// return in order, so their wait for a tile, which counts the loads that may still be out, then covers that tile and all but the
+// youngest touches too: the first tile waits for the panel.  That is what touching costs where the weights are near, and why it is for
+// those that are not (b_in_hbm).
 //   base: the panel's first row at the k of line 0; lines from..to of ROWS rows, of which `valid` exist.
 constexpr int kTouchBytes = 256;
 template <int ROWS, int NW>
@@ -266,8 +269,7 @@ __device__ __forceinline__ void touch_lines(const bf16_t* base, int ld, int vali
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(voff), "s"(base), "s"(dst) : "m0");
   }
 }
-// Forward products in tiles of 128 x 128 and more (in the encoder step of 4096 rows the 768-column ones went from 25.9 to 23.7 us, on the
-// bottleneck CNN 17.7 -> 17.0 and 11.0 -> 10.1).  Smaller tiles run several to a CU or have their whole k in flight: 64 x 64 over k =
+// Forward products in tiles of 128 x 128 and more (touching_pays).  Smaller tiles run several to a CU or have their whole k in flight: 64 x 64 over k =
 // 768 lost 1 us of 10 to the touching itself, the small-product kernel was level.
 template <int BM, int BN, Layout LA, Layout LB>
 constexpr bool touches = LA == Layout::RowK && LB == Layout::RowK && BM >= 128 && BN >= 128;
@@ -1462,6 +1464,16 @@ hipError_t launch_small(const GemmProblem& q, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Where the large tiles of a product whose weights lie in HBM do better without touching them (forward passes of encoders, alone and
+// followed by their backward pass): 256 x 192 tiles that do not divide by the XCDs, whose panels two or three workgroups share (3720 rows:
+// +0.5 to +2.3 % a step); lone 128 x 128 tiles with eight panels or more whose rows lie a power of two of 2 KB and more apart, so that the lanes'
+// lines meet on few channels (4096 x 1024 over k = 1024 and 4096: +0.4 to +2 %; 768 columns over 768 and 3072, 512 over 512 and 2048: -0.2 to
+// -1.2 %; 12544 x 256 over 1024 in the bottleneck CNN: -0.3 %).
+inline bool touching_pays(const GemmProblem& q, int bm, int bn, bool lone) {
+  if (bn == 192) return tile_count(q, bm, bn) % 8 == 0;
+  return !(lone && bm == 128 && q.N >= 1024 && q.K >= 1024 && (q.K & (q.K - 1)) == 0);
+}
+
 template <int BM, int BN, int STAGES, int WAVES_M, int WAVES_N, Layout LA, Layout LB, Gather GA, Gather GB>
 hipError_t launch_tile(const GemmProblem& q, hipStream_t stream) {
   GemmParams p = make_params(q, BM, BN);
@@ -1477,6 +1489,7 @@ hipError_t launch_tile(const GemmProblem& q, hipStream_t stream) {
   auto kernel = gemm_bf16_dma_kernel<BM, BN, STAGES, WAVES_M, WAVES_N, LA, LB, GA, GB>;
   if (lds_bytes > 64 * 1024)
     if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kernel), lds_bytes); e != hipSuccess) return e;
+  if constexpr (touches<BM, BN, LA, LB>) { if (!touching_pays(q, BM, BN, false)) p.touch_blocks = 0; }
   p.slice_in_x = q.k_splits > 1 && q.k_splits % 8 == 0 && p.tiles_m * p.tiles_n <= 65535;
   const dim3 grid = p.slice_in_x ? dim3(grid_y, p.tiles_m * p.tiles_n) : dim3(p.tiles_m * p.tiles_n, grid_y);
   hipLaunchKernelGGL(kernel, grid, dim3(64 * WAVES_M * WAVES_N), lds_bytes, stream, p);
@@ -1498,6 +1511,7 @@ hipError_t launch_tile_pipe(const GemmProblem& q, hipStream_t stream) {
   auto kernel = gemm_bf16_pipe_kernel<BM, BN, STAGES, WAVES_M, WAVES_N, KGB, LA, LB, GA, GB>;
   if (lds_bytes > 64 * 1024)
     if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kernel), lds_bytes); e != hipSuccess) return e;
+  if constexpr (touches<BM, BN, LA, LB>) { if (!touching_pays(q, BM, BN, true)) p.touch_blocks = 0; }
   p.slice_in_x = q.k_splits > 1 && q.k_splits % 8 == 0 && p.tiles_m * p.tiles_n <= 65535;
   const dim3 grid = p.slice_in_x ? dim3(grid_y, p.tiles_m * p.tiles_n) : dim3(p.tiles_m * p.tiles_n, grid_y);
   hipLaunchKernelGGL(kernel, grid, dim3(64 * WAVES_M * WAVES_N), lds_bytes, stream, p);

@@ -90,6 +90,7 @@ struct GemmProblem {
   // The product runs beside workgroups of another stream: where the tile choice is between one 128 x 128 workgroup
   // that takes most of a CU's LDS and one that leaves room for a neighbour, take the latter.
   bool share_cu = false;
+  bool b_in_hbm = false;          // B is weights that other traffic has driven out of the caches: see touch_lines
   float* a_row_sum = nullptr;     // optional [M]: sum_k A(m, k), written once by the tiles of column block 0
   // AffineBwdStore: the affine's input (pre-affine convolution output), the partial column sums [tile rows][2][N]
   // (room for (M + 63) / 64 tile rows and col_partial_spare more: taken by parity, four classes of pixels may each end in a tile of
@@ -122,6 +123,11 @@ inline hipError_t raise_lds_limit(const void* kernel, size_t lds_bytes) {
 // Checks shapes and alignment on the host, then enqueues one kernel.  Returns hipSuccess,
 // hipErrorInvalidValue for a problem the kernel cannot take, or the launch error.
 hipError_t launch_gemm(const GemmProblem& p, hipStream_t stream);
+// Whether a step over so many bytes of weights and workspace drives the weights out of the 256 MB cache from one use to the next.  Encoders
+// of 1 to 12 layers of 256 to 1024 features, step with and without touching in the large tiles: below 340 MB 0 to +3.5 % (1 layer of 1024 and 48 x
+// 128 tokens, 336 MB), above it level to -10 % (12 of 640 and 64 x 128, 386 MB).  Perceptrons never gain, up to 800 MB: +2 to +7 % up to 200
+// MB, level beyond.  Convolutional networks gain at any size, most in their 3 x 3 convolutions.
+inline bool weights_driven_out(size_t weights, size_t workspace) { return weights + workspace >= (size_t)340 * 1000 * 1000; }
 bool gemm_dma_accepts(const GemmProblem& p);
 hipError_t launch_gemm_dma(const GemmProblem& p, hipStream_t stream);
 // The weight gradient of a 3 x 3 convolution of stride 1 with all taps in one workgroup (conv3_wgrad.hip): into how many slices it cuts the

@@ -260,6 +260,7 @@ class ResnetModel : public Model {
     g.aux_out = y_keep; g.ldaux = c.cout; g.aux_raw = 1;
     g.residual = residual; g.ldres = c.cout;
     g.act = relu ? Act::Relu : Act::None;
+    g.b_in_hbm = true;
     g.name = "conv_fwd";
     return gemm(g, s);
   }
