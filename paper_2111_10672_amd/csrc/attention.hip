@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256) void attention_fwd_kernel(const bf16_t* __rest
         const int key = 32 * j + 8 * g + 4 * hh;
         *reinterpret_cast<uint2*>(p_tile + (key >> 6) * (32 * kRowBytes) + lds_offset(qi, (key & 63) >> 3) + (key & 7) * 2) = uint2{pp[j][2 * g], pp[j][2 * g + 1]};
       }
-    asm volatile("" ::: "memory");  // read back through pointers of another type
+    lanes_together();
     bf16_t* dst = prob + (size_t)z * seq * seq;
 #pragma unroll
     for (int it = 0; it < 8; ++it) {
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256) void attention_fwd_kernel(const bf16_t* __rest
       }
     }
   }
-  asm volatile("" ::: "memory");
+  lanes_together();
   // ctx through the same LDS region (P is dead once its copy is read): 32 rows x 64 floats, four consecutive
   // features per 16-byte write, the 16 chunks of a row permuted by row % 16 (see the backward kernel's write_out)
   float* stage = reinterpret_cast<float*>(p_tile);
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(256) void attention_fwd_kernel(const bf16_t* __rest
       const int chunk = (8 * n + 2 * g + hh) ^ (qi & 15);
       *reinterpret_cast<f32x4*>(stage + qi * kPitch + chunk * 4) = f32x4{o[n][4 * g], o[n][4 * g + 1], o[n][4 * g + 2], o[n][4 * g + 3]};
     }
-  asm volatile("" ::: "memory");
+  lanes_together();
   bf16_t* out = ctx + (size_t)b * seq * ld_ctx + h * kHeadDim;
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
@@ -318,14 +318,14 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_kernel(const bf16_t* __r
   // accumulators are four consecutive features of one row: a result parks in the wave's staging rows with 8-byte
   // writes and leaves as whole 128-byte rows.
   auto write_out = [&](f32x16 (&o)[2], int col_block) {
-    asm volatile("" ::: "memory");
+    lanes_together();
     const int prow = lane & 31;
 #pragma unroll
     for (int n = 0; n < 2; ++n)
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         *reinterpret_cast<uint2*>(out_stage + lds_offset(prow, 4 * n + g) + hh * 8) = uint2{pack_bf16(o[n][4 * g], o[n][4 * g + 1]), pack_bf16(o[n][4 * g + 2], o[n][4 * g + 3])};
-    asm volatile("" ::: "memory");
+    lanes_together();
     bf16_t* out = dqkv + (size_t)b * seq * ld_qkv + col_block * hidden + h * kHeadDim;
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_kernel(const bf16_t* __r
       if (q0 + row < seq)
         *reinterpret_cast<u32x4*>(out + (size_t)(q0 + row) * ld_qkv + c * 8) = *reinterpret_cast<const u32x4*>(out_stage + lds_offset(row, c));
     }
-    asm volatile("" ::: "memory");
+    lanes_together();
   };
   auto zero = [](f32x16 (&o)[2]) {
 #pragma unroll

@@ -98,17 +98,17 @@ __device__ __forceinline__ void to_fragments(const uint32_t (&pp)[2][8], u32x4 (
 // The same 64 keys to memory as whole 128-byte row pieces, through the wave's staging rows.  LDS operations of one wave
 // complete in order.  out: row q0, first key of the tile; keys: how many of its keys exist.
 __device__ __forceinline__ void store_rows(const u32x4 (&frag)[4], char* mine, bf16_t* out, int ld, int rows, int keys, int lane) {
-  asm volatile("" ::: "memory");
+  lanes_together();
 #pragma unroll
   for (int kg = 0; kg < 4; ++kg) *reinterpret_cast<u32x4*>(mine + lds_offset(lane & 31, 2 * kg + (lane >> 5))) = frag[kg];
-  asm volatile("" ::: "memory");
+  lanes_together();
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
     const int row = it * 8 + (lane >> 3), chunk = lane & 7;
     if (row < rows && chunk * 8 < keys)
       *reinterpret_cast<u32x4*>(out + (size_t)row * ld + chunk * 8) = *reinterpret_cast<const u32x4*>(mine + lds_offset(row, chunk));
   }
-  asm volatile("" ::: "memory");
+  lanes_together();
 }
 
 // out[32 queries, 64 features] = sum over keys of frag x tile, by all four waves; tiles are KRow tiles in the wave's own
@@ -142,7 +142,7 @@ __device__ __forceinline__ void keys_product(const u32x4 (&frag)[TPW][4], char* 
             o[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b[n]), __builtin_bit_cast(bf16x8, a[0]), o[n], 0, 0, 0);
         }
       }
-    asm volatile("" ::: "memory");
+    lanes_together();
 #pragma unroll
     for (int n = 0; n < 2; ++n)
 #pragma unroll

@@ -231,11 +231,11 @@ __global__ __launch_bounds__(512) void conv3_wgrad_kernel(GemmParams p, int x_ro
   static_for<9>([&](auto tap_c) {
     constexpr int tap = decltype(tap_c)::value;
     if (pixels != (tap < 5 ? 0 : 1)) return;
-    asm volatile("" ::: "memory");
+    lanes_together();
 #pragma unroll
     for (int g = 0; g < 4; ++g)
       *reinterpret_cast<f32x4*>(stage + (lane & 31) * kPitch + 8 * g + 4 * half) = f32x4{acc[tap][4 * g], acc[tap][4 * g + 1], acc[tap][4 * g + 2], acc[tap][4 * g + 3]};
-    asm volatile("" ::: "memory");
+    lanes_together();
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
       const int row = it * 8 + (lane >> 3), c = (lane & 7) * 4;

@@ -389,6 +389,17 @@ struct FragmentReader {
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) { return bf16_pack2(lo, hi); }
 
+// Between the parts of an exchange through LDS among the lanes of one wave.  LDS operations of a wave complete in order, so nothing
+// has to be waited for, but the lanes have to come together: without a convergent operation the compiler may run lanes that take
+// no part in a later store (a wave partly beyond the last column or row) in a branch of their own, ahead of the others or
+// behind them.  It did so where a wave parks two pieces one after the other: rows parked by such lanes were read with the second
+// piece's values.
+__device__ __forceinline__ void lanes_together() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // Epilogue.  Each wave parks 32 rows of its WM x WN accumulator tile at a time in its own LDS region (the tile
 // ring is dead by then) and reads them back row by row, so that bias, mask and result move in 16-byte pieces
 // along n.  LDS operations of one wave complete in order, so the pieces need no wait between them.
@@ -647,12 +658,9 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         *reinterpret_cast<f32x4*>(park_at + j * 32 + 8 * g) = f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-    // All lanes park a piece together, after all have read the one before: without a convergent operation here the compiler may
-    // run the pieces of the lanes that store nothing (a wave partly beyond the last column) in a branch of their own ahead of
-    // the others', and the first piece's rows parked by those lanes were then read with the second piece's values.
-    if constexpr (TM > 1) __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_wave_barrier();   // (see lanes_together; the compiler may keep global loads and stores moving here)
   };
-  auto piece_done = [&]() { if constexpr (TM > 1) __builtin_amdgcn_wave_barrier(); };
+  auto piece_done = [&]() { __builtin_amdgcn_wave_barrier(); };
   if (!MAPPED && p.epilogue == (int)Epilogue::StoreF32) {
     constexpr int kPerRow = WN / 4, kRowStep = 64 / kPerRow, kIters = (32 + kRowStep - 1) / kRowStep;
     const int c = (lane % kPerRow) * 4, n = col_base + c, row0 = lane / kPerRow;
@@ -824,13 +832,13 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
     constexpr int kCols = 2 * WN;                       // [dz * y | dz] of the wave's WN columns
     constexpr int kPerLane = (kCols + 63) / 64;
     static_assert(kRowStep * kCols <= 32 * kPitch, "the lanes' column sums fit in the wave's staging rows");
-    asm volatile("" ::: "memory");
+    lanes_together();
     if (lane < kPerRow * kRowStep) {
       float* mine = stage + (lane / kPerRow) * kCols + c;
 #pragma unroll
       for (int e = 0; e < 8; ++e) { mine[e] = s_dzy[e]; mine[WN + e] = s_dz[e]; }
     }
-    asm volatile("" ::: "memory");
+    lanes_together();
     float wave_sum[kPerLane];
 #pragma unroll
     for (int u = 0; u < kPerLane; ++u) {
@@ -842,7 +850,7 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
       }
       wave_sum[u] = t;
     }
-    asm volatile("" ::: "memory");
+    lanes_together();
 #pragma unroll
     for (int u = 0; u < kPerLane; ++u)
       if (lane + 64 * u < kCols) stage[lane + 64 * u] = wave_sum[u];
