@@ -169,6 +169,18 @@ def test_weight_gradient_slices_are_bounded(cfg, most):
         spb.spb_model_destroy(m)
 
 
+# Partial sums are as large as the convolutions in their place of a unit need: with all twelve buffers of the largest one's size these were 994 and
+# 173 MB (a basic unit has no third convolution, and its projection's slices are a tenth of a 3x3 convolution's).
+@pytest.mark.parametrize("cfg,k,most", [(_plain_cnn(128, 32, 3, [2, 2, 2, 2], [64, 128, 256, 512]), 10, 900_000_000),
+                                        (_plain_cnn(16, 32, 3, [1, 1, 1, 1], [64, 128, 256, 512]), 2, 130_000_000)])
+def test_partial_sums_are_sized_by_their_place(cfg, k, most):
+    m = spb.spb_model_create(spb.desc_from_config(cfg))
+    try:
+        assert spb.spb_workspace_size(m, k) <= most
+    finally:
+        spb.spb_model_destroy(m)
+
+
 # Column sums of input gradients by pixel parity take three rows more: a model that fits the library's own workspace only without them does so.
 def test_a_model_at_the_library_workspaces_limit_fits():
     m = spb.spb_model_create(spb.desc_from_config(_plain_cnn(5, 8, 3, [1, 1], [64, 128])))
