@@ -14,7 +14,8 @@
 // waves 2400 cycles.  In the step of the 32-pixel basic CNN the gathering products took 50, 32, 29 and 33 us on 200 to 350 workgroups
 // each; the step went from 1257 to 1177 us, that of the 224-pixel bottleneck CNN from 4950 to 4876.
 //
-// Which pixel a row is comes from a table in LDS, worked out once; -1 stands for the zeros.  The slices of the pixel range go to
+// Which pixel a row is comes from a table in LDS, worked out for up to 48 steps at a time (a longer slice drains the ring and starts again
+// behind them); -1 stands for the zeros.  The slices of the pixel range go to
 // float32 partial results that the unit's reduction adds up in order.
 #include <algorithm>
 
@@ -24,15 +25,20 @@ namespace spb {
 namespace gemm_dma_detail {
 
 constexpr int kWgradStages = 4, kWgradAhead = 6;
+constexpr int kWgradTable = 48;           // steps whose pixels the table holds at a time
 constexpr int kWgradLoads = 6;            // a wave's loads of a step at most: 48 instructions of 8 rows
 // Workgroups of a launch, beside the input-gradient chain of the other stream: 96, 128, 160, 224 gave steps of 1201, 1181, 1187, 1204 us on
-// the 32-pixel basic CNN and 4943, 4900, 4875, 4871 on the 224-pixel bottleneck CNN.
-constexpr int kWgradBlocks = 128;
+// the 32-pixel basic CNN and 4943, 4900, 4875, 4871 on the 224-pixel bottleneck CNN.  Where that makes more than kWgradTable steps a slice,
+// a unit's chain is long enough for more: 128, 160, 192, 256 gave 1893, 1850, 1820, 1790 us for three blocks of 256 x 64 x 64 x 64, 3522, 3348, 3250,
+// 3255 for 256 x 32 x 32 x 256, 6279, 6089, 5949, 6354 for 256 x 48 x 48 x 192, 4931, 4738, 4728, 4812 for the 224-pixel basic CNN at batch 250.
+// (As many as keep a slice within one table, 353 for the first: 1848 us and 52 MB of partial results a buffer instead of 28.)
+constexpr int kWgradBlocks = 128, kWgradBlocksLong = 192;
 constexpr size_t kExchangeBytes = 4 * 4 * 4096;
 inline int wgrad_x_rows(int width) { return (kTileK + 2 * width + 4 + 7) / 8 * 8; }
 inline int wgrad_tiles(const ConvGeom& c) { return (int)(((long long)c.n * (c.rh + 1) * (c.rw + 1) + kTileK - 1) / kTileK); }
 inline size_t wgrad_lds(const ConvGeom& c, int tiles_per_slice) {
-  const size_t loop = (size_t)kWgradStages * (kTileK + wgrad_x_rows(c.rw)) * kRowBytes + ((size_t)(tiles_per_slice - 1) * kTileK + wgrad_x_rows(c.rw)) * sizeof(int);
+  const size_t table = (size_t)(std::min(tiles_per_slice, kWgradTable) - 1) * kTileK + wgrad_x_rows(c.rw);
+  const size_t loop = (size_t)kWgradStages * (kTileK + wgrad_x_rows(c.rw)) * kRowBytes + table * sizeof(int);
   return std::max(loop, kExchangeBytes);
 }
 
@@ -52,17 +58,20 @@ __global__ __launch_bounds__(512) void conv3_wgrad_kernel(GemmParams p, int x_ro
   const int width = p.conv.rw, height = p.conv.rh, channels = p.conv.sc, pitch = width + 1;
   const int slot_bytes = (kTileK + x_rows) * kRowBytes;      // 64 rows of dy, then the rows of x
   const int all = p.conv.n * (height + 1) * pitch;
-  const int t_first = blockIdx.y * p.k_tiles_per_split;
-  const int n_tiles = max(min((all + kTileK - 1) / kTileK - t_first, p.k_tiles_per_split), 0);
+  const int t_end = min((all + kTileK - 1) / kTileK, ((int)blockIdx.y + 1) * p.k_tiles_per_split);
+  int t_first = blockIdx.y * p.k_tiles_per_split;            // of the steps the table holds
+  int n_tiles = max(min(t_end - t_first, kWgradTable), 0);   // them
   int* table = reinterpret_cast<int*>(lds + kWgradStages * slot_bytes);
 
-  // ---- row e of the slice's table: number first * 64 - (W + 2) + e
-  for (int e = threadIdx.x; e < (n_tiles - 1) * kTileK + x_rows; e += 512) {
-    const int q = t_first * kTileK - (width + 2) + e;
-    const int row = q / pitch, b = q - row * pitch, n = row / (height + 1), a = row - n * (height + 1);
-    table[e] = q >= 0 && q < all && b < width && a < height ? (n * height + a) * width + b : -1;
-  }
-  __syncthreads();
+  // ---- row e of the table: number first * 64 - (W + 2) + e
+  auto fill_table = [&]() {
+    for (int e = threadIdx.x; e < (n_tiles - 1) * kTileK + x_rows; e += 512) {
+      const int q = t_first * kTileK - (width + 2) + e;
+      const int row = q / pitch, b = q - row * pitch, n = row / (height + 1), a = row - n * (height + 1);
+      table[e] = q >= 0 && q < all && b < width && a < height ? (n * height + a) * width + b : -1;
+    }
+    __syncthreads();
+  };
 
   // ---- loads: instruction u = 8 i + wave of a tile is rows 8 u .. of its slot.  A lane's chunk: rows k and k + 2 lie half a row apart (krow_rot).
   const int n_loads = ((kTileK + x_rows) / 8 - wave + 7) / 8;   // this wave's
@@ -89,12 +98,6 @@ __global__ __launch_bounds__(512) void conv3_wgrad_kernel(GemmParams p, int x_ro
 #pragma unroll
     for (int i = 0; i < kWgradLoads; ++i) asm volatile("" : "+v"(pixel[i]));
   };
-  for (int t = 0; t < min(2, n_tiles); ++t) {
-    look_up(t);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    looked_up();
-    static_for<kWgradLoads>([&](auto i) { if (decltype(i)::value < n_loads) load(i, pixel[decltype(i)::value], t); });
-  }
 
   // ---- fragments
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
@@ -143,7 +146,14 @@ __global__ __launch_bounds__(512) void conv3_wgrad_kernel(GemmParams p, int x_ro
       default: __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
     }
   };
-  if (n_tiles > 0) {
+  while (n_tiles > 0) {
+    fill_table();
+    for (int t = 0; t < min(2, n_tiles); ++t) {
+      look_up(t);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      looked_up();
+      static_for<kWgradLoads>([&](auto i) { if (decltype(i)::value < n_loads) load(i, pixel[decltype(i)::value], t); });
+    }
     wait_loads(n_tiles > 1);
     pin();
     asm volatile("" ::: "memory");
@@ -188,8 +198,10 @@ __global__ __launch_bounds__(512) void conv3_wgrad_kernel(GemmParams p, int x_ro
     for (int tap = 0; tap < 9; ++tap) asm volatile("" : "+v"(fb[tap]));
     looked_up();
     asm volatile("" : "+v"(fa[0]), "+v"(fa[1]));
+    __syncthreads();   // every wave is done with the ring and the table
+    t_first += n_tiles;
+    n_tiles = min(t_end - t_first, kWgradTable);
   }
-  __syncthreads();
 
   // ---- the two halves of the pixels: one wave of a pair finishes taps 0 to 4, the other 5 to 8, two of each at a time
   auto exchange = [&](int of, int which) { return reinterpret_cast<f32x4*>(lds + ((of * 4 + (wave & 3)) * 2 + which) * 4096 + lane * 16); };   // of: whose sums
@@ -249,25 +261,21 @@ __global__ __launch_bounds__(512) void conv3_wgrad_kernel(GemmParams p, int x_ro
 using namespace gemm_dma_detail;
 
 // Slices of the pixel range for about kWgradBlocks workgroups (beside the input-gradient chain of the other stream), at least 256 pixels each
-// (the zeros not counted: no more slices than the gathering product takes of a model small enough for the library's own workspace), and
-// so many that one has at most 48 steps (the table).  0: not this kernel's convolution, or so many pixels that the table asks for more than
-// kWgradMostBlocks workgroups: the partial results of each are 147 KB, in twelve buffers (128 channels of 1.6 million pixels: 321 MB a
-// buffer).  256 images of 64 x 64 pixels and 64 channels take 352.
-constexpr int kWgradMostBlocks = 512;
+// (the zeros not counted: no more slices than the gathering product takes of a model small enough for the library's own workspace); for about
+// kWgradBlocksLong where the slices would be long.  0: not this kernel's convolution.
 int conv3_wgrad_splits(const ConvGeom& c, int c_out) {
   if (c.r != 3 || c.s != 3 || c.stride != 1 || c.pad != 1 || c.pad_w != 1 || c.transposed || c.sh != c.rh || c.sw != c.rw || c.sc % 64 || c_out % 64) return 0;
-  if ((long long)c.n * (c.rh + 1) * (c.rw + 1) > 0x7FFFFFFFLL - 4096 || kTileK + wgrad_x_rows(c.rw) > 64 * kWgradLoads || wgrad_lds(c, 48) > 160 * 1024) return 0;
-  const int tiles = wgrad_tiles(c), blocks = c.sc / 64 * (c_out / 64), least = (tiles + 47) / 48;
+  if ((long long)c.n * (c.rh + 1) * (c.rw + 1) > 0x7FFFFFFFLL - 4096 || kTileK + wgrad_x_rows(c.rw) > 64 * kWgradLoads || wgrad_lds(c, kWgradTable) > 160 * 1024) return 0;
+  const int blocks = c.sc / 64 * (c_out / 64);
   const int pixel_tiles = (int)(((long long)c.n * c.rh * c.rw + kTileK - 1) / kTileK);
   const int s = std::min((kWgradBlocks + blocks - 1) / blocks, std::max(pixel_tiles / 4, 1));
-  if (least <= s) return s;
-  return (long long)least * blocks <= kWgradMostBlocks ? least : 0;
+  return (wgrad_tiles(c) + s - 1) / s <= kWgradTable ? s : (kWgradBlocksLong + blocks - 1) / blocks;
 }
 
 bool conv3_wgrad_accepts(const GemmProblem& q) {
   return q.b_gather == Gather::ConvPatchT && q.a_gather == Gather::None && q.a_layout == Layout::KRow && q.epilogue == Epilogue::StoreF32 && !q.bias &&
          !q.a_row_sum && q.alpha == 1.f && q.batch == 1 && q.N == 9 * q.conv.sc && q.ldc == q.N && q.K == q.conv.n * q.conv.rh * q.conv.rw &&
-         conv3_wgrad_splits(q.conv, q.M) > 0 && (wgrad_tiles(q.conv) + q.k_splits - 1) / q.k_splits <= 48;
+         conv3_wgrad_splits(q.conv, q.M) > 0;
 }
 
 hipError_t launch_conv3_wgrad(const GemmProblem& q, hipStream_t stream) {

@@ -171,7 +171,9 @@ def test_weight_gradient_slices_are_bounded(cfg, most):
 
 # Partial sums are as large as the convolutions in their place of a unit need: with all twelve buffers of the largest one's size these were 994 and
 # 173 MB (a basic unit has no third convolution, and its projection's slices are a tenth of a 3x3 convolution's).
+# The slices of a long 3x3 weight gradient are bounded by the workgroups (256 images of 64 x 64 took 6934 MB with 353 slices, 6360 with 39).
 @pytest.mark.parametrize("cfg,k,most", [(_plain_cnn(128, 32, 3, [2, 2, 2, 2], [64, 128, 256, 512]), 10, 900_000_000),
+                                        (_plain_cnn(256, 64, 3, [2, 2, 2, 2], [64, 128, 256, 512]), 10, 6_400_000_000),
                                         (_plain_cnn(16, 32, 3, [1, 1, 1, 1], [64, 128, 256, 512]), 2, 130_000_000)])
 def test_partial_sums_are_sized_by_their_place(cfg, k, most):
     m = spb.spb_model_create(spb.desc_from_config(cfg))

@@ -148,6 +148,12 @@ def test_every_unit_of_the_cnns_on_odd_images(name):
     _teacher_forced(name)
 
 
+# 3x3 weight gradients of more pixels than a workgroup's table holds at a time
+@pytest.mark.parametrize("name", ["long_slice_resnet_basic_bf16"])
+def test_weight_gradients_over_several_tables(name):
+    _teacher_forced(name, units_to_run=[1], check_handed_down=False)
+
+
 @pytest.mark.parametrize("name", ["rows_attention_136_bf16", "rows_attention_256_bf16", "rows_attention_328_bf16", "rows_attention_512_bf16",
                                   "rows_attention_chain_bf16", "rows_attention_chain2_bf16", "long_attention_520_bf16"])
 def test_encoder_layers_of_more_than_128_positions(name):

@@ -83,6 +83,9 @@ CONFIGS = {
                                   stem=dict(kernel=3, stride=1, pad=1, pool=False, width=64), stage_blocks=[1, 1, 1, 1], stage_widths=[64, 128, 192, 256], classes=7),
     "pixel_resnet_basic_bf16": dict(family="resnet_basic", dtype="bf16", batch=3, image=[3, 3, 3],
                                     stem=dict(kernel=3, stride=1, pad=1, pool=False, width=64), stage_blocks=[2, 2, 2], stage_widths=[64, 64, 128], classes=7),
+    # 147 steps of 64 pixels in three slices: each works out its pixels twice, for 48 steps and for one
+    "long_slice_resnet_basic_bf16": dict(family="resnet_basic", dtype="bf16", batch=48, image=[13, 13, 3],
+                                         stem=dict(kernel=3, stride=1, pad=1, pool=False, width=512), stage_blocks=[1], stage_widths=[512], classes=7),
     # attention over more than 128 positions, by rows of 32 queries whose keys four waves divide: one 64-key tile a wave and
     # three waves at work, four whole tiles, two tiles a wave with a ragged last one and an idle wave, four times two
     "rows_attention_136_bf16": dict(family="encoder", dtype="bf16", batch=3, seq=136, layers=2, hidden=128, heads=2, ffn=128, vocab=97, loss_rows=41),
