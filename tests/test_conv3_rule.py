@@ -8,6 +8,7 @@ import subprocess
 
 import pytest
 
+import workloads as wl
 from paper_2111_10672_amd.build import hipcc
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -26,7 +27,8 @@ int main() {
     c.n = n; c.sh = c.sw = c.rh = c.rw = image; c.sc = cin; c.r = c.s = 3; c.stride = 1; c.pad = c.pad_w = 1; c.transposed = transposed;
     c.w_cin = cout; c.w_cout = cin;
     g.M = n * image * image; g.N = cout; g.K = 9 * cin; g.lda = g.K; g.ldb = transposed ? cout : g.K; g.ldc = cout;
-    std::printf("%d\n", (int)gemm_dma_detail::conv3_accepts(g));
+    const auto t = gemm_dma_detail::conv3_tile(g);
+    std::printf("%d:%dx%d\n", (int)gemm_dma_detail::conv3_accepts(g), t.bm, t.bn);
   }
 }
 """
@@ -46,17 +48,22 @@ TIMED = [
 
 
 @pytest.fixture(scope="module")
-def accepts(tmp_path_factory):
+def ask(tmp_path_factory):
     d = tmp_path_factory.mktemp("conv3_rule")
     src, exe = d / "rule.hip", d / "rule"
     src.write_text(PROGRAM)
     subprocess.run([hipcc(), "-std=c++17", "--offload-host-only", "-I" + os.path.join(ROOT, "paper_2111_10672_amd", "csrc"),
                     "-I" + os.path.join(ROOT, "include"), str(src), "-o", str(exe)], check=True, capture_output=True, text=True)
 
-    def ask(shapes):
+    def run(shapes):
         out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, s)) for s in shapes), check=True, capture_output=True, text=True).stdout
-        return [line == "1" for line in out.split()]
-    return ask
+        return [line.split(":") for line in out.split()]
+    return run
+
+
+@pytest.fixture(scope="module")
+def accepts(ask):
+    return lambda shapes: [taken == "1" for taken, _ in ask(shapes)]
 
 
 def test_each_timed_shape_goes_to_the_faster_kernel(accepts):
@@ -68,3 +75,17 @@ def test_each_timed_shape_goes_to_the_faster_kernel(accepts):
 def test_what_the_kernel_does_not_hold_stays_refused(accepts):
     # channels that are not whole 64-groups; a row too wide for the patch of the smallest tile
     assert accepts([(8, 14, 96, 96, 0), (8, 14, 32, 64, 1), (1, 255, 512, 512, 0), (2, 40, 512, 512, 1)]) == [False] * 4
+
+
+# The configurations that run each large tile with a part-filled last one.
+@pytest.mark.parametrize("name,block,tile", [
+    ("odd_tiles_128x64_resnet_basic_bf16", 0, "128x64"), ("odd_tiles_stride2_resnet_basic_bf16", 0, "128x64"),
+    ("odd_tiles_stride2_resnet_basic_bf16", 1, "128x64"), ("odd_tiles_256x64_resnet_basic_bf16", 0, "256x64"),
+    ("odd_tiles_128x128_resnet_basic_bf16", 0, "128x128"), ("odd_tiles_64x128_resnet_basic_bf16", 0, "64x128"),
+])
+def test_configurations_of_part_filled_tiles(ask, name, block, tile):
+    cfg = wl.get_config(name)
+    b = wl.resnet_layout(cfg)["blocks"][block]
+    shape, width = b["out_hw"][0], b["cout"]
+    assert cfg["batch"] * shape * shape % int(tile.split("x")[0])
+    assert ask([(cfg["batch"], shape, width, width, t) for t in (0, 1)]) == [["1", tile]] * 2

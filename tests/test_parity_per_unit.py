@@ -148,6 +148,13 @@ def test_every_unit_of_the_cnns_on_odd_images(name):
     _teacher_forced(name)
 
 
+@pytest.mark.parametrize("name,units", [("odd_tiles_128x64_resnet_basic_bf16", [2, 1]), ("odd_tiles_stride2_resnet_basic_bf16", [2, 1]),
+                                        ("odd_tiles_256x64_resnet_basic_bf16", [1]), ("odd_tiles_128x128_resnet_basic_bf16", [1]),
+                                        ("odd_tiles_64x128_resnet_basic_bf16", [1])])
+def test_part_filled_large_tiles_of_convolutions(name, units):
+    _teacher_forced(name, units_to_run=units)
+
+
 # 3x3 weight gradients of more pixels than a workgroup's table holds at a time
 @pytest.mark.parametrize("name", ["long_slice_resnet_basic_bf16"])
 def test_weight_gradients_over_several_tables(name):

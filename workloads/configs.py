@@ -83,6 +83,19 @@ CONFIGS = {
                                   stem=dict(kernel=3, stride=1, pad=1, pool=False, width=64), stage_blocks=[1, 1, 1, 1], stage_widths=[64, 128, 192, 256], classes=7),
     "pixel_resnet_basic_bf16": dict(family="resnet_basic", dtype="bf16", batch=3, image=[3, 3, 3],
                                     stem=dict(kernel=3, stride=1, pad=1, pool=False, width=64), stage_blocks=[2, 2, 2], stage_widths=[64, 64, 128], classes=7),
+    # the same convolutions in each of the large tiles with a part-filled last one, forward, input gradient and weight gradient (tests/test_conv3_rule.py
+    # holds them there): 32799 pixels of 64 and of 128 channels in 128 x 64, with a stride-2 block behind them whose input gradient comes in 128 x 64
+    # and 128 x 128 tiles of 8775, 8190, 8190 and 7644 pixels; 116281 of 64 in 256 x 64; 10309 of 256 in 128 x 128; 2597 of 512 in 64 x 128
+    "odd_tiles_128x64_resnet_basic_bf16": dict(family="resnet_basic", dtype="bf16", batch=39, image=[29, 29, 3],
+                                               stem=dict(kernel=3, stride=1, pad=1, pool=False, width=64), stage_blocks=[1, 1], stage_widths=[64, 128], classes=7),
+    "odd_tiles_stride2_resnet_basic_bf16": dict(family="resnet_basic", dtype="bf16", batch=39, image=[29, 29, 3],
+                                                stem=dict(kernel=3, stride=1, pad=1, pool=False, width=128), stage_blocks=[1, 1], stage_widths=[128, 256], classes=7),
+    "odd_tiles_256x64_resnet_basic_bf16": dict(family="resnet_basic", dtype="bf16", batch=121, image=[31, 31, 3],
+                                               stem=dict(kernel=3, stride=1, pad=1, pool=False, width=64), stage_blocks=[1], stage_widths=[64], classes=7),
+    "odd_tiles_128x128_resnet_basic_bf16": dict(family="resnet_basic", dtype="bf16", batch=61, image=[13, 13, 3],
+                                                stem=dict(kernel=3, stride=1, pad=1, pool=False, width=256), stage_blocks=[1], stage_widths=[256], classes=7),
+    "odd_tiles_64x128_resnet_basic_bf16": dict(family="resnet_basic", dtype="bf16", batch=53, image=[7, 7, 3],
+                                               stem=dict(kernel=3, stride=1, pad=1, pool=False, width=512), stage_blocks=[1], stage_widths=[512], classes=7),
     # 147 steps of 64 pixels in three slices: each works out its pixels twice, for 48 steps and for one
     "long_slice_resnet_basic_bf16": dict(family="resnet_basic", dtype="bf16", batch=48, image=[13, 13, 3],
                                          stem=dict(kernel=3, stride=1, pad=1, pool=False, width=512), stage_blocks=[1], stage_widths=[512], classes=7),
