@@ -1455,6 +1455,21 @@ inline bool small_product_fits(const GemmProblem& q) {
 // 32 x 32 tiles only while they still make a single round over the CUs.
 inline bool small_product_tile64(const GemmProblem& q) { return tile_count(q, 64, 64) >= 192 || tile_count(q, 32, 32) > 256; }
 
+// 64 x 64 tiles that would leave a quarter of the chip or more idle: 32 x 64, if those make one round.  A CU then pulls three
+// quarters of the bytes, and the ring holds three tiles of a wave's quarter instead of two (504 rows, 768 columns, in the encoder
+// step of 7 x 72 tokens, 42 such products: 1442 -> 1358 us the step; over 18900 products of drawn shapes, alone, 0.82 of the time forward and
+// 0.87 for weight gradients).  But where the tiles do not divide by the XCDs, the rows of tiles that read one panel of B lie on different XCDs, each
+// of which fetches it, and twice as many rows fetch it twice as often.  That shows for few rows and a B beyond an XCD's 4 MB of L2: weight
+// gradients 127 x 3128 over k = 504 6.6 us in 64 x 64 and 5.7 in 32 x 64, over 2804 16.1 and 22.1, 122 x 3624 over 7358 35 and 57, but 333 x 1336 over
+// 8192 43 and 38.  Forward it does where the 64 x 64 tiles do divide: 343 x 1280 over 3240 13.4 and 16.9.
+inline bool small_product_rows32(const GemmProblem& q) {
+  if (tile_count(q, 64, 64) >= 192 || tile_count(q, 32, 64) > 256) return false;
+  if (tile_count(q, 32, 64) % 8 == 0) return true;
+  const double a = 2e-6 * q.M * q.K, b = 2e-6 * q.N * q.K;   // MB
+  if (q.a_layout == Layout::KRow) return q.M > 256 || b <= 4.5;
+  return tile_count(q, 64, 64) % 8 != 0 || a >= 3.1 || b <= 3.3;
+}
+
 template <int BM, int BN, Layout LA, Layout LB>
 hipError_t launch_small(const GemmProblem& q, hipStream_t stream) {
   GemmParams p = make_params(q, BM, BN);
@@ -1537,10 +1552,7 @@ hipError_t launch_layouts(const GemmProblem& q, hipStream_t stream) {
   if constexpr (GA == Gather::None && GB == Gather::None) {
     if (small_product_fits(q) && q.epilogue != Epilogue::AffineBwdStore) {   // (the small kernel's epilogue has no column sums)
       if (small_product_tile64(q)) {
-        // 64 x 64 tiles that would leave a quarter of the chip or more idle: 32 x 64, if those make one round.  A CU then pulls three
-        // quarters of the bytes, and the ring holds three tiles of a wave's quarter instead of two (504 rows, 768 columns, in the encoder
-        // step of 7 x 72 tokens, 42 such products: 1442 -> 1358 us the step).
-        if (tiles(64, 64) < 192 && tiles(32, 64) <= 256) return launch_small<32, 64, LA, LB>(q, stream);
+        if (small_product_rows32(q)) return launch_small<32, 64, LA, LB>(q, stream);
         return launch_small<64, 64, LA, LB>(q, stream);
       }
       return launch_small<32, 32, LA, LB>(q, stream);
