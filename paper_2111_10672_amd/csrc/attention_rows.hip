@@ -7,7 +7,8 @@
 //
 // The four waves share a row of 32 queries and divide the keys: a wave's scores are 32 queries x at most 128 keys, 64
 // registers a lane, so a row of 512 is held whole and its exponentials are worked out once.  That - some 10 vector
-// instructions an element at 4 cycles, 16 for the exponential itself - is what bounds the forward kernel; 80 KB of LDS
+// instructions an element at 4 cycles, 16 for the exponential itself - is what bounds the forward kernel (8 x 512 tokens, 12 heads: the vector
+// ALUs are at work half of a CU's cycles, the matrix cores 5 %); 80 KB of LDS
 // let two workgroups share a CU and cover each other's exchanges.
 //
 // Every sum is added in the order of the passes these kernels replace (and which other head sizes and longer rows still
