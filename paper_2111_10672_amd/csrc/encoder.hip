@@ -118,6 +118,7 @@ class EncoderModel : public Model {
     g.dtype = dtype; g.a_layout = Layout::KRow; g.b_layout = Layout::KRow; g.epilogue = Epilogue::StoreF32;
     g.M = n_out; g.N = n_in; g.K = rows; g.A = dz; g.lda = lddz; g.B = a; g.ldb = lda; g.C = dw; g.ldc = n_in; g.a_row_sum = db;
     g.a_pad_zero = g.b_pad_zero = true;
+    g.beside = true;
     g.name = "gemm_bf16_wgrad";
     return g;
   }

@@ -1462,8 +1462,10 @@ inline bool small_product_tile64(const GemmProblem& q) { return tile_count(q, 64
 // of which fetches it, and twice as many rows fetch it twice as often.  That shows for few rows and a B beyond an XCD's 4 MB of L2: weight
 // gradients 127 x 3128 over k = 504 6.6 us in 64 x 64 and 5.7 in 32 x 64, over 2804 16.1 and 22.1, 122 x 3624 over 7358 35 and 57, but 333 x 1336 over
 // 8192 43 and 38.  Forward it does where the 64 x 64 tiles do divide: 343 x 1280 over 3240 13.4 and 16.9.
+// Nor for the encoder's weight gradients, whose workgroups have a CU to themselves: twice as many take it from the input-gradient chain (8
+// layers of 448 features and 1600 tokens 1129 -> 1180 us a step, 5 of 320 and 3080 598 -> 618).
 inline bool small_product_rows32(const GemmProblem& q) {
-  if (tile_count(q, 64, 64) >= 192 || tile_count(q, 32, 64) > 256) return false;
+  if (tile_count(q, 64, 64) >= 192 || tile_count(q, 32, 64) > 256 || q.beside) return false;
   if (tile_count(q, 32, 64) % 8 == 0) return true;
   const double a = 2e-6 * q.M * q.K, b = 2e-6 * q.N * q.K;   // MB
   if (q.a_layout == Layout::KRow) return q.M > 256 || b <= 4.5;

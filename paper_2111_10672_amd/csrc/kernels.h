@@ -90,6 +90,7 @@ struct GemmProblem {
   // The product runs beside workgroups of another stream: where the tile choice is between one 128 x 128 workgroup
   // that takes most of a CU's LDS and one that leaves room for a neighbour, take the latter.
   bool share_cu = false;
+  bool beside = false;            // runs beside the chain of another stream: the CUs it leaves to that count for more than its own time
   bool b_in_hbm = false;          // B is weights that other traffic has driven out of the caches: see touch_lines
   float* a_row_sum = nullptr;     // optional [M]: sum_k A(m, k), written once by the tiles of column block 0
   // AffineBwdStore: the affine's input (pre-affine convolution output), the partial column sums [tile rows][2][N]

@@ -6,6 +6,8 @@ same quarters of k in the same order.
 import os
 import subprocess
 
+import pytest
+
 from paper_2111_10672_amd.build import hipcc
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -15,12 +17,13 @@ PROGRAM = r"""
 #include "gemm_dma_impl.h"
 using namespace spb;
 int main() {
-  int kind;
+  int kind, beside;
   GemmProblem g;
   g.dtype = DType::BF16;
-  while (std::scanf("%d %d %d %d", &kind, &g.M, &g.N, &g.K) == 4) {
+  while (std::scanf("%d %d %d %d %d", &kind, &g.M, &g.N, &g.K, &beside) == 5) {
     g.a_layout = kind ? Layout::KRow : Layout::RowK;   // weight gradient or forward
     g.b_layout = g.a_layout;
+    g.beside = beside;
     std::printf("%d\n", gemm_dma_detail::small_product_fits(g) && gemm_dma_detail::small_product_tile64(g) && gemm_dma_detail::small_product_rows32(g));
   }
 }
@@ -37,11 +40,26 @@ TIMED = [
 ]
 
 
-def test_each_timed_shape_gets_the_faster_tile(tmp_path):
-    src, exe = tmp_path / "rule.hip", tmp_path / "rule"
+@pytest.fixture(scope="module")
+def takes32(tmp_path_factory):
+    d = tmp_path_factory.mktemp("small_tile_rule")
+    src, exe = d / "rule.hip", d / "rule"
     src.write_text(PROGRAM)
     subprocess.run([hipcc(), "-std=c++17", "--offload-host-only", "-I" + os.path.join(ROOT, "paper_2111_10672_amd", "csrc"),
                     "-I" + os.path.join(ROOT, "include"), str(src), "-o", str(exe)], check=True, capture_output=True, text=True)
-    out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, s)) for s, _, _ in TIMED), check=True, capture_output=True, text=True).stdout.split()
-    wrong = [(s, a, b) for (s, a, b), rows32 in zip(TIMED, out) if (rows32 == "1") != (a < b)]
-    assert len(out) == len(TIMED) and not wrong, wrong
+
+    def ask(shapes, beside):
+        out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, s)) + f" {beside}" for s in shapes), check=True, capture_output=True, text=True).stdout
+        return [line == "1" for line in out.split()]
+    return ask
+
+
+def test_each_timed_shape_gets_the_faster_tile(takes32):
+    got = takes32([s for s, _, _ in TIMED], 0)
+    wrong = [(s, a, b) for (s, a, b), rows32 in zip(TIMED, got) if rows32 != (a < b)]
+    assert len(got) == len(TIMED) and not wrong, wrong
+
+
+# The encoder's weight gradients share the chip with its input-gradient chain, and more workgroups are worse for the step.
+def test_products_beside_another_chain_keep_the_fewer_workgroups(takes32):
+    assert not any(takes32([(1, 896, 448, 1600), (1, 320, 1280, 3080), (1, 768, 512, 2048)], 1))
