@@ -1490,13 +1490,14 @@ hipError_t launch_small(const GemmProblem& q, hipStream_t stream) {
 }
 
 // Where the large tiles of a product whose weights lie in HBM do better without touching them (forward passes of encoders, alone and
-// followed by their backward pass): 256 x 192 tiles that do not divide by the XCDs, whose panels two or three workgroups share (3720 rows:
-// +0.5 to +2.3 % a step); lone 128 x 128 tiles with eight panels or more whose rows lie a power of two of 2 KB and more apart, so that the lanes'
+// followed by their backward pass): tiles that do not divide by the XCDs and are too few for seven workgroups to share a panel (3720 rows in 256 x
+// 192 tiles, two sharers: +0.5 to +2.3 % a step; 5160 rows of 896 features in 128 x 128, six: +1.5); lone 128 x 128 tiles with eight panels or more whose rows lie a power of two of 2 KB and more apart, so that the lanes'
 // lines meet on few channels (4096 x 1024 over k = 1024 and 4096: +0.4 to +2 %; 768 columns over 768 and 3072, 512 over 512 and 2048: -0.2 to
 // -1.2 %; 12544 x 256 over 1024 in the bottleneck CNN: -0.3 %).
 inline bool touching_pays(const GemmProblem& q, int bm, int bn, bool lone) {
-  if (bn == 192) return tile_count(q, bm, bn) % 8 == 0;
-  return !(lone && bm == 128 && q.N >= 1024 && q.K >= 1024 && (q.K & (q.K - 1)) == 0);
+  const int tiles_m = (q.M + bm - 1) / bm;
+  const int sharers = tile_count(q, bm, bn) % 8 == 0 ? std::min(tiles_m, (int)kTileGroupM) : (tiles_m + kTileGroupM - 1) / kTileGroupM;   // see touch_panel
+  return sharers >= 7 && !(lone && bm == 128 && q.N >= 1024 && q.K >= 1024 && (q.K & (q.K - 1)) == 0);
 }
 
 template <int BM, int BN, int STAGES, int WAVES_M, int WAVES_N, Layout LA, Layout LB, Gather GA, Gather GB>

@@ -33,6 +33,7 @@ int main() {
 ASKED = [
     ((8192, 1024, 1024, 0, 128, 128, 0), 0), ((2048, 2048, 2048, 0, 128, 128, 1), 0), ((4096, 2048, 2048, 0, 256, 192, 0), 0), ((8192, 2048, 2048, 0, 256, 256, 1), 0),
     ((8192, 1024, 1024, 1, 128, 128, 0), 1), ((4096, 768, 3072, 1, 128, 128, 1), 1), ((4096, 1024, 1024, 1, 128, 128, 1), 0), ((4096, 1024, 4096, 1, 128, 128, 1), 0),
+    ((5160, 896, 896, 1, 128, 128, 0), 0), ((7320, 768, 768, 1, 128, 128, 0), 1),
     ((8192, 512, 512, 1, 128, 128, 1), 1), ((12544, 256, 1024, 1, 128, 128, 1), 1), ((4096, 2304, 768, 1, 256, 192, 0), 1), ((3720, 2304, 768, 1, 256, 192, 0), 0), ((8192, 4096, 1024, 1, 256, 256, 1), 1),
 ]
 
