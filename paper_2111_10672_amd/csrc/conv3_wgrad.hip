@@ -33,6 +33,10 @@ constexpr int kWgradLoads = 6;            // a wave's loads of a step at most: 4
 // 3255 for 256 x 32 x 32 x 256, 6279, 6089, 5949, 6354 for 256 x 48 x 48 x 192, 4931, 4738, 4728, 4812 for the 224-pixel basic CNN at batch 250.
 // (As many as keep a slice within one table, 353 for the first: 1848 us and 52 MB of partial results a buffer instead of 28.)
 constexpr int kWgradBlocks = 128, kWgradBlocksLong = 192;
+// Fewer steps a slice than this do not pay for the start and the exchange: five steps 14.7 us for 4056 pixels of 128 channels and 16.0 for 8112, where
+// the gathering product takes 12.1 and 14.2.  46 CNNs with their two streams: from 6 steps on 0.990 of the time with every size here, from
+// 10 0.982, from 13 0.977, from 17 0.978, from 26 0.979, never 0.981 (48 images of 49 x 49, 35 units: 3513 -> 3414 us, 3397 before this kernel).
+constexpr int kWgradLeastSteps = 13;
 constexpr size_t kExchangeBytes = 4 * 4 * 4096;
 inline int wgrad_x_rows(int width) { return (kTileK + 2 * width + 4 + 7) / 8 * 8; }
 inline int wgrad_tiles(const ConvGeom& c) { return (int)(((long long)c.n * (c.rh + 1) * (c.rw + 1) + kTileK - 1) / kTileK); }
@@ -262,14 +266,16 @@ using namespace gemm_dma_detail;
 
 // Slices of the pixel range for about kWgradBlocks workgroups (beside the input-gradient chain of the other stream), at least 256 pixels each
 // (the zeros not counted: no more slices than the gathering product takes of a model small enough for the library's own workspace); for about
-// kWgradBlocksLong where the slices would be long.  0: not this kernel's convolution.
+// kWgradBlocksLong where the slices would be long.  0: not this kernel's convolution, or one of too few steps.
 int conv3_wgrad_splits(const ConvGeom& c, int c_out) {
   if (c.r != 3 || c.s != 3 || c.stride != 1 || c.pad != 1 || c.pad_w != 1 || c.transposed || c.sh != c.rh || c.sw != c.rw || c.sc % 64 || c_out % 64) return 0;
   if ((long long)c.n * (c.rh + 1) * (c.rw + 1) > 0x7FFFFFFFLL - 4096 || kTileK + wgrad_x_rows(c.rw) > 64 * kWgradLoads || wgrad_lds(c, kWgradTable) > 160 * 1024) return 0;
   const int blocks = c.sc / 64 * (c_out / 64);
   const int pixel_tiles = (int)(((long long)c.n * c.rh * c.rw + kTileK - 1) / kTileK);
   const int s = std::min((kWgradBlocks + blocks - 1) / blocks, std::max(pixel_tiles / 4, 1));
-  return (wgrad_tiles(c) + s - 1) / s <= kWgradTable ? s : (kWgradBlocksLong + blocks - 1) / blocks;
+  const int steps = (wgrad_tiles(c) + s - 1) / s;
+  if (steps < kWgradLeastSteps) return 0;
+  return steps <= kWgradTable ? s : (kWgradBlocksLong + blocks - 1) / blocks;
 }
 
 bool conv3_wgrad_accepts(const GemmProblem& q) {
