@@ -126,8 +126,8 @@ inline hipError_t raise_lds_limit(const void* kernel, size_t lds_bytes) {
 hipError_t launch_gemm(const GemmProblem& p, hipStream_t stream);
 // Whether a step over so many bytes of weights and workspace drives the weights out of the 256 MB cache from one use to the next.  Encoders
 // of 1 to 12 layers of 256 to 1024 features, step with and without touching in the large tiles: below 340 MB 0 to +3.5 % (1 layer of 1024 and 48 x
-// 128 tokens, 336 MB), above it level to -10 % (12 of 640 and 64 x 128, 386 MB).  Perceptrons never gain, up to 800 MB: +2 to +7 % up to 200
-// MB, level beyond.  Convolutional networks gain at any size, most in their 3 x 3 convolutions.
+// 128 tokens, 336 MB), above it level to -10 % (12 of 640 and 64 x 128, 386 MB).  Perceptrons (with the gradients they write) lose 2 to 7 % up to 200 MB and on both
+// sides of level from there to 340; beyond, 75 of them ran in 0.88 to 1.03 of the time (mean 0.998).  Convolutional networks gain at any size, most in their 3 x 3 convolutions.
 inline bool weights_driven_out(size_t weights, size_t workspace) { return weights + workspace >= (size_t)340 * 1000 * 1000; }
 bool gemm_dma_accepts(const GemmProblem& p);
 hipError_t launch_gemm_dma(const GemmProblem& p, hipStream_t stream);
