@@ -3,6 +3,7 @@
 // the 3-channel input, and the fixed-order sum of split-k partial products.  Each moves every tensor through
 // HBM once, in 16-byte pieces along the channel index.
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -28,6 +29,7 @@ __device__ __forceinline__ uint16_t to_bf16(float v) { return bf16_round(v); }
 // Backward of z = scale * y + shift followed by an optional ReLU whose output is `act`:
 //   dz = dout * [act > 0]   (dz = dout without act);   dy = scale * dz;   dsum = dz (optional)
 //   partial[block][0][c] = sum over the block's rows of dz * y;   partial[block][1][c] = sum of dz
+// Without y the latter alone, partial[block][c]; without partial neither.
 // A workgroup takes a range of rows (blockIdx.x) of a slab of at most 256 channels (blockIdx.y), so that wide
 // tensors still give many workgroups while the partial sums stay small next to the tensor.  Thread t owns chunk
 // t % slab_chunks of the slab, rows (t / slab_chunks), (t / slab_chunks) + rows_per_pass, ...
@@ -52,9 +54,8 @@ __global__ __launch_bounds__(256) void affine_relu_bwd_kernel(const uint16_t* __
   if (active) {
     // two rows per trip, all their loads requested before the first is used
     auto finish = [&](size_t off, const u32x4& dw, const u32x4& yw, const u32x4& aw) {
-      float d[8], yv[8], o[8];
+      float d[8], o[8];
       unpack8(dw, d);
-      unpack8(yw, yv);
       if (act) {
         float a[8];
         unpack8(aw, a);
@@ -62,7 +63,13 @@ __global__ __launch_bounds__(256) void affine_relu_bwd_kernel(const uint16_t* __
         for (int e = 0; e < 8; ++e) if (!(a[e] > 0.f)) d[e] = 0.f;
       }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) { s1[e] += d[e] * yv[e]; s0[e] += d[e]; o[e] = sc[e] * d[e]; }
+      for (int e = 0; e < 8; ++e) { s0[e] += d[e]; o[e] = sc[e] * d[e]; }
+      if (y) {
+        float yv[8];
+        unpack8(yw, yv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s1[e] += d[e] * yv[e];
+      }
       *reinterpret_cast<u32x4*>(dy + off) = pack8(o);
       if (dsum) *reinterpret_cast<u32x4*>(dsum + off) = pack8(d);
     };
@@ -79,7 +86,7 @@ __global__ __launch_bounds__(256) void affine_relu_bwd_kernel(const uint16_t* __
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         d[u] = fetch(dout, off0 + u * pass);
-        yv[u] = fetch(y, off0 + u * pass);
+        yv[u] = y ? fetch(y, off0 + u * pass) : zero;
         a[u] = act ? fetch(act, off0 + u * pass) : zero;
       }
 #pragma unroll
@@ -87,9 +94,10 @@ __global__ __launch_bounds__(256) void affine_relu_bwd_kernel(const uint16_t* __
     }
     for (; r < last; r += rows_per_pass) {
       const size_t off = (size_t)r * channels + chunk * 8;
-      finish(off, fetch(dout, off), fetch(y, off), act ? fetch(act, off) : zero);
+      finish(off, fetch(dout, off), y ? fetch(y, off) : zero, act ? fetch(act, off) : zero);
     }
   }
+  if (!partial) return;
   if (lane_row < rows_per_pass) {  // lanes past the tensor's last chunk park zeros
     float* mine = sh + ((size_t)lane_row * slab_chunks + local_chunk) * 16;
 #pragma unroll
@@ -104,108 +112,158 @@ __global__ __launch_bounds__(256) void affine_relu_bwd_kernel(const uint16_t* __
     if (channel >= channels) continue;
     float acc = 0.f;
     for (int l = 0; l < rows_per_pass; ++l) acc += sh[((size_t)l * slab_chunks + (c >> 3)) * 16 + which * 8 + (c & 7)];
-    partial[((size_t)blockIdx.x * 2 + which) * channels + channel] = acc;
+    if (y) partial[((size_t)blockIdx.x * 2 + which) * channels + channel] = acc;
+    else if (which) partial[(size_t)blockIdx.x * channels + channel] = acc;
   }
 }
 
-// out_a[c] = sum_b partial[b][0][c], out_b[c] = sum_b partial[b][1][c].  A workgroup takes 16 neighbouring columns
-// (reduce_pairs_blocks workgroups in all): thread (g, c) adds blocks g, g + 16, ... of column c in order - the 16
-// threads of a group read 64 contiguous bytes, where one wavefront per column touched a cache line per lane - and
-// the 16 group sums of a column are added in group order: the same bits on every run.
-__device__ __forceinline__ void reduce_pairs_block(unsigned block, const float* __restrict__ partial, int n_blocks, int width,
-                                                   float* __restrict__ out_a, float* __restrict__ out_b) {
-  __shared__ float sh[16][17];
+// ---- small fixed-order reductions, many per launch (see ReduceTask) ----
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// (512: a row of the longest reductions, a 3x3 convolution of 64 channels in 128 slices, is one workgroup's: see reduce_rows_block)
+constexpr int kReduceThreads = 512;
+
+// p[0] + p[stride] + ... (every step-th of count slices from `from` on, in order): eight requested at a time, and what is left over four, two and
+// one at a time.  (An unrolled loop leaves up to seven to a loop that waits for each.)
+template <typename V>
+__device__ __forceinline__ V sum_slices(const V* __restrict__ p, size_t stride, int from, int count, int step) {
+  V s = {};
+  const V* at = p + (size_t)from * stride;
+  const size_t hop = (size_t)step * stride;
+  int left = from < count ? (count - from + step - 1) / step : 0;
+  auto take = [&](auto n) {
+    constexpr int N = decltype(n)::value;
+    V v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = at[i * hop];
+#pragma unroll
+    for (int i = 0; i < N; ++i) s += v[i];
+    at += N * hop;
+    left -= N;
+  };
+  while (left >= 8) take(std::integral_constant<int, 8>{});
+  if (left >= 4) take(std::integral_constant<int, 4>{});
+  if (left >= 2) take(std::integral_constant<int, 2>{});
+  if (left >= 1) take(std::integral_constant<int, 1>{});
+  return s;
+}
+
+// Column sums of partial [count][columns].  A workgroup takes 16 neighbouring columns: thread (g, c) adds rows g, g + 32, ... of
+// column c in order - the 16 threads of a group read 64 contiguous bytes, where one wavefront per column touched a cache line
+// per lane - and the 32 group sums of a column are added in group order: the same bits on every run.
+__device__ __forceinline__ void reduce_columns_block(unsigned block, const ReduceTask& k) {
+  constexpr int kGroups = kReduceThreads / 16;
+  __shared__ float sh[kGroups][17];
+  const bool pairs = k.kind == ReduceTask::kPairs;
+  const int columns = pairs ? 2 * k.width : k.width;
   const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
   const int col = block * 16 + c;
-  float s = 0.f;
-  if (col < 2 * width) {
-#pragma unroll 8
-    for (int b = g; b < n_blocks; b += 16) s += partial[(size_t)b * 2 * width + col];
-  }
-  sh[g][c] = s;
+  sh[g][c] = col < columns ? sum_slices(k.partial + col, columns, g, k.count, kGroups) : 0.f;
   __syncthreads();
-  if (threadIdx.x < 16 && col < 2 * width) {
+  if (threadIdx.x < 16 && col < columns) {
     float t = 0.f;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) t += sh[q][c];
-    if (col < width) out_a[col] = t;
-    else out_b[col - width] = t;
+    for (int q = 0; q < kGroups; ++q) t += sh[q][c];
+    if (col < k.width) k.out[col] = t;
+    if (pairs && col >= k.width) k.out_b[col - k.width] = t;
+    if (!pairs && k.out_b) k.out_b[col] = t;
   }
-}
-__global__ __launch_bounds__(256) void reduce_pairs_kernel(const float* __restrict__ partial, int n_blocks, int width,
-                                                           float* __restrict__ out_a, float* __restrict__ out_b) {
-  reduce_pairs_block(blockIdx.x, partial, n_blocks, width, out_a, out_b);
 }
 
 // out[j] = sum over slices of partial[slice][map(j)], slices added in index order; map drops padded input channels.
 __device__ __forceinline__ void splitk_reduce_block(unsigned block, const float* __restrict__ partial, int slices, long long slice_stride,
                                                     float* __restrict__ out, long long numel, int cin, int cin_padded) {
-  const long long j = (long long)block * 256 + threadIdx.x;
+  const long long j = (long long)block * kReduceThreads + threadIdx.x;
   if (j >= numel) return;
   const long long src = cin == cin_padded ? j : (j / cin) * cin_padded + (j % cin);
-  float s = 0.f;
-  for (int z = 0; z < slices; ++z) s += partial[(size_t)z * slice_stride + src];
-  out[j] = s;
-}
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int slices, long long slice_stride,
-                                                            float* __restrict__ out, long long numel, int cin, int cin_padded) {
-  splitk_reduce_block(blockIdx.x, partial, slices, slice_stride, out, numel, cin, cin_padded);
+  out[j] = sum_slices(partial + src, slice_stride, 0, slices, 1);
 }
 
-// The same for tensors without channel padding, four neighbouring elements per thread and four slices requested
-// at a time (the additions still run in slice order).
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// The same for tensors without channel padding, four neighbouring elements per thread.
 __device__ __forceinline__ void splitk_reduce4_block(unsigned block, const f32x4* __restrict__ partial, int slices, long long slice_stride4,
                                                      f32x4* __restrict__ out, long long numel4) {
-  const long long j = (long long)block * 256 + threadIdx.x;
-  if (j >= numel4) return;
-  f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  int z = 0;
-  for (; z + 4 <= slices; z += 4) {
-    const f32x4 a = partial[(size_t)z * slice_stride4 + j], b = partial[(size_t)(z + 1) * slice_stride4 + j];
-    const f32x4 c = partial[(size_t)(z + 2) * slice_stride4 + j], d = partial[(size_t)(z + 3) * slice_stride4 + j];
-    s += a; s += b; s += c; s += d;
-  }
-  for (; z < slices; ++z) s += partial[(size_t)z * slice_stride4 + j];
-  out[j] = s;
+  const long long j = (long long)block * kReduceThreads + threadIdx.x;
+  if (j < numel4) out[j] = sum_slices(partial + j, slice_stride4, 0, slices, 1);
 }
-// Many slices: 32 groups of four elements per workgroup and eight threads on each, which take every eighth slice; their sums are added
-// in order.  (One thread a group: 9216 threads with 39 slices each, 18 to 27 us beside the input-gradient chain.)
+// Many slices: 32 groups of four elements per workgroup and sixteen threads on each, which take every sixteenth slice; their sums are
+// added in order.  (One thread a group: 9216 threads with 39 slices each, 18 to 27 us beside the input-gradient chain.)
 constexpr int kWideSlices = 16;
 __device__ __forceinline__ void splitk_reduce4_wide_block(unsigned block, const f32x4* __restrict__ partial, int slices, long long slice_stride4,
-                                                          f32x4* __restrict__ out, long long numel4) {
-  __shared__ f32x4 sh[8][32];
+                                                          f32x4* __restrict__ out, long long numel4, f32x4* sh) {
+  constexpr int kPhases = kReduceThreads / 32;
   const int c = threadIdx.x & 31, phase = threadIdx.x >> 5;
   const long long j = (long long)block * 32 + c;
   f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  if (j < numel4) {
-#pragma unroll 4
-    for (int z = phase; z < slices; z += 8) s += partial[(size_t)z * slice_stride4 + j];
-  }
-  sh[phase][c] = s;
+  if (j < numel4) s = sum_slices(partial + j, slice_stride4, phase, slices, kPhases);
+  sh[threadIdx.x] = s;
   __syncthreads();
   if (phase == 0 && j < numel4) {
 #pragma unroll
-    for (int q = 1; q < 8; ++q) s += sh[q][c];
+    for (int q = 1; q < kPhases; ++q) s += sh[q * 32 + c];
     out[j] = s;
   }
 }
-__global__ __launch_bounds__(256) void splitk_reduce4_kernel(const f32x4* __restrict__ partial, int slices, long long slice_stride4,
-                                                             f32x4* __restrict__ out, long long numel4) {
-  splitk_reduce4_block(blockIdx.x, partial, slices, slice_stride4, out, numel4);
+
+// Output channels of a convolution's weight gradient (see make_conv_weight_task): S[k] = sum over the slices, dW[k] = scale * S[k],
+// dscale = sum_k w[k] * S[k], k in groups of four.  k.threads threads (a power of two, 64 to 512) have a channel's whole row, so the dot product
+// needs no second pass.  Rows of fewer groups than that share the slices out among threads / row of them per group, whose sums are added
+// in order.  As few threads as leave each six loads or fewer (1024 rows of 64 groups in 12 slices, beside the input-gradient chain: 19 us with a
+// workgroup per row, 13 with a wavefront; 512 of 32 in 48: 27 and, with 12 loads each, 38).
+__device__ __forceinline__ void reduce_rows_block(unsigned block, const ReduceTask& k, f32x4* sh) {
+  __shared__ float dots[kReduceThreads / 64];
+  const int n = k.width, t = threadIdx.x & (k.threads - 1), first = threadIdx.x - t;   // place in the row's threads, and theirs in the workgroup
+  const int row = block * (kReduceThreads / k.threads) + first / k.threads;
+  const bool exists = row < k.rows;
+  const f32x4* partial = reinterpret_cast<const f32x4*>(k.partial) + (size_t)row * n;
+  const uint2* w = static_cast<const uint2*>(k.weight) + (size_t)row * n;
+  f32x4* out = reinterpret_cast<f32x4*>(k.out) + (size_t)row * n;
+  const float sc = exists ? bf(static_cast<const uint16_t*>(k.scale)[row]) : 0.f;
+  float dot = 0.f;
+  auto finish = [&](int c, const f32x4& s) {
+    const uint2 b = w[c];
+    out[c] = s * sc;
+    dot += __uint_as_float(b.x << 16) * s[0] + __uint_as_float(b.x & 0xFFFF0000u) * s[1] + __uint_as_float(b.y << 16) * s[2] +
+           __uint_as_float(b.y & 0xFFFF0000u) * s[3];
+  };
+  auto sum = [&](int c, int from, int step) { return sum_slices(partial + c, k.stride, from, k.count, step); };
+  const int phases = k.threads / n;
+  if (phases <= 1) {
+    if (exists)
+      for (int c = t; c < n; c += k.threads) finish(c, sum(c, 0, 1));
+  } else {
+    const int phase = t / n, c = t - phase * n;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    if (exists && phase < phases) s = sum(c, phase, phases);
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    if (exists && t < n) {
+      for (int q = 1; q < min(phases, k.count); ++q) s += sh[first + q * n + t];
+      finish(t, s);
+    }
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) dot += __shfl_xor(dot, d);
+  if ((threadIdx.x & 63) == 0) dots[threadIdx.x >> 6] = dot;
+  __syncthreads();
+  if (exists && t == 0) {
+    float v = dots[first / 64];
+    for (int q = 1; q < k.threads / 64; ++q) v += dots[first / 64 + q];
+    k.out_b[row] = v;
+  }
 }
 
 // Several of the reductions above in one launch: the column sums of a unit's affine backward passes and the k-slice
 // sums of its weight gradients are a handful of tiny kernels each bound by its launch; a table in the kernel
-// arguments says which range of workgroups does which, with the arithmetic (and so the bits) of the kernels above.
-__global__ __launch_bounds__(256) void unit_reduce_kernel(ReduceTable t) {
+// arguments says which range of workgroups does which.
+__global__ __launch_bounds__(kReduceThreads) void unit_reduce_kernel(ReduceTable t) {
+  __shared__ f32x4 sh[kReduceThreads];
   int i = 0;
   while (i + 1 < t.n && blockIdx.x >= t.end_block[i]) ++i;
   const unsigned block = blockIdx.x - (i ? t.end_block[i - 1] : 0u);
   const ReduceTask& k = t.task[i];
-  if (k.kind == ReduceTask::kPairs) reduce_pairs_block(block, k.partial, k.count, k.width, k.out, k.out_b);
+  if (k.kind == ReduceTask::kPairs || k.kind == ReduceTask::kColumns) reduce_columns_block(block, k);
+  else if (k.kind == ReduceTask::kRows4) reduce_rows_block(block, k, sh);
   else if (k.kind == ReduceTask::kSlices4Wide)
-    splitk_reduce4_wide_block(block, reinterpret_cast<const f32x4*>(k.partial), k.count, k.stride, reinterpret_cast<f32x4*>(k.out), k.numel);
+    splitk_reduce4_wide_block(block, reinterpret_cast<const f32x4*>(k.partial), k.count, k.stride, reinterpret_cast<f32x4*>(k.out), k.numel, sh);
   else if (k.kind == ReduceTask::kSlices4)
     splitk_reduce4_block(block, reinterpret_cast<const f32x4*>(k.partial), k.count, k.stride, reinterpret_cast<f32x4*>(k.out), k.numel);
   else splitk_reduce_block(block, k.partial, k.count, k.stride, k.out, k.numel, k.cin, k.cin_padded);
@@ -361,23 +419,44 @@ size_t affine_partial_floats(long long rows, int channels) {
 
 hipError_t launch_affine_relu_bwd(const void* dout, const void* act, const void* y, const void* scale, void* dy, void* dsum,
                                   float* partial, float* dscale, float* dshift, long long rows, int channels, hipStream_t s, ReduceTask* deferred) {
-  if (!dout || !y || !scale || !dy || !partial || !dscale || !dshift || rows <= 0 || channels <= 0 || channels % 8 || channels > 2048)
-    return hipErrorInvalidValue;
+  if (!dout || !scale || !dy || rows <= 0 || channels <= 0 || channels % 8 || channels > 2048) return hipErrorInvalidValue;
+  if (partial ? !dshift || !deferred || (y && !dscale) : y != nullptr) return hipErrorInvalidValue;
   const int rpb = affine_rows_per_block(rows, channels);
   const int blocks = (int)((rows + rpb - 1) / rpb);
   const int slab_chunks = affine_slab_chunks(channels);
   const size_t lds = (size_t)(256 / slab_chunks) * slab_chunks * 16 * sizeof(float);
   hipLaunchKernelGGL(affine_relu_bwd_kernel, dim3(blocks, affine_slabs(channels)), dim3(256), lds, s, (const uint16_t*)dout, (const uint16_t*)act,
                      (const uint16_t*)y, (const uint16_t*)scale, (uint16_t*)dy, (uint16_t*)dsum, partial, rows, channels, rpb);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (deferred) {   // the caller adds the column sums up later (launch_unit_reduce)
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  if (partial && y) {   // the caller adds the column sums up later (launch_unit_reduce)
     deferred->kind = ReduceTask::kPairs; deferred->partial = partial; deferred->count = blocks; deferred->width = channels;
     deferred->out = dscale; deferred->out_b = dshift; deferred->blocks = reduce_pairs_blocks(channels);
-    return hipSuccess;
+  } else if (partial) {
+    *deferred = make_columns_task(partial, blocks, channels, dshift, nullptr);
   }
-  hipLaunchKernelGGL(reduce_pairs_kernel, dim3(reduce_pairs_blocks(channels)), dim3(256), 0, s, partial, blocks, channels, dscale, dshift);
-  return hipGetLastError();
+  return hipSuccess;
+}
+
+ReduceTask make_columns_task(const float* partial, int count, int width, float* out, float* out_copy) {
+  ReduceTask t;
+  t.kind = ReduceTask::kColumns; t.partial = partial; t.count = count; t.width = width; t.out = out; t.out_b = out_copy;
+  t.blocks = (unsigned)((width + 15) / 16);
+  return t;
+}
+
+bool make_conv_weight_task(const float* partial, int slices, int channels, int row, const void* weight, const void* scale, float* dw, float* dscale,
+                           ReduceTask* task) {
+  if (!partial || !weight || !scale || !dw || !dscale || !task || slices < 1 || channels <= 0 || row <= 0 || row % 4 ||
+      ((reinterpret_cast<uintptr_t>(partial) | reinterpret_cast<uintptr_t>(weight) | reinterpret_cast<uintptr_t>(dw)) & 15))
+    return false;
+  task->kind = ReduceTask::kRows4;
+  task->partial = partial; task->count = slices; task->width = row / 4; task->stride = (long long)channels * (row / 4);
+  task->weight = weight; task->scale = scale; task->out = dw; task->out_b = dscale;
+  task->rows = channels;
+  task->threads = 64;
+  while (task->threads < kReduceThreads && (long long)task->width * slices > 6LL * task->threads) task->threads *= 2;
+  task->blocks = (unsigned)((channels + kReduceThreads / task->threads - 1) / (kReduceThreads / task->threads));
+  return true;
 }
 
 bool make_splitk_reduce_task(const float* partial, int slices, long long slice_stride, float* out, long long numel, int cin, int cin_padded,
@@ -392,7 +471,7 @@ bool make_splitk_reduce_task(const float* partial, int slices, long long slice_s
   } else {
     task->kind = ReduceTask::kSlices; task->stride = slice_stride; task->numel = numel;
   }
-  task->blocks = task->kind == ReduceTask::kSlices4Wide ? (unsigned)((task->numel + 31) / 32) : blocks_for(task->numel);
+  task->blocks = task->kind == ReduceTask::kSlices4Wide ? (unsigned)((task->numel + 31) / 32) : (unsigned)((task->numel + kReduceThreads - 1) / kReduceThreads);
   return true;
 }
 
@@ -408,23 +487,10 @@ hipError_t launch_unit_reduce(const ReduceTask* tasks, int n, hipStream_t s) {
       end += t.task[i].blocks;
       t.end_block[i] = end;
     }
-    hipLaunchKernelGGL(unit_reduce_kernel, dim3(end), dim3(256), 0, s, t);
+    hipLaunchKernelGGL(unit_reduce_kernel, dim3(end), dim3(kReduceThreads), 0, s, t);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
   return hipSuccess;
-}
-
-hipError_t launch_splitk_reduce(const float* partial, int slices, long long slice_stride, float* out, long long numel, int cin, int cin_padded,
-                                hipStream_t s) {
-  if (!partial || !out || slices < 1 || numel <= 0 || cin <= 0 || cin_padded < cin) return hipErrorInvalidValue;
-  if (cin == cin_padded && numel % 4 == 0 && slice_stride % 4 == 0 && (reinterpret_cast<uintptr_t>(partial) & 15) == 0 &&
-      (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
-    hipLaunchKernelGGL(splitk_reduce4_kernel, dim3(blocks_for(numel / 4)), dim3(256), 0, s, reinterpret_cast<const f32x4*>(partial), slices,
-                       slice_stride / 4, reinterpret_cast<f32x4*>(out), numel / 4);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks_for(numel)), dim3(256), 0, s, partial, slices, slice_stride, out, numel, cin, cin_padded);
-  return hipGetLastError();
 }
 
 hipError_t launch_splitk_reduce_bf16(const float* partial, int slices, long long slice_stride, void* out, long long numel, hipStream_t s) {

@@ -773,7 +773,8 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
     for (int e = 0; e < 8; ++e) { s_dzy[e] = 0.f; s_dz[e] = 0.f; }
     // A lane's units (8 outputs each) in order: piece by piece, kIters rows per piece.  The two per-element chunks
     // of unit u + 2 are requested before unit u is worked out and stored: three sets of registers in rotation, and
-    // waiting for a chunk never waits for a store issued after it.
+    // waiting for a chunk never waits for a store issued after it.  The affine's input is read only where somebody kept it (not at
+    // a unit's output, see make_conv_weight_task: 200704 x 256 over k = 64 with all other tensors 133 -> 120 us in the step).
     constexpr int kUnits = TM * kIters;
     auto unit_row = [&](int u) { return (u / kIters) * 32 + row0 + (u % kIters) * kRowStep; };
     // Optional: a second gradient that joins the product before the rounding (the shortcut's, where the product is a
@@ -785,7 +786,7 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
       if (!active) return;
       const size_t row = (size_t)near_row(min(unit_row(u), WM - 1));   // a clamped, always valid row
       a = *reinterpret_cast<const u32x4*>(xsrc + row * ldx + n);
-      y = *reinterpret_cast<const u32x4*>(ysrc + row * p.ldy + n);
+      if (ysrc) y = *reinterpret_cast<const u32x4*>(ysrc + row * p.ldy + n);
       if (rsrc) r = *reinterpret_cast<const u32x4*>(rsrc + row * p.ldres + n);
     };
     request2(0, ab[0], yb[0], rb[0]);
@@ -814,13 +815,16 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
         }
         unpack_bf16x8(pack_bf16x8(v), d);   // the gradient as a separate pass would have read it back from memory
         unpack_bf16x8(ab[u % 3], a);
-        unpack_bf16x8(yb[u % 3], y);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           if (!(a[e] > 0.f)) d[e] = 0.f;
-          s_dzy[e] += d[e] * y[e];
           s_dz[e] += d[e];
           o[e] = sc[e] * d[e];
+        }
+        if (ysrc) {
+          unpack_bf16x8(yb[u % 3], y);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s_dzy[e] += d[e] * y[e];
         }
         const size_t m = row_at(i * 32 + row);
         if (dz_out) *reinterpret_cast<u32x4*>(dz_out + m * p.ldaux + n) = pack_bf16x8(d);   // exact: d is bfloat16 already
@@ -864,7 +868,9 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
 #pragma unroll
         for (int w = 0; w < WAVES_M; ++w) t += stage[w * (32 * kPitch) + col];   // wave wm + WAVES_M * wn: this column block's waves lie side by side
         const int which = col / WN, cn = col_base + col % WN;
-        if (cn < p.N) p.col_partial[((size_t)tile_m * 2 + which) * p.N + cn] = t;
+        if (cn >= p.N) continue;
+        if (ysrc) p.col_partial[((size_t)tile_m * 2 + which) * p.N + cn] = t;
+        else if (which) p.col_partial[(size_t)tile_m * p.N + cn] = t;
       }
     }
     return;

@@ -31,7 +31,8 @@ enum class Epilogue : int {
   // ReLU's output: d = acc rounded to T (what a separate pass would have read back), dz = mask[m, n] > 0 ? d : 0,
   // C (T) = col_scale[n] * dz, and per tile row of the product col_partial[tile_m][0][n] = sum over its rows of
   // dz * affine_y[m, n], col_partial[tile_m][1][n] = sum of dz (float32; reduce_pairs adds the tile rows up).
-  // With residual: d = acc + residual[m, n] before the rounding; with aux_out: aux_out (T) = dz.
+  // With residual: d = acc + residual[m, n] before the rounding; with aux_out: aux_out (T) = dz.  Without affine_y: the sums of dz
+  // alone, col_partial[tile_m][n].
   AffineBwdStore = 4,
 };
 
@@ -93,7 +94,7 @@ struct GemmProblem {
   bool beside = false;            // runs beside the chain of another stream: the CUs it leaves to that count for more than its own time
   bool b_in_hbm = false;          // B is weights that other traffic has driven out of the caches: see touch_lines
   float* a_row_sum = nullptr;     // optional [M]: sum_k A(m, k), written once by the tiles of column block 0
-  // AffineBwdStore: the affine's input (pre-affine convolution output), the partial column sums [tile rows][2][N]
+  // AffineBwdStore: the affine's input (pre-affine convolution output; may be null), the partial column sums [tile rows][2 or 1][N]
   // (room for (M + 63) / 64 tile rows and col_partial_spare more: taken by parity, four classes of pixels may each end in a tile of
   // their own) and where the launcher reports how many tile rows it wrote
   const void* affine_y = nullptr;
@@ -161,16 +162,16 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t stream);
 
 // ---- memory-bound kernels of the residual-CNN units (NHWC bfloat16, channels % 8 == 0, <= 2048) ----
 // Backward of "per-channel affine, then optional ReLU whose output is act": dz = dout * [act > 0] (dz = dout if act is
-// null); dy = scale * dz; dsum = dz (optional); dscale[c] = sum dz * y; dshift[c] = sum dz (float32, overwritten).
-// partial: scratch of affine_partial_floats(rows, channels) floats.
-// With `deferred` the column sums stay per-workgroup partial sums and *deferred describes the reduction that finishes
-// them (for launch_unit_reduce); dscale and dshift are written by that reduction.
+// null); dy = scale * dz; dsum = dz (optional).  With `partial` (scratch of affine_partial_floats(rows, channels) floats) the
+// column sums for dscale[c] = sum dz * y and dshift[c] = sum dz too, as per-workgroup partial sums: *deferred describes the
+// reduction that finishes them (for launch_unit_reduce).  Without y: dshift only.
 size_t affine_partial_floats(long long rows, int channels);
 // One small fixed-order reduction: kPairs = the column sums of an affine backward pass (partial [count][2][width] ->
-// out [width], out_b [width]); kSlices / kSlices4 = the k-slices of a weight gradient (see launch_splitk_reduce;
-// kSlices4 and, for many slices, kSlices4Wide count in groups of four floats).  blocks = workgroups it takes.
+// out [width], out_b [width]); kColumns = single column sums (partial [count][width] -> out [width], and a copy in out_b if given); kSlices /
+// kSlices4 = the k-slices of a weight gradient (kSlices4 and, for many slices, kSlices4Wide count in groups of four floats); kRows4 = those of
+// a weight gradient and what follows from them (see make_conv_weight_task).  blocks = workgroups it takes.
 struct ReduceTask {
-  enum Kind { kPairs = 0, kSlices4 = 1, kSlices = 2, kSlices4Wide = 3 };
+  enum Kind { kPairs = 0, kSlices4 = 1, kSlices = 2, kSlices4Wide = 3, kColumns = 4, kRows4 = 5 };
   int kind = kPairs;
   const float* partial = nullptr;
   int count = 0, width = 0;
@@ -178,6 +179,9 @@ struct ReduceTask {
   float* out = nullptr;
   float* out_b = nullptr;
   int cin = 0, cin_padded = 0;
+  const void* weight = nullptr;
+  const void* scale = nullptr;
+  int rows = 0, threads = 0;
   unsigned blocks = 0;
 };
 inline unsigned reduce_pairs_blocks(int width) { return (unsigned)((2 * width + 15) / 16); }   // workgroups of a kPairs task
@@ -189,16 +193,20 @@ struct ReduceTable {
 };
 hipError_t launch_affine_relu_bwd(const void* dout, const void* act, const void* y, const void* scale, void* dy, void* dsum,
                                   float* partial, float* dscale, float* dshift, long long rows, int channels, hipStream_t s,
-                                  ReduceTask* deferred = nullptr);
-// The reduction launch_splitk_reduce would run, as a task; false if the arguments are not valid.
+                                  ReduceTask* deferred);
+ReduceTask make_columns_task(const float* partial, int count, int width, float* out, float* out_copy);
+// The gradients of a convolution's weights and of the per-channel scale behind it, from the k-slices partial [slices][channels][row] of
+// S = sum over pixels of dz (x) input patch, where dz is the gradient at the affine's output: dw = scale * S and dscale = sum over a
+// channel's weights of w * S.  The latter is the sum of dz times the convolution's output y, which therefore nobody has to
+// keep: y = sum w * patch, so sum dz * y = sum w * (sum dz * patch).  False if the arguments are not valid (row must be a multiple of 4).
+bool make_conv_weight_task(const float* partial, int slices, int channels, int row, const void* weight, const void* scale, float* dw, float* dscale,
+                           ReduceTask* task);
+// out[j] = sum over slices of partial[slice * slice_stride + map(j)], j < numel; map(j) = j, or with cin < cin_padded
+// (j / cin) * cin_padded + j % cin (drops the zero channels a 3-channel input was padded with), as a task; false if the arguments are not valid.
 bool make_splitk_reduce_task(const float* partial, int slices, long long slice_stride, float* out, long long numel, int cin, int cin_padded,
                              ReduceTask* task);
-// All of the tasks in one launch (several if there are more than ReduceTable::kMax), same bits as one launch each.
+// All of the tasks in one launch (several if there are more than ReduceTable::kMax).
 hipError_t launch_unit_reduce(const ReduceTask* tasks, int n, hipStream_t s);
-// out[j] = sum over slices of partial[slice * slice_stride + map(j)], j < numel; map(j) = j, or with cin < cin_padded
-// (j / cin) * cin_padded + j % cin (drops the zero channels a 3-channel input was padded with).
-hipError_t launch_splitk_reduce(const float* partial, int slices, long long slice_stride, float* out, long long numel, int cin, int cin_padded,
-                                hipStream_t s);
 // out[j] (bfloat16) = sum over slices of partial[slice * slice_stride + j], j < numel; numel a multiple of 8, 16-byte aligned.
 hipError_t launch_splitk_reduce_bf16(const float* partial, int slices, long long slice_stride, void* out, long long numel, hipStream_t s);
 // 3x3 / stride 2 / padding 1 max-pool of x [n, h, w, c]; which (optional, [n, oh, ow, c]) records the winning window position.

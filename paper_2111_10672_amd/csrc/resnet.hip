@@ -8,10 +8,14 @@
 //   input gradient   dx[pixel, ci]   = sum_{tap, co} dy[(pixel - tap) / stride][co] * w[co][tap][ci]
 //   weight gradient  dw[co][tap][ci] = sum_pixel dy[pixel][co] * x[pixel + tap][ci]            k cut into slices
 // The per-channel affine that follows each convolution (a BatchNorm folded to scale and shift, kept
-// trainable), the ReLU and the residual add ride in the forward product's epilogue, which also writes the
-// pre-affine output a unit above the cut keeps for the scale gradient.  Backward, one memory-bound kernel per
-// convolution turns the incoming gradient into dy and the scale/shift gradients; the shortcut's gradient
-// joins in the epilogue of the block's first input-gradient product.
+// trainable), the ReLU and the residual add ride in the forward product's epilogue.
+// Backward, the masked gradient dz at an affine's output gives dy = scale * dz, which the input-gradient product reads, the
+// gradient of the shift (column sums of dz), and that of the scale:
+//   inside a unit            sum of dz * y, with the pre-affine output y that the forward pass of a unit above the cut keeps;
+//   at a unit's output       dz is in memory anyway, for the shortcut, so the weight gradients of the last convolution and of the projection
+//                            are formed from it: S = sum over pixels of dz (x) patch, dw = scale * S, and the scale's gradient is
+//                            sum over a channel's weights of w * S.  No y is kept, written or read there.
+// All but the lowest unit's first dz form in the epilogue of the input-gradient product above, where the shortcut's gradient joins too.
 #include <algorithm>
 #include <cmath>
 
@@ -37,10 +41,10 @@ struct Block {
 };
 
 // Offsets of one unit's tensors in the workspace.
-struct ConvBuf { size_t y = 0, a = 0; };   // pre-affine output (kept only above the cut), post-activation output
+struct ConvBuf { size_t y = 0, a = 0; };   // pre-affine output (kept only above the cut, and not at a unit's output), post-activation output
 struct UnitBuf {
   std::vector<ConvBuf> conv;    // main-path convolutions; the last one's `a` is the unit's output
-  ConvBuf proj;                 // projection shortcut: y = pre-affine, a = its affine output
+  size_t proj = 0;              // projection shortcut: its affine output
   size_t xpad = 0, wpad = 0, pool_out = 0, which = 0;  // stem only
   size_t out = 0;               // the unit's output tensor
 };
@@ -204,14 +208,13 @@ class ResnetModel : public Model {
       const bool keep = unit >= cut, keep_out = keep || unit + 1 >= cut;
       u.conv.resize(b.convs.size());
       if (b.has_proj) {
-        u.proj.y = keep ? take(act_bytes(b.proj.out_rows(batch_), b.proj.cout)) : 0;
-        u.proj.a = transient();   // only the forward pass reads the shortcut's output
+        u.proj = transient();   // only the forward pass reads the shortcut's output
       }
       for (size_t j = 0; j < b.convs.size(); ++j) {
         const Conv& c = b.convs[j];
         const size_t bytes = act_bytes(c.out_rows(batch_), c.cout);
         const bool last = j + 1 == b.convs.size();
-        u.conv[j].y = keep ? take(bytes) : 0;
+        u.conv[j].y = keep && !last ? take(bytes) : 0;
         u.conv[j].a = (last ? keep_out : keep) ? take(bytes) : transient();
       }
       u.out = u.conv.back().a;
@@ -304,9 +307,9 @@ class ResnetModel : public Model {
   // take that epilogue (the caller then runs the two passes), 0 or an error code otherwise.
   // With `residual` (a second gradient of the same tensor: the shortcut's) the sum of the two is what the ReLU masks,
   // and dz_out (optional) receives that masked sum: the form for a unit's LAST input gradient, which then also does
-  // the affine pass at the output of the unit below.
+  // the affine pass at the output of the unit below; it has no `y`, and shift_copy (optional) receives the shift's gradient once more.
   int conv_dgrad_affine(const Conv& c, const void* dy, const void* w, const Conv& below, const void* act, const void* y, void* dy_below,
-                        float* partial, int spare_rows, hipStream_t s, const void* residual = nullptr, void* dz_out = nullptr) {
+                        float* partial, int spare_rows, hipStream_t s, const void* residual = nullptr, void* dz_out = nullptr, float* shift_copy = nullptr) {
     GemmProblem g;
     g.dtype = dtype; g.a_layout = Layout::RowK; g.b_layout = Layout::KRow; g.epilogue = Epilogue::AffineBwdStore;
     if (!pointwise(c)) {
@@ -326,15 +329,22 @@ class ResnetModel : public Model {
     if (int rc = gemm(g, s)) return rc;
     ReduceTask task;
     const int tile_rows = fused_tile_rows_;
-    task.kind = ReduceTask::kPairs; task.partial = partial; task.count = tile_rows; task.width = below.cout;
-    task.out = static_cast<float*>(grad_ptrs[below.scale]); task.out_b = static_cast<float*>(grad_ptrs[below.shift]);
-    task.blocks = reduce_pairs_blocks(below.cout);
-    reduce_bytes_ += (double)tile_rows * 2 * below.cout * 4;
+    if (y) {
+      task.kind = ReduceTask::kPairs; task.partial = partial; task.count = tile_rows; task.width = below.cout;
+      task.out = static_cast<float*>(grad_ptrs[below.scale]); task.out_b = static_cast<float*>(grad_ptrs[below.shift]);
+      task.blocks = reduce_pairs_blocks(below.cout);
+    } else {
+      task = make_columns_task(partial, tile_rows, below.cout, static_cast<float*>(grad_ptrs[below.shift]), shift_copy);
+    }
+    reduce_bytes_ += (double)tile_rows * (y ? 2 : 1) * below.cout * 4;
     reduces_.push_back(task);
     return SPB_OK;
   }
-  // dw = sum over pixels of dy (x) x-patch, as k-slices added up in a fixed order
-  int conv_wgrad(const Conv& c, const void* x, const void* dy, float* partial, float* dw, hipStream_t s) {
+  // A projection's affine meets the same dz as its unit's last convolution: its shift has the same gradient.
+  float* projection_shift(const Block& b) const { return b.has_proj ? static_cast<float*>(grad_ptrs[b.proj.shift]) : nullptr; }
+  // dw = sum over pixels of dy (x) x-patch, as k-slices added up in a fixed order; from_dz: dy is dz, and the scale's gradient follows too
+  int conv_wgrad(const Conv& c, const void* x, const void* dy, float* partial, bool from_dz, hipStream_t s) {
+    float* dw = static_cast<float*>(grad_ptrs[c.w]);
     GemmProblem g;
     g.dtype = dtype; g.a_layout = Layout::KRow; g.b_layout = Layout::KRow; g.epilogue = Epilogue::StoreF32;
     if (!pointwise(c)) { g.b_gather = Gather::ConvPatchT; g.conv = geom(c); }
@@ -345,19 +355,24 @@ class ResnetModel : public Model {
     if (int rc = gemm(g, s)) return rc;
     const long long numel = (long long)c.cout * c.k * c.k * c.cin;
     ReduceTask task;   // the k-slices are added up with the unit's other small reductions
-    if (!make_splitk_reduce_task(partial, g.k_splits, (long long)c.cout * g.N, dw, numel, c.cin, c.cin_eff, &task)) return check(hipErrorInvalidValue, "weight-gradient reduction");
-    reduce_bytes_ += (double)(g.k_splits + 1) * numel * 4;
+    const bool ok = from_dz ? make_conv_weight_task(partial, g.k_splits, c.cout, g.N, param_ptrs[c.w], param_ptrs[c.scale], dw,
+                                                    static_cast<float*>(grad_ptrs[c.scale]), &task)
+                            : make_splitk_reduce_task(partial, g.k_splits, (long long)c.cout * g.N, dw, numel, c.cin, c.cin_eff, &task);
+    if (!ok) return check(hipErrorInvalidValue, "weight-gradient reduction");
+    reduce_bytes_ += (double)(g.k_splits + 1) * numel * 4 + (from_dz ? 2.0 * numel : 0.0);
     reduces_.push_back(task);
     return SPB_OK;
   }
-  // gradient at the affine's output -> dy, dscale, dshift (and the masked gradient itself, if asked for)
-  int affine_bwd(const Conv& c, const void* dout, const void* act, const void* y, void* dy, void* dsum, float* partial, hipStream_t s) {
+  // gradient at the affine's output -> dy, dscale (with y), dshift (and the masked gradient itself, if asked for)
+  int affine_bwd(const Conv& c, const void* dout, const void* act, const void* y, void* dy, void* dsum, float* partial, hipStream_t s, float* shift_copy = nullptr) {
     const long long rows = c.out_rows(batch_);
     ReduceTask task;
-    if (int rc = run("affine_relu_bwd", (double)rows * c.cout * 2 * (3 + (act ? 1 : 0) + (dsum ? 1 : 0)), s, [&] {
+    if (int rc = run("affine_relu_bwd", (double)rows * c.cout * 2 * (2 + (y ? 1 : 0) + (act ? 1 : 0) + (dsum ? 1 : 0)), s, [&] {
           return launch_affine_relu_bwd(dout, act, y, param_ptrs[c.scale], dy, dsum, partial, static_cast<float*>(grad_ptrs[c.scale]),
                                         static_cast<float*>(grad_ptrs[c.shift]), rows, c.cout, s, &task); })) return rc;
-    reduce_bytes_ += (double)task.count * 2 * c.cout * 4;
+    if (!partial) return SPB_OK;
+    if (shift_copy) task.out_b = shift_copy;   // (only without y)
+    reduce_bytes_ += (double)task.count * (y ? 2 : 1) * c.cout * 4;
     reduces_.push_back(task);
     return SPB_OK;
   }
@@ -402,13 +417,13 @@ class ResnetModel : public Model {
       const bool keep = (int)i + 1 >= cut;
       const void* shortcut = cur;
       if (b.has_proj) {
-        if (int rc = conv_forward(b.proj, cur, param_ptrs[b.proj.w], keep_ptr(keep, u.proj.y), nullptr, false, w + u.proj.a, s)) return rc;
-        shortcut = w + u.proj.a;
+        if (int rc = conv_forward(b.proj, cur, param_ptrs[b.proj.w], nullptr, nullptr, false, w + u.proj, s)) return rc;
+        shortcut = w + u.proj;
       }
       const void* h = cur;
       for (size_t j = 0; j < b.convs.size(); ++j) {
         const bool last = j + 1 == b.convs.size();
-        if (int rc = conv_forward(b.convs[j], h, param_ptrs[b.convs[j].w], keep_ptr(keep, u.conv[j].y), last ? shortcut : nullptr, true,
+        if (int rc = conv_forward(b.convs[j], h, param_ptrs[b.convs[j].w], keep_ptr(keep && !last, u.conv[j].y), last ? shortcut : nullptr, true,
                                   w + u.conv[j].a, s)) return rc;
         h = w + u.conv[j].a;
       }
@@ -494,11 +509,11 @@ class ResnetModel : public Model {
       // the block's output gradient, masked by its ReLU, feeds the last convolution's affine and the shortcut (where
       // the unit above could fuse that pass into its last product, dy and dsum are there already)
       if (!incoming_fused)
-        if (int rc = affine_bwd(b.convs[last], dout, w + u.out, w + u.conv[last].y, dy, dsum, apart(last), s)) return rc;
+        if (int rc = affine_bwd(b.convs[last], dout, w + u.out, nullptr, dy, dsum, apart(last), s, projection_shift(b))) return rc;
       for (int j = last; j >= 1; --j) {
         const void* in_j = w + u.conv[j - 1].a;
-        if (int rc = conv_wgrad(b.convs[j], in_j, dy, wpart(j), static_cast<float*>(grad_ptrs[b.convs[j].w]), fork(s))) return rc;
-        reader[dy_slot] = mark();
+        if (int rc = conv_wgrad(b.convs[j], in_j, j == last ? dsum : dy, wpart(j), j == last, fork(s))) return rc;
+        if (j != last) reader[dy_slot] = mark();
         const int next_slot = (dy_slot + 1) % 3;
         void* dy_next = dy_slots[next_slot];
         if (int rc = wait_mark(s, reader[next_slot])) return rc;   // whoever read that slot is done with it
@@ -515,20 +530,19 @@ class ResnetModel : public Model {
       }
       const void* shortcut_grad = dsum;
       void* dys = G(set, 3);
-      if (b.has_proj)
-        if (int rc = affine_bwd(b.proj, dsum, nullptr, w + u.proj.y, dys, nullptr, apart(kProjSlot), s)) return rc;
       {
         // the unit's last weight gradients and, behind them, all of its small reductions: the fork comes after every
         // affine pass of the unit, and nothing below reads what the reductions write
-        hipStream_t side = fork(s);
-        if (int rc = conv_wgrad(b.convs[0], x_in, dy, wpart(0), static_cast<float*>(grad_ptrs[b.convs[0].w]), side)) return rc;
+        hipStream_t to = fork(s);
+        if (int rc = conv_wgrad(b.convs[0], x_in, dy, wpart(0), false, to)) return rc;
         if (b.has_proj)
-          if (int rc = conv_wgrad(b.proj, x_in, dys, wpart(kProjSlot), static_cast<float*>(grad_ptrs[b.proj.w]), side)) return rc;
-        if (int rc = flush_reduces(side)) return rc;
+          if (int rc = conv_wgrad(b.proj, x_in, dsum, wpart(kProjSlot), true, to)) return rc;
+        if (int rc = flush_reduces(to)) return rc;
         unit_done[i] = mark();
       }
       if (b.has_proj) {
         if (need_dx) {
+          if (int rc = affine_bwd(b.proj, dsum, nullptr, nullptr, dys, nullptr, nullptr, s)) return rc;
           if (int rc = conv_dgrad(b.proj, dys, param_ptrs[b.proj.w], nullptr, w + p.g[3], s)) return rc;
           shortcut_grad = w + p.g[3];
         }
@@ -542,8 +556,9 @@ class ResnetModel : public Model {
         const int set_below = (i - 1) % Plan::kSets, last_below = (int)below.convs.size() - 1;
         if (i + 2 < (int)blocks_.size())
           if (int rc = wait_mark(s, unit_done[i + 2])) return rc;   // the unit that last used that set
-        const int fused = conv_dgrad_affine(b.convs[0], dy, param_ptrs[b.convs[0].w], below.convs[last_below], x_in, w + p.unit[i].conv[last_below].y,
-                                            G(set_below, 0), apart_of(set_below, last_below), p.spare_rows, s, shortcut_grad, G(set_below, 4));
+        const int fused = conv_dgrad_affine(b.convs[0], dy, param_ptrs[b.convs[0].w], below.convs[last_below], x_in, nullptr,
+                                            G(set_below, 0), apart_of(set_below, last_below), p.spare_rows, s, shortcut_grad, G(set_below, 4),
+                                            projection_shift(below));
         if (fused < 0) return fused;
         if (fused > 0) { set_error("resnet: the last input gradient of unit %d cannot carry the affine pass below it", i + 1); return SPB_ERR_INVALID_ARG; }
         incoming_fused = true;
@@ -568,7 +583,7 @@ class ResnetModel : public Model {
       set = 0;
       if (int rc = affine_bwd(stem_, d, w + su.conv[0].a, w + su.conv[0].y, G(0, 0), nullptr, apart(0), s)) return rc;
       const void* stem_in = stem_.cin_eff != stem_.cin ? (const void*)(w + su.xpad) : x_;
-      if (int rc = conv_wgrad(stem_, stem_in, G(0, 0), wpart(0), static_cast<float*>(grad_ptrs[stem_.w]), s)) return rc;
+      if (int rc = conv_wgrad(stem_, stem_in, G(0, 0), wpart(0), false, s)) return rc;
       if (int rc = flush_reduces(s)) return rc;
     }
     return SPB_OK;

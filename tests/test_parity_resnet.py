@@ -108,3 +108,29 @@ def test_resnet101_style_stack_at_table1_depths():
                     assert torch.isnan(g).all(), f"{info['name']} was written below the cut"
     finally:
         model.close()
+
+
+# The scale's gradient at a unit's output is formed from the weights and the weight gradient, not from the convolution's output: it must not
+# need the scale itself.  Rows of the reduction: 4 to 1152 groups of four (small channel counts; 512 channels, 3 x 3), with one slice and with many.
+@pytest.mark.parametrize("name", ["small_resnet_basic_bf16", "small_resnet_bottleneck_bf16", "odd_tiles_64x128_resnet_basic_bf16", "long_slice_resnet_basic_bf16"])
+def test_scales_of_zero_at_a_units_output(name):
+    cfg = wl.get_config(name)
+    params, batch = wl.make_params(cfg, 0, True), wl.make_batch(cfg, 0)
+    closing = "aff3.scale" if cfg["family"] == "resnet_bottleneck" else "aff2.scale"
+    zeroed = [n for n in params if n.endswith(closing) or n.endswith("projaff.scale")]
+    for i, n in enumerate(zeroed):
+        params[n][i % 2::3] = 0
+    n_units = wl.unit_count(cfg)
+    k = n_units - 1
+    _, exact = oracle.spb_step(cfg, params, batch, k)
+    _, ref = oracle.spb_step(cfg, params, batch, k, oracle.round_to_bf16)
+    model = spb.SpbModel(cfg, params)
+    try:
+        model.step({n: t.cuda() for n, t in batch.items()}, k)
+        torch.cuda.synchronize()
+        gpu = {n: g.double().cpu().numpy() for n, g in model.grad_dict(k).items()}
+        check_gradients(gpu, ref, "bf16", exact)
+        for i, n in enumerate(zeroed):
+            assert (ref[n][i % 2::3] != 0).any(), n     # the oracle's gradient of a zero scale is not zero
+    finally:
+        model.close()
