@@ -512,8 +512,10 @@ class ResnetModel : public Model {
         if (int rc = affine_bwd(b.convs[last], dout, w + u.out, nullptr, dy, dsum, apart(last), s, projection_shift(b))) return rc;
       for (int j = last; j >= 1; --j) {
         const void* in_j = w + u.conv[j - 1].a;
-        if (int rc = conv_wgrad(b.convs[j], in_j, j == last ? dsum : dy, wpart(j), j == last, fork(s))) return rc;
-        if (j != last) reader[dy_slot] = mark();
+        if (j == last || need_dx) {
+          if (int rc = conv_wgrad(b.convs[j], in_j, j == last ? dsum : dy, wpart(j), j == last, fork(s))) return rc;
+          if (j != last) reader[dy_slot] = mark();
+        }
         const int next_slot = (dy_slot + 1) % 3;
         void* dy_next = dy_slots[next_slot];
         if (int rc = wait_mark(s, reader[next_slot])) return rc;   // whoever read that slot is done with it
@@ -532,11 +534,17 @@ class ResnetModel : public Model {
       void* dys = G(set, 3);
       {
         // the unit's last weight gradients and, behind them, all of its small reductions: the fork comes after every
-        // affine pass of the unit, and nothing below reads what the reductions write
-        hipStream_t to = fork(s);
+        // affine pass of the unit, and nothing below reads what the reductions write.  In the lowest unit all but the last
+        // convolution's run on the chain, which has nothing else left to do, while the second stream catches up (224-pixel bottleneck CNN, 17 of 18
+        // units: it was 270 us behind).
+        hipStream_t to = need_dx ? fork(s) : s;
+        if (!need_dx)
+          for (int j = last - 1; j >= 1; --j)
+            if (int rc = conv_wgrad(b.convs[j], w + u.conv[j - 1].a, dy_slots[last - j], wpart(j), false, to)) return rc;
         if (int rc = conv_wgrad(b.convs[0], x_in, dy, wpart(0), false, to)) return rc;
         if (b.has_proj)
           if (int rc = conv_wgrad(b.proj, x_in, dsum, wpart(kProjSlot), true, to)) return rc;
+        if (!need_dx) to = fork(s);   // the reductions wait for both
         if (int rc = flush_reduces(to)) return rc;
         unit_done[i] = mark();
       }
