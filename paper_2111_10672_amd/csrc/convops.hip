@@ -390,12 +390,21 @@ __global__ __launch_bounds__(256) void avgpool_bwd_kernel(const uint16_t* __rest
   dx[idx] = to_bf16(bf(dpooled[b * c + ch]) / (float)hw);
 }
 
-// out[row, 0..c_out) = in[row, 0..c_in) followed by zeros
+// out[row, 0..c_out) = in[row, 0..c_in) followed by zeros; a thread writes 8 channels of a row with one store (a store of 2 bytes per
+// thread: 64 images of 224 x 224 x 3 53 us)
 __global__ __launch_bounds__(256) void pad_channels_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out, long long rows, int c_in, int c_out) {
+  const int chunks = c_out >> 3;
   const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= rows * c_out) return;
-  const int ch = idx % c_out;
-  out[idx] = ch < c_in ? in[(idx / c_out) * c_in + ch] : (uint16_t)0;
+  const long long row = idx / chunks;
+  if (row >= rows) return;
+  const int first = (int)(idx - row * chunks) * 8;
+  uint16_t v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = first + e < c_in ? in[row * c_in + first + e] : (uint16_t)0;
+  u32x4 o;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) o[d] = v[2 * d] | ((uint32_t)v[2 * d + 1] << 16);
+  *reinterpret_cast<u32x4*>(out + idx * 8) = o;
 }
 
 unsigned blocks_for(long long n) { return (unsigned)((n + 255) / 256); }
@@ -534,8 +543,8 @@ hipError_t launch_avgpool_bwd(const void* dpooled, void* dx, int n, int hw, int 
 }
 
 hipError_t launch_pad_channels(const void* in, void* out, long long rows, int c_in, int c_out, hipStream_t s) {
-  if (!in || !out || rows <= 0 || c_in <= 0 || c_out < c_in) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(pad_channels_kernel, dim3(blocks_for(rows * c_out)), dim3(256), 0, s, (const uint16_t*)in, (uint16_t*)out, rows, c_in, c_out);
+  if (!in || !out || rows <= 0 || c_in <= 0 || c_out < c_in || c_out % 8 || (reinterpret_cast<uintptr_t>(out) & 15)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(pad_channels_kernel, dim3(blocks_for(rows * (c_out / 8))), dim3(256), 0, s, (const uint16_t*)in, (uint16_t*)out, rows, c_in, c_out);
   return hipGetLastError();
 }
 
