@@ -942,6 +942,43 @@ __device__ __forceinline__ void store_wave_tile(const GemmParams& p, f32x16 (&ac
   }
 }
 
+// Bias gradient of a weight-gradient product: sum over k of A(row, k), by the workgroups of tile column 0: one more MFMA per A fragment, against a
+// fragment of ones.  The waves that share the rows of a fragment take its k-groups in turn, and their sums are added through LDS
+// after the tile loop.  (Adding up A's rows from LDS with vector instructions, as the kernels for taller wave tiles do for want of
+// registers, cost those workgroups 400 cycles of 1150 per tile, and the product waits for them: 768 x 3072 over 4096 46.0 -> 43.2 us, a
+// perceptron of 768-3072-2304-768-24 and 4096 rows 394 -> 387.)
+template <int TM>
+struct RowSumMfma {
+  f32x16 acc[TM];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+  }
+  __device__ __forceinline__ void add(int i, const u32x4& a) {
+    const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ones), __builtin_bit_cast(bf16x8, a), acc[i], 0, 0, 0);
+  }
+  // all 16 accumulators of lane l hold the sum of row l % 32; part: the dead tile ring, WAVES_N rows of BM floats
+  template <int BM, int WM, int WAVES_N>
+  __device__ __forceinline__ void finish(const GemmParams& p, float* part, int m0, int wm, int wn, int lane) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+      if (lane < 32) part[wn * BM + wm * WM + i * 32 + lane] = acc[i][0];
+    __syncthreads();
+    if ((int)threadIdx.x < BM && m0 + (int)threadIdx.x < p.M) {
+      float v = part[threadIdx.x];
+#pragma unroll
+      for (int w = 1; w < WAVES_N; ++w) v += part[w * BM + threadIdx.x];
+      p.a_row_sum[m0 + threadIdx.x] = v;
+    }
+    __syncthreads();
+  }
+};
+template <int TM, int TN>
+constexpr bool row_sum_by_mfma = TM <= 2 && TM * TN <= 6;   // 16 registers per row of fragments, beside 16 per fragment pair
+
 template <int BM, int BN, int STAGES, int WAVES_M, int WAVES_N, Layout LA, Layout LB, Gather GA, Gather GB>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(GemmParams p) {
   constexpr int NW = WAVES_M * WAVES_N;
@@ -996,9 +1033,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   // the partial sums of the kPhases threads of a chunk are added up once, after the tile loop.
   constexpr int kChunks = BM / 8, kPhases = 64 * NW / kChunks;
   static_assert(kPhases >= 1 && kTileK % kPhases == 0 && (size_t)kPhases * BM * 4 <= (size_t)STAGES * kStageBytes, "row-sum partition");
-  const bool want_row_sum = LA == Layout::KRow && p.a_row_sum != nullptr && tile_n == 0;
+  constexpr bool kRowSums = LA == Layout::KRow && GB == Gather::None;   // (convolutions have no bias)
+  const bool want_row_sum = kRowSums && p.a_row_sum != nullptr && tile_n == 0;
   float row_sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const int sum_chunk = threadIdx.x % kChunks, sum_phase = threadIdx.x / kChunks;
+  constexpr bool kSumByMfma = kRowSums && row_sum_by_mfma<TM, TN>;
+  RowSumMfma<kSumByMfma ? TM : 1> sums;
+  if constexpr (kSumByMfma) sums.clear();
 
   for (int t = t_first; t < n_steps; ++t) {
     // Tiles t+1 .. t+STAGES-2 may stay in flight if they were all issued; near the end wait for everything.
@@ -1026,6 +1067,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
           for (int j = 0; j < TN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b[g * TN + j]),   // operands exchanged:
                                                                 __builtin_bit_cast(bf16x8, a[g * TM + i]), acc[i][j], 0, 0, 0);  // see store_wave_tile
+      if constexpr (kSumByMfma) {
+        if (want_row_sum) {
+#pragma unroll
+          for (int g = 0; g < kBatch; ++g) {
+            if ((kb + g) % WAVES_N != wn) continue;   // uniform
+#pragma unroll
+            for (int i = 0; i < TM; ++i) sums.add(i, a[g * TM + i]);
+          }
+        }
+      }
       if constexpr (LA == Layout::RowK && LB == Layout::RowK) {
         // Keep the batch's LDS reads ahead of its MFMAs (the scheduler otherwise sinks each read to its use
         // and the wave eats one LDS latency per MFMA).
@@ -1033,7 +1084,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
         __builtin_amdgcn_sched_group_barrier(0x008, kBatch * TM * TN, 0);    // MFMA
       }
     }
-    if constexpr (LA == Layout::KRow) {
+    if constexpr (kRowSums && !kSumByMfma) {
       if (want_row_sum) {
 #pragma unroll
         for (int j = 0; j < kTileK / kPhases; ++j) {
@@ -1048,7 +1099,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
     }
   }
   wait_loads_and_barrier<0>();  // every wave is done with the tile ring
-  if constexpr (LA == Layout::KRow) {
+  if constexpr (kSumByMfma) {
+    if (want_row_sum) sums.template finish<BM, WM, WAVES_N>(p, reinterpret_cast<float*>(lds), m0, wm, wn, lane);   // uniform over the workgroup
+  } else if constexpr (kRowSums) {
     if (want_row_sum) {  // uniform over the workgroup
       float* part = reinterpret_cast<float*>(lds);
 #pragma unroll
@@ -1141,10 +1194,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_pipe_kernel(
   // block and added in its second
   constexpr int kChunks = BM / 8, kPhases = 64 * NW / kChunks, kSumReads = kTileK / kPhases;
   static_assert(kPhases >= 1 && kTileK % kPhases == 0 && (size_t)kPhases * BM * 4 <= (size_t)STAGES * kStageBytes, "row-sum partition");
-  const bool want_row_sum = LA == Layout::KRow && p.a_row_sum != nullptr && tile_n == 0;
+  constexpr bool kRowSums = LA == Layout::KRow && GB == Gather::None;   // (convolutions have no bias)
+  const bool want_row_sum = kRowSums && p.a_row_sum != nullptr && tile_n == 0;
   float row_sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const int sum_chunk = threadIdx.x % kChunks, sum_phase = threadIdx.x / kChunks;
   u32x4 sum_rows[kSumReads];
+  constexpr bool kSumByMfma = kRowSums && row_sum_by_mfma<TM, TN>;
+  RowSumMfma<kSumByMfma ? TM : 1> sums;
+  if constexpr (kSumByMfma) sums.clear();
 
   auto pin = [] { __builtin_amdgcn_sched_barrier(0); };   // the instruction scheduler moves nothing across this point
   auto lds_done = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
@@ -1203,7 +1260,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_pipe_kernel(
       // ---- the fragments of this block are in registers
       lds_done();
       keep(cur);
-      if constexpr (LA == Layout::KRow) {
+      if constexpr (kRowSums && !kSumByMfma) {
         if (blk == 1 && want_row_sum) {
 #pragma unroll
           for (int r = 0; r < kSumReads; ++r) {
@@ -1248,7 +1305,18 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_pipe_kernel(
         if constexpr (idx == 0 && load_part < PARTS) issue_part(load_tile, load_part);
         pin();
       });
-      if constexpr (LA == Layout::KRow) {
+      if constexpr (kSumByMfma) {
+        if (want_row_sum) {
+#pragma unroll
+          for (int g = 0; g < KGB; ++g) {
+            if ((blk * KGB + g) % WAVES_N != wn) continue;   // uniform
+#pragma unroll
+            for (int i = 0; i < TM; ++i) sums.add(i, fa[cur][g * TM + i]);
+          }
+          pin();
+        }
+      }
+      if constexpr (kRowSums && !kSumByMfma) {
         if (blk == 0 && want_row_sum) {
 #pragma unroll
           for (int r = 0; r < kSumReads; ++r) {
@@ -1264,7 +1332,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_pipe_kernel(
   lds_done();
   // Every wave is past the last tile's barrier, which it reached with the whole tile in registers: the ring is dead.
   __syncthreads();
-  if constexpr (LA == Layout::KRow) {
+  if constexpr (kSumByMfma) {
+    if (want_row_sum) sums.template finish<BM, WM, WAVES_N>(p, reinterpret_cast<float*>(lds), m0, wm, wn, lane);   // uniform over the workgroup
+  } else if constexpr (kRowSums) {
     if (want_row_sum) {  // uniform over the workgroup
       float* part = reinterpret_cast<float*>(lds);
 #pragma unroll
