@@ -164,11 +164,18 @@ __global__ __launch_bounds__(256) void softmax_xent_any_kernel(const float* __re
   if (threadIdx.x == 0) row_loss[row] = lse - ((unsigned)y < (unsigned)classes ? z[y] : 0.f);
 }
 
-// Adds the per-row losses in a fixed order (same result on every run) and stores the mean.
+// Adds the per-row losses in a fixed order (same result on every run) and stores the mean: thread t rows t, t + 256, ..., eight loads in flight at
+// a time (one at a time: 4096 rows 5.5 us, 3.2 so).
 __global__ __launch_bounds__(256) void mean_kernel(const float* __restrict__ row_loss, int rows, float* __restrict__ out) {
   __shared__ float red[4];
-  float s = 0.f;
-  for (int i = threadIdx.x; i < rows; i += 256) s += row_loss[i];
+  float s = (int)threadIdx.x < rows ? row_loss[threadIdx.x] : 0.f;
+  for (int base = threadIdx.x + 256; base < rows; base += 8 * 256) {
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = base + i * 256 < rows ? row_loss[base + i * 256] : 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s += v[i];
+  }
   s = wave_sum(s);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
