@@ -269,19 +269,22 @@ __global__ __launch_bounds__(kReduceThreads) void unit_reduce_kernel(ReduceTable
   else splitk_reduce_block(block, k.partial, k.count, k.stride, k.out, k.numel, k.cin, k.cin_padded);
 }
 
-// The same with a bfloat16 result (the input gradient of a product whose k range was cut into slices): eight
-// neighbouring elements per thread, slices added in index order, one rounding at the end.
+// The same with a bfloat16 result (the input gradient of a product whose k range was cut into slices, with the ReLU below it where there is one):
+// eight neighbouring elements per thread, slices added in index order, one rounding at the end.
 __global__ __launch_bounds__(256) void splitk_reduce_bf16_kernel(const f32x4* __restrict__ partial, int slices, long long slice_stride4,
-                                                                 uint4* __restrict__ out, long long numel8) {
+                                                                 const u32x4* __restrict__ mask, u32x4* __restrict__ out, long long numel8) {
   const long long j = (long long)blockIdx.x * 256 + threadIdx.x;
   if (j >= numel8) return;
-  f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
-#pragma unroll 4
-  for (int z = 0; z < slices; ++z) {
-    lo += partial[(size_t)z * slice_stride4 + 2 * j];
-    hi += partial[(size_t)z * slice_stride4 + 2 * j + 1];
+  const u32x4 m = mask ? mask[j] : u32x4{};
+  const f32x4 lo = sum_slices(partial + 2 * j, slice_stride4, 0, slices, 1), hi = sum_slices(partial + 2 * j + 1, slice_stride4, 0, slices, 1);
+  float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  if (mask) {
+    float a[8];
+    unpack8(m, a);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = a[e] > 0.f ? v[e] : 0.f;
   }
-  out[j] = make_uint4(bf16_pack2(lo[0], lo[1]), bf16_pack2(lo[2], lo[3]), bf16_pack2(hi[0], hi[1]), bf16_pack2(hi[2], hi[3]));
+  out[j] = pack8(v);
 }
 
 // 3x3 window, stride 2, padding 1 (acting as -inf); the first maximum in row-major window order wins.
@@ -502,12 +505,12 @@ hipError_t launch_unit_reduce(const ReduceTask* tasks, int n, hipStream_t s) {
   return hipSuccess;
 }
 
-hipError_t launch_splitk_reduce_bf16(const float* partial, int slices, long long slice_stride, void* out, long long numel, hipStream_t s) {
+hipError_t launch_splitk_reduce_bf16(const float* partial, int slices, long long slice_stride, const void* mask, void* out, long long numel, hipStream_t s) {
   if (!partial || !out || slices < 1 || numel <= 0 || numel % 8 || slice_stride % 4 || slice_stride < numel ||
-      (reinterpret_cast<uintptr_t>(partial) & 15) || (reinterpret_cast<uintptr_t>(out) & 15))
+      ((reinterpret_cast<uintptr_t>(partial) | reinterpret_cast<uintptr_t>(mask) | reinterpret_cast<uintptr_t>(out)) & 15))
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(splitk_reduce_bf16_kernel, dim3(blocks_for(numel / 8)), dim3(256), 0, s, reinterpret_cast<const f32x4*>(partial), slices,
-                     slice_stride / 4, reinterpret_cast<uint4*>(out), numel / 8);
+                     slice_stride / 4, static_cast<const u32x4*>(mask), static_cast<u32x4*>(out), numel / 8);
   return hipGetLastError();
 }
 

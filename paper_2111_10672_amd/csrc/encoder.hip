@@ -250,7 +250,7 @@ class EncoderModel : public Model {
         g.k_splits = slices; g.epilogue = Epilogue::StoreF32; g.C = w + p.logits; g.ldc = H;
         if (int rc = gemm(g, s)) return rc;
         if (int rc = run("splitk_reduce", (double)(slices * 4 + 2) * R * H, s, [&] {
-              return launch_splitk_reduce_bf16(reinterpret_cast<const float*>(w + p.logits), slices, (long long)R * H, w + p.dy, (long long)R * H, s); }))
+              return launch_splitk_reduce_bf16(reinterpret_cast<const float*>(w + p.logits), slices, (long long)R * H, nullptr, w + p.dy, (long long)R * H, s); }))
           return rc;
       } else if (int rc = gemm(g, s)) return rc;
     }

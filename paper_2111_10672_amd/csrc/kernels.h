@@ -140,8 +140,10 @@ hipError_t launch_conv3_wgrad(const GemmProblem& p, hipStream_t stream);
 // float32 products of small dense layers (latency-bound): see gemm_f32_small.hip
 bool gemm_f32_small_accepts(const GemmProblem& p);
 hipError_t launch_gemm_f32_small(const GemmProblem& p, hipStream_t stream);
+bool gemm_f32_pair_accepts(const GemmProblem& d, const GemmProblem& w);
+hipError_t launch_gemm_f32_pair(const GemmProblem& d, const GemmProblem& w, hipStream_t stream);
 // The input-gradient product d (RowK x KRow) and the weight-gradient product w (KRow x KRow) of one dense layer,
-// which do not depend on each other: one launch when both are small enough for the small-product kernel
+// which do not depend on each other: one launch when both are small enough for the small-product kernel of their type
 // (gemm_pair_shares_launch says whether), otherwise w and then d, one launch each.
 bool gemm_pair_shares_launch(const GemmProblem& d, const GemmProblem& w);
 hipError_t launch_gemm_pair(const GemmProblem& d, const GemmProblem& w, hipStream_t stream);
@@ -207,8 +209,9 @@ bool make_splitk_reduce_task(const float* partial, int slices, long long slice_s
                              ReduceTask* task);
 // All of the tasks in one launch (several if there are more than ReduceTable::kMax).
 hipError_t launch_unit_reduce(const ReduceTask* tasks, int n, hipStream_t s);
-// out[j] (bfloat16) = sum over slices of partial[slice * slice_stride + j], j < numel; numel a multiple of 8, 16-byte aligned.
-hipError_t launch_splitk_reduce_bf16(const float* partial, int slices, long long slice_stride, void* out, long long numel, hipStream_t s);
+// out[j] (bfloat16) = sum over slices of partial[slice * slice_stride + j], j < numel, or 0 where mask[j] (bfloat16, optional) is not positive; numel a
+// multiple of 8, all 16-byte aligned.
+hipError_t launch_splitk_reduce_bf16(const float* partial, int slices, long long slice_stride, const void* mask, void* out, long long numel, hipStream_t s);
 // 3x3 / stride 2 / padding 1 max-pool of x [n, h, w, c]; which (optional, [n, oh, ow, c]) records the winning window position.
 hipError_t launch_maxpool_fwd(const void* x, void* out, uint8_t* which, int n, int h, int w, int c, hipStream_t s);
 hipError_t launch_maxpool_bwd(const void* dout, const uint8_t* which, void* da, int n, int h, int w, int c, hipStream_t s);
