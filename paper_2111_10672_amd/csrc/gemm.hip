@@ -328,12 +328,13 @@ hipError_t launch_gemm(const GemmProblem& p, hipStream_t stream) {
 }
 
 bool gemm_pair_shares_launch(const GemmProblem& d, const GemmProblem& w) {
-  return d.dtype == DType::BF16 && w.dtype == DType::BF16 && operands_valid(d) && operands_valid(w) && gemm_dma_accepts(d) &&
-         gemm_dma_accepts(w) && gemm_dma_pair_accepts(d, w);
+  if (d.dtype != w.dtype || !operands_valid(d) || !operands_valid(w)) return false;
+  if (d.dtype == DType::F32) return gemm_f32_pair_accepts(d, w);
+  return gemm_dma_accepts(d) && gemm_dma_accepts(w) && gemm_dma_pair_accepts(d, w);
 }
 
 hipError_t launch_gemm_pair(const GemmProblem& d, const GemmProblem& w, hipStream_t stream) {
-  if (gemm_pair_shares_launch(d, w)) return launch_gemm_dma_pair(d, w, stream);
+  if (gemm_pair_shares_launch(d, w)) return d.dtype == DType::F32 ? launch_gemm_f32_pair(d, w, stream) : launch_gemm_dma_pair(d, w, stream);
   hipError_t e = launch_gemm(w, stream);
   if (e != hipSuccess) return e;
   return launch_gemm(d, stream);

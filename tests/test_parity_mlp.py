@@ -181,3 +181,58 @@ def test_step_replays_identically_from_a_hip_graph():
         for n, g in m.grad_dict(k).items():
             assert torch.equal(g, eager[n]), n
     m.close()
+
+
+# The head's input gradient cut into k-slices (many classes, rows of dlogits that are not whole cache lines; or few rows): with a remainder in the
+# last slice, more slices than fit the logits' place, and the unsliced neighbours.  One step against the same step in float64 on the same stored
+# bfloat16 operands would need the library's activations; the per-unit bound of the oracle holds, 2e-2.
+@pytest.mark.parametrize("batch,dims", [(200, [64, 504, 4999]), (64, [72, 200, 2051]), (64, [64, 1024, 2100]), (130, [64, 136, 4608]), (33, [64, 512, 5000])])
+def test_head_input_gradient_in_slices(batch, dims):
+    cfg = dict(family="mlp", dtype="bf16", batch=batch, dims=dims)
+    gen = torch.Generator().manual_seed(batch)
+    x = torch.randn(batch, dims[0], generator=gen).bfloat16()
+    labels = torch.randint(0, dims[-1], (batch,), generator=gen, dtype=torch.int32)
+    params = {}
+    for u, (i, o) in enumerate(zip(dims, dims[1:])):
+        params[f"fc{u}.weight"] = (torch.randn(o, i, generator=gen) * (2.0 / i) ** 0.5).bfloat16()
+        params[f"fc{u}.bias"] = (torch.randn(o, generator=gen) * 0.02).bfloat16()
+    model = spb.SpbModel(cfg, params)
+    try:
+        model.step({"x": x.cuda(), "labels": labels.cuda()}, 2)
+        torch.cuda.synchronize()
+        got = {n: g.double().cpu() for n, g in model.grad_dict(2).items()}
+    finally:
+        model.close()
+    q = lambda t: t.float().bfloat16().double()
+    w = {n: p.double() for n, p in params.items()}
+    z1 = x.double() @ w["fc0.weight"].T + w["fc0.bias"]
+    a1 = q(z1.clamp(min=0))
+    prob = torch.softmax(a1 @ w["fc1.weight"].T + w["fc1.bias"], 1)
+    prob[torch.arange(batch), labels.long()] -= 1.0
+    dlogits = q(prob / batch)
+    dz = q((dlogits @ w["fc1.weight"]) * (a1 > 0))
+    ref = {"fc1.weight": dlogits.T @ a1, "fc1.bias": dlogits.sum(0), "fc0.weight": dz.T @ x.double(), "fc0.bias": dz.sum(0)}
+    for n, r in ref.items():
+        assert (got[n] - r).norm() <= 2e-2 * r.norm(), (n, float((got[n] - r).norm() / r.norm()))
+
+
+# The two products of a float32 layer in one launch: odd tiles on either side, and one tile more than fits (512 workgroups, two launches).
+@pytest.mark.parametrize("batch,dims", [(1, [4, 4, 2]), (33, [36, 68, 100, 10]), (64, [256, 256, 256, 10]), (96, [512, 508, 33]), (128, [512, 512, 516]), (1000, [100, 204, 7])])
+def test_float32_layers_in_one_launch(batch, dims):
+    cfg = dict(family="mlp", dtype="f32", batch=batch, dims=dims)
+    gen = torch.Generator().manual_seed(batch)
+    x, labels = torch.randn(batch, dims[0], generator=gen), torch.randint(0, dims[-1], (batch,), generator=gen, dtype=torch.int32)
+    params = {}
+    for u, (i, o) in enumerate(zip(dims, dims[1:])):
+        params[f"fc{u}.weight"] = torch.randn(o, i, generator=gen) * (2.0 / i) ** 0.5
+        params[f"fc{u}.bias"] = torch.randn(o, generator=gen) * 0.02
+    L = len(dims) - 1
+    model = spb.SpbModel(cfg, params)
+    try:
+        model.step({"x": x.cuda(), "labels": labels.cuda()}, L)
+        torch.cuda.synchronize()
+        got = {n: g.double().cpu().numpy() for n, g in model.grad_dict(L).items()}
+    finally:
+        model.close()
+    _, ref = oracle.spb_step(cfg, params, {"x": x, "labels": labels}, L)
+    check_gradients(got, ref, "f32")
