@@ -82,10 +82,10 @@ __device__ __forceinline__ f32x4 read_fragment32(const char* tile, int g, int la
   }
 }
 
-// kRing: tiles per wave in flight
-template <int kRing, Layout LA, Layout LB>
+// kRing: tiles per wave in flight; NW: wavefronts, each with its part of k
+template <int kRing, int NW, Layout LA, Layout LB>
 __device__ __forceinline__ void f32_small_product(const GemmParams& p, int block, char* lds) {
-  static_assert(kRing == 2 || kRing == 4, "ring depth");
+  static_assert((kRing == 2 || kRing == 4) && NW % 4 == 0, "ring depth, wavefronts");
   const int tile = xcd_tile(block, p.tiles_m * p.tiles_n);
   const int tile_m = tile % p.tiles_m, tile_n = tile / p.tiles_m;
   const int m0 = tile_m * 32, n0 = tile_n * 32;
@@ -94,7 +94,7 @@ __device__ __forceinline__ void f32_small_product(const GemmParams& p, int block
   char* ring = lds + wave * (kRing * kStage);
 
   const int tiles = (p.K + kTile - 1) / kTile;
-  const int per_wave = (tiles + 3) / 4;
+  const int per_wave = (tiles + NW - 1) / NW;
   const int my_first = wave * per_wave;
   const int n = max(min(tiles, my_first + per_wave) - my_first, 0);  // tiles of this wave
 
@@ -156,19 +156,22 @@ __device__ __forceinline__ void f32_small_product(const GemmParams& p, int block
   }
   __syncthreads();
 
-  // wave w finishes rows 8 w .. 8 w + 7: lane -> (row, 4 columns)
+  // wave w < 4 finishes rows 8 w .. 8 w + 7: lane -> (row, 4 columns)
+  if (wave >= 4) return;
   const int row = 8 * wave + (lane >> 3), c = (lane & 7) * 4;
   const int m = m0 + row, nn = n0 + c;
   if (want_row_sum && lane < 8) {
     const float* at = red + (8 * wave + lane) * kPitch + 32;
-    const float v = ((at[0] + at[32 * kPitch]) + at[2 * 32 * kPitch]) + at[3 * 32 * kPitch];
+    float v = at[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += at[w * (32 * kPitch)];
     if (m0 + 8 * wave + lane < p.M) p.a_row_sum[m0 + 8 * wave + lane] = v;
   }
   if (m >= p.M || nn >= p.N) return;
   const float* at = red + row * kPitch + c;
   f32x4 v = *reinterpret_cast<const f32x4*>(at);
 #pragma unroll
-  for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const f32x4*>(at + w * (32 * kPitch));
+  for (int w = 1; w < NW; ++w) v += *reinterpret_cast<const f32x4*>(at + w * (32 * kPitch));
   const float* bias = static_cast<const float*>(p.bias);
   const float* mask = static_cast<const float*>(p.mask);
   float* out = static_cast<float*>(p.C) + (size_t)m * p.ldc + nn;
@@ -195,10 +198,10 @@ __device__ __forceinline__ void f32_small_product(const GemmParams& p, int block
   }
 }
 
-template <Layout LA, Layout LB>
-__global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmParams p) {
+template <int NW, Layout LA, Layout LB>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_small_kernel(GemmParams p) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  f32_small_product<4, LA, LB>(p, blockIdx.x, lds);
+  f32_small_product<16 / NW, NW, LA, LB>(p, blockIdx.x, lds);
 }
 
 // The input gradient and the weight gradient of a dense layer, which do not depend on each other, in one launch: the first product's tiles
@@ -208,18 +211,25 @@ template <Layout LA1, Layout LB1, Layout LA2, Layout LB2>
 __global__ __launch_bounds__(256) void gemm_f32_small_pair_kernel(GemmParams p1, GemmParams p2) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int n1 = p1.tiles_m * p1.tiles_n;
-  if ((int)blockIdx.x < n1) f32_small_product<2, LA1, LB1>(p1, blockIdx.x, lds);
-  else f32_small_product<2, LA2, LB2>(p2, blockIdx.x - n1, lds);
+  if ((int)blockIdx.x < n1) f32_small_product<2, 4, LA1, LB1>(p1, blockIdx.x, lds);
+  else f32_small_product<2, 4, LA2, LB2>(p2, blockIdx.x - n1, lds);
 }
 
+template <int NW, Layout LA, Layout LB>
+hipError_t launch_waves(const GemmProblem& q, hipStream_t stream) {
+  const GemmParams p = make_params(q, 32, 32);
+  constexpr size_t lds_bytes = (size_t)16 * kStage;  // 128 KiB; the parked partial tiles (18 or 36 KiB) overlay it
+  auto kernel = gemm_f32_small_kernel<NW, LA, LB>;
+  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kernel), (size_t)lds_bytes); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kernel, dim3(p.tiles_m * p.tiles_n), dim3(64 * NW), lds_bytes, stream, p);
+  return hipGetLastError();
+}
+// A wave multiplies its tiles one after the other, 16 dependent MFMAs of 64 cycles each: from three tiles a wave on eight waves of half the
+// part (with half the ring: the same bytes in flight).
 template <Layout LA, Layout LB>
 hipError_t launch(const GemmProblem& q, hipStream_t stream) {
-  const GemmParams p = make_params(q, 32, 32);
-  constexpr size_t lds_bytes = (size_t)4 * 4 * kStage;  // 128 KiB; the parked partial tiles (18 KiB) overlay it
-  auto kernel = gemm_f32_small_kernel<LA, LB>;
-  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kernel), (size_t)lds_bytes); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3(p.tiles_m * p.tiles_n), dim3(256), lds_bytes, stream, p);
-  return hipGetLastError();
+  if (q.K > 8 * kTile) return launch_waves<8, LA, LB>(q, stream);
+  return launch_waves<4, LA, LB>(q, stream);
 }
 
 }  // namespace
