@@ -216,9 +216,11 @@ def test_head_input_gradient_in_slices(batch, dims):
         assert (got[n] - r).norm() <= 2e-2 * r.norm(), (n, float((got[n] - r).norm() / r.norm()))
 
 
-# The two products of a float32 layer in one launch: odd tiles on either side, and one tile more than fits (512 workgroups, two launches).
-@pytest.mark.parametrize("batch,dims", [(1, [4, 4, 2]), (33, [36, 68, 100, 10]), (64, [256, 256, 256, 10]), (96, [512, 508, 33]), (128, [512, 512, 516]), (1000, [100, 204, 7])])
-def test_float32_layers_in_one_launch(batch, dims):
+# The two products of a float32 layer in one launch: odd tiles on either side, and one tile more than fits (512 workgroups, two launches).  Forward
+# products in 16 x 16 tiles: remainders of rows, columns and k, a wave without a tile, 256 tiles and one more row of them.
+@pytest.mark.parametrize("batch,dims", [(1, [4, 4, 2]), (33, [36, 68, 100, 10]), (64, [256, 256, 256, 10]), (96, [512, 508, 33]), (128, [512, 512, 516]),
+                                        (1000, [100, 204, 7]), (17, [788, 36, 10]), (3, [260, 20, 5]), (64, [1024, 1024, 12]), (65, [1024, 1024, 12])])
+def test_float32_layers_in_few_tiles(batch, dims):
     cfg = dict(family="mlp", dtype="f32", batch=batch, dims=dims)
     gen = torch.Generator().manual_seed(batch)
     x, labels = torch.randn(batch, dims[0], generator=gen), torch.randint(0, dims[-1], (batch,), generator=gen, dtype=torch.int32)
