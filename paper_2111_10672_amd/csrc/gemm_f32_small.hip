@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256) void gemm_f32_small_pair_kernel(GemmParams p1,
   else f32_small_product<2, 4, LA2, LB2>(p2, blockIdx.x - n1, lds);
 }
 
-// The same for forward products of few tiles and a longer k in 16 x 16 tiles: four times the workgroups, each pulling half the bytes through its
+// The same for forward products of few tiles in 16 x 16 tiles: four times the workgroups, each pulling half the bytes through its
 // CU (which is what a workgroup waits for: 64 x 256 over 784 10.3 us on 16 workgroups, 6.5 on 64).  v_mfma_f32_16x16x4_f32: the lanes of quarter
 // h take k = 4 h + e of a group of 16 in instruction e.
 constexpr int kTinyWaves = 8, kTinyRing = 4, kTinyStage = 32 * kRowBytes, kTinyPitch = 20;
@@ -348,7 +348,8 @@ hipError_t launch_gemm_f32_small(const GemmProblem& p, hipStream_t stream) {
   if (!gemm_f32_small_accepts(p)) return hipErrorInvalidValue;
   if (p.a_layout == Layout::RowK && p.b_layout == Layout::RowK) {
     const long tiny = (long)((p.M + 15) / 16) * ((p.N + 15) / 16);
-    if (p.K > 256 && tiny <= 256) return launch_tiny(p, stream);   // (one workgroup to a CU)
+    // one workgroup to a CU, and more of k than the eight waves would leave most of idle (64 features: level; 256: 0.91 to 0.93 of the step)
+    if (p.K > 96 && tiny <= 256) return launch_tiny(p, stream);
     return launch<Layout::RowK, Layout::RowK>(p, stream);
   }
   if (p.a_layout == Layout::RowK && p.b_layout == Layout::KRow) return launch<Layout::RowK, Layout::KRow>(p, stream);
