@@ -49,7 +49,7 @@ void Model::ensure_side_stream(hipStream_t s) {
   bool ok = true;
   // The events of forks and marks only order one stream of this device behind another (hipStreamWaitEvent): nobody asks them from the host, which
   // is what a system-scope fence would be for, and that fence writes the L2s back and empties them in the middle of the pass (32-pixel
-  // basic CNN 1160 -> 1110 us, ragged encoder 1370 -> 1341).  The join, behind which a caller may look at the gradients, keeps it.
+  // basic CNN 1156 -> 1126 us, encoder of 7 x 72 tokens 1369 -> 1343).  The join, behind which a caller may look at the gradients, keeps it.
   for (int i = 0; ok && i < 2 + kMarks; ++i) {
     const unsigned fence = i == 1 ? 0u : hipEventDisableSystemFence;
     ok = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming | fence) == hipSuccess;

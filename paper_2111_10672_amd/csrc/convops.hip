@@ -206,8 +206,8 @@ __device__ __forceinline__ void splitk_reduce4_wide_block(unsigned block, const 
 // Output channels of a convolution's weight gradient (see make_conv_weight_task): S[k] = sum over the slices, dW[k] = scale * S[k],
 // dscale = sum_k w[k] * S[k], k in groups of four.  k.threads threads (a power of two, 64 to 512) have a channel's whole row, so the dot product
 // needs no second pass.  Rows of fewer groups than that share the slices out among threads / row of them per group, whose sums are added
-// in order.  As few threads as leave each six loads or fewer (1024 rows of 64 groups in 12 slices, beside the input-gradient chain: 19 us with a
-// workgroup per row, 13 with a wavefront; 512 of 32 in 48: 27 and, with 12 loads each, 38).
+// in order.  As few threads as leave each six loads or fewer, which sum_slices has in flight together (alone, 1024 rows of 64 groups in 12 slices and the
+// unit's other sums: 11.4 us with a workgroup per row, 10.0 so).
 __device__ __forceinline__ void reduce_rows_block(unsigned block, const ReduceTask& k, f32x4* sh) {
   __shared__ float dots[kReduceThreads / 64];
   const int n = k.width, t = threadIdx.x & (k.threads - 1), first = threadIdx.x - t;   // place in the row's threads, and theirs in the workgroup
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(256) void avgpool_bwd_kernel(const uint16_t* __rest
 }
 
 // out[row, 0..c_out) = in[row, 0..c_in) followed by zeros; a thread writes 8 channels of a row with one store (a store of 2 bytes per
-// thread: 64 images of 224 x 224 x 3 53 us)
+// thread: 64 images of 224 x 224 x 3 53 us, 18 so)
 __global__ __launch_bounds__(256) void pad_channels_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out, long long rows, int c_in, int c_out) {
   const int chunks = c_out >> 3;
   const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;

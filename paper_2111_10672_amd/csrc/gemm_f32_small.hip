@@ -211,7 +211,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_small_kernel(GemmParams p) {
 
 // The input gradient and the weight gradient of a dense layer, which do not depend on each other, in one launch: the first product's tiles
 // take the lower block indices.  Half-size rings, so that a workgroup of each fits on a CU.  (Both are bound by latency, and a launch
-// costs 4 of them: 256 x 256 over 10, 64 rows, 8.4 us as two launches, 4.9 as one.)
+// costs 4 of them: 256 x 256 over 10, 64 rows, 8.4 us as two launches, 4.7 as one.)
 template <Layout LA1, Layout LB1, Layout LA2, Layout LB2>
 __global__ __launch_bounds__(256) void gemm_f32_small_pair_kernel(GemmParams p1, GemmParams p2) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(256) void gemm_f32_small_pair_kernel(GemmParams p1,
 }
 
 // The same for forward products of few tiles in 16 x 16 tiles: four times the workgroups, each pulling half the bytes through its
-// CU (which is what a workgroup waits for: 64 x 256 over 784 10.3 us on 16 workgroups, 6.5 on 64).  v_mfma_f32_16x16x4_f32: the lanes of quarter
+// CU (which is what a workgroup waits for: 64 x 256 over 784 10.3 us on 16 workgroups, 5.9 on 64).  v_mfma_f32_16x16x4_f32: the lanes of quarter
 // h take k = 4 h + e of a group of 16 in instruction e.
 constexpr int kTinyWaves = 8, kTinyRing = 4, kTinyStage = 32 * kRowBytes, kTinyPitch = 20;
 __global__ __launch_bounds__(64 * kTinyWaves) void gemm_f32_tiny_kernel(GemmParams p) {

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void softmax_xent_any_kernel(const float* __re
 }
 
 // Adds the per-row losses in a fixed order (same result on every run) and stores the mean: thread t rows t, t + 256, ..., eight loads in flight at
-// a time (one at a time: 4096 rows 5.5 us, 3.2 so).
+// a time (one at a time: 4096 rows 5.5 us, 4.6 so; 1000 rows level).
 __global__ __launch_bounds__(256) void mean_kernel(const float* __restrict__ row_loss, int rows, float* __restrict__ out) {
   __shared__ float red[4];
   float s = (int)threadIdx.x < rows ? row_loss[threadIdx.x] : 0.f;

@@ -163,7 +163,7 @@ class MlpModel : public Model {
 
   // Into how many slices the k range of the head's input gradient, as long as there are classes, is cut: as many as give each CU a 128 x 128 tile,
   // with eight tiles of k or more each.  Their float32 partial products go where the logits were (read for the last time by the loss),
-  // so they must fit there.  (1000 x 504 over 4999 classes: 24 us in 32 x 64 tiles, 19 with its reduction in 8 slices.)  Whole steps of 400
+  // so they must fit there.  (1000 x 504 over 4999 classes: 24 us in 32 x 64 tiles, 19.5 with its reduction in 8 slices.)  Whole steps of 400
   // perceptrons: 0.86 to 1.02 of the time (mean 0.94) from 4608 classes on where the rows of dlogits are not whole 128-byte lines, 0.86 to 1.00 for
   // up to 64 rows; else 0.95 to 1.06, and no slices.
   int head_slices(const GemmProblem& d) const {
