@@ -147,11 +147,11 @@ __device__ __forceinline__ V sum_slices(const V* __restrict__ p, size_t stride, 
   return s;
 }
 
-// Column sums of partial [count][columns].  A workgroup takes 16 neighbouring columns: thread (g, c) adds rows g, g + 32, ... of
+// Column sums of partial [count][columns].  A workgroup takes 16 neighbouring columns: thread (g, c) adds rows g, g + kGroups, ... of
 // column c in order - the 16 threads of a group read 64 contiguous bytes, where one wavefront per column touched a cache line
-// per lane - and the 32 group sums of a column are added in group order: the same bits on every run.
+// per lane - and the group sums of a column are added in group order: the same bits on every run.
+template <int kGroups>
 __device__ __forceinline__ void reduce_columns_block(unsigned block, const ReduceTask& k) {
-  constexpr int kGroups = kReduceThreads / 16;
   __shared__ float sh[kGroups][17];
   const bool pairs = k.kind == ReduceTask::kPairs;
   const int columns = pairs ? 2 * k.width : k.width;
@@ -254,19 +254,32 @@ __device__ __forceinline__ void reduce_rows_block(unsigned block, const ReduceTa
 // Several of the reductions above in one launch: the column sums of a unit's affine backward passes and the k-slice
 // sums of its weight gradients are a handful of tiny kernels each bound by its launch; a table in the kernel
 // arguments says which range of workgroups does which.
+__device__ __forceinline__ int task_of(const ReduceTable& t, unsigned& block) {
+  int i = 0;
+  while (i + 1 < t.n && block >= t.end_block[i]) ++i;
+  if (i) block -= t.end_block[i - 1];
+  return i;
+}
 __global__ __launch_bounds__(kReduceThreads) void unit_reduce_kernel(ReduceTable t) {
   __shared__ f32x4 sh[kReduceThreads];
-  int i = 0;
-  while (i + 1 < t.n && blockIdx.x >= t.end_block[i]) ++i;
-  const unsigned block = blockIdx.x - (i ? t.end_block[i - 1] : 0u);
-  const ReduceTask& k = t.task[i];
-  if (k.kind == ReduceTask::kPairs || k.kind == ReduceTask::kColumns) reduce_columns_block(block, k);
+  unsigned block = blockIdx.x;
+  const ReduceTask& k = t.task[task_of(t, block)];
+  if (k.kind == ReduceTask::kPairs || k.kind == ReduceTask::kColumns) reduce_columns_block<kReduceThreads / 16>(block, k);
   else if (k.kind == ReduceTask::kRows4) reduce_rows_block(block, k, sh);
   else if (k.kind == ReduceTask::kSlices4Wide)
     splitk_reduce4_wide_block(block, reinterpret_cast<const f32x4*>(k.partial), k.count, k.stride, reinterpret_cast<f32x4*>(k.out), k.numel, sh);
   else if (k.kind == ReduceTask::kSlices4)
     splitk_reduce4_block(block, reinterpret_cast<const f32x4*>(k.partial), k.count, k.stride, reinterpret_cast<f32x4*>(k.out), k.numel);
   else splitk_reduce_block(block, k.partial, k.count, k.stride, k.out, k.numel, k.cin, k.cin_padded);
+}
+// A table of column sums only, at a pass's end with nothing beside it (the layer norms' of an encoder): bound by the start of its 2400
+// workgroups where there are few rows to add and by HBM where there are many, so workgroups of half as many threads and no more LDS than these
+// sums need (24 pairs of 768 columns: over 32 rows 8.0 us in the kernel above, 4.1 so; over 256 rows 20.1 and 15.0).
+constexpr int kColumnThreads = 256;
+__global__ __launch_bounds__(kColumnThreads) void column_sums_kernel(ReduceTable t) {
+  unsigned block = blockIdx.x;
+  const int i = task_of(t, block);
+  reduce_columns_block<kColumnThreads / 16>(block, t.task[i]);
 }
 
 // The same with a bfloat16 result (the input gradient of a product whose k range was cut into slices, with the ReLU below it where there is one):
@@ -493,13 +506,16 @@ hipError_t launch_unit_reduce(const ReduceTask* tasks, int n, hipStream_t s) {
     ReduceTable t;
     t.n = std::min(n - first, (int)ReduceTable::kMax);
     unsigned end = 0;
+    bool columns_only = true;
     for (int i = 0; i < t.n; ++i) {
       t.task[i] = tasks[first + i];
       if (t.task[i].blocks == 0) return hipErrorInvalidValue;
+      columns_only = columns_only && (t.task[i].kind == ReduceTask::kPairs || t.task[i].kind == ReduceTask::kColumns);
       end += t.task[i].blocks;
       t.end_block[i] = end;
     }
-    hipLaunchKernelGGL(unit_reduce_kernel, dim3(end), dim3(kReduceThreads), 0, s, t);
+    if (columns_only) hipLaunchKernelGGL(column_sums_kernel, dim3(end), dim3(kColumnThreads), 0, s, t);
+    else hipLaunchKernelGGL(unit_reduce_kernel, dim3(end), dim3(kReduceThreads), 0, s, t);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -97,6 +97,17 @@ def test_an_earlier_error_costs_no_overlap(run, spoil, mend):
     """)
 
 
+def test_a_pass_that_ends_in_column_sums_only_has_a_kernel_for_them(run):
+    """An encoder's layer norm gradients are one launch at the pass's end, on the caller's stream, of workgroups as small as column
+    sums need (those of the CNNs' mixed reductions took 3 to 5 us longer)."""
+    run("""
+    m, s = Model(ENCODER), stream(1)
+    lines, _ = m.step(s)
+    sums = [l for l in lines if "column_sums_kernel" in l]
+    assert sums and all(l.endswith(f" {hip.fake_id(s)}") for l in sums) and not any("unit_reduce_kernel" in l for l in lines), lines
+    """)
+
+
 def test_callers_streams_share_no_side_stream(run):
     """Workers on streams of their own: neither's weight gradients wait for the other's.  Models on one stream, whose steps
     follow one another anyway, use the same side stream, and nothing stays behind."""
