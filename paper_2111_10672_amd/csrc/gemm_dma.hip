@@ -58,6 +58,7 @@ bool gemm_dma_accepts(const GemmProblem& p) {
     if (p.b_gather == Gather::ConvWeightT && (c.w_cin % 8 || c.w_cout % 8)) return false;
   }
   if (p.batch < 1 || p.batch > 65535 || (p.batch > 1 && p.a_row_sum)) return false;
+  if (p.a_row_sum && (p.a_layout != Layout::KRow || p.b_gather != Gather::None)) return false;   // (the tile loops of the others don't form them)
   // batch offsets must keep every operand 16-byte aligned
   for (const BatchStride* b : {&p.a_batch, &p.b_batch, &p.c_batch})
     if (b->inner_count < 1 || b->outer % 8 || b->inner % 8) return false;

@@ -349,7 +349,8 @@ hipError_t launch_gemm_f32_small(const GemmProblem& p, hipStream_t stream) {
   if (p.a_layout == Layout::RowK && p.b_layout == Layout::RowK) {
     const long tiny = (long)((p.M + 15) / 16) * ((p.N + 15) / 16);
     // one workgroup to a CU, and more of k than the eight waves would leave most of idle (64 features: level; 256: 0.91 to 0.93 of the step)
-    if (p.K > 96 && tiny <= 256) return launch_tiny(p, stream);
+    // (which adds up no rows of A)
+    if (p.K > 96 && tiny <= 256 && !p.a_row_sum) return launch_tiny(p, stream);
     return launch<Layout::RowK, Layout::RowK>(p, stream);
   }
   if (p.a_layout == Layout::RowK && p.b_layout == Layout::KRow) return launch<Layout::RowK, Layout::KRow>(p, stream);
