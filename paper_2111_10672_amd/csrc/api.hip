@@ -297,7 +297,7 @@ int spb_forward(spb_model* m, const void* x, const int32_t* labels, const int32_
   SPB_REQUIRE((reinterpret_cast<uintptr_t>(x) & 15u) == 0, SPB_ERR_INVALID_ARG, "spb_forward: input is not 16-byte aligned");
   if (int rc = depth_ok(m, k, "spb_forward")) return rc;
   SPB_REQUIRE(m->impl->params_bound, SPB_ERR_STATE, "spb_forward: parameters are not bound");
-  const size_t need = m->impl->workspace_size(k);
+  const size_t need = m->impl->workspace_need(k);
   SPB_REQUIRE(workspace && workspace_bytes >= need, SPB_ERR_WORKSPACE, "spb_forward: workspace of %zu bytes, depth %d needs %zu", workspace_bytes, k, need);
   SPB_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & 255u) == 0, SPB_ERR_WORKSPACE, "spb_forward: workspace is not 256-byte aligned");
   if (m->impl->forks) m->impl->ensure_side_stream(static_cast<hipStream_t>(stream));

@@ -84,7 +84,8 @@ class CallersSides {
 class Model {
  public:
   virtual ~Model();
-  virtual size_t workspace_size(int k) const = 0;
+  virtual size_t workspace_size(int k) const = 0;                                  // what callers are asked for: does not fall with k
+  virtual size_t workspace_need(int k) const { return workspace_size(k); }         // what a forward pass of depth k touches, at most that
   virtual int forward(const void* x, const int32_t* labels, const int32_t* loss_rows, int k, void* ws, float* loss_out, hipStream_t s) = 0;
   virtual int backward(int k, hipStream_t s) = 0;
   // Where a forward pass that stashed for depth k keeps the input of unit `unit` (>= L - k), and where the gradient

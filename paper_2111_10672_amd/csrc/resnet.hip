@@ -131,6 +131,7 @@ class ResnetModel : public Model {
     static constexpr int kReduceSlots = 4, kProjSlot = kReduceSlots - 1;   // a unit has at most three convolutions and a projection, which has the last place
     size_t affine_partial[kSets][kReduceSlots], wgrad_partial[kSets][kReduceSlots];   // per set of units
     int spare_rows;   // of column sums, beside one per 64 rows: for input gradients by pixel parity
+    bool first;       // of the plans there are: see plan(k)
     size_t total;
   };
   static constexpr int kFwdPool = 8, kSpareRows = 3;
@@ -160,8 +161,9 @@ class ResnetModel : public Model {
   // Partial sums lie in one buffer per set and convolution of a unit.  Small models have them all of one size; beyond the library's workspace
   // each is as large as the convolutions in its place need (the 32-pixel basic CNN of 18 layers, batch 128: 994 -> 889 MB; the
   // 224-pixel bottleneck CNN of 50, batch 64: 5821 -> 5763).
+  static constexpr size_t kStatic = SPB_STATIC_WORKSPACE_BYTES;
   Plan plan(int k) const {
-    constexpr size_t kStatic = SPB_STATIC_WORKSPACE_BYTES, kMost = (size_t)Plan::kSets * Plan::kReduceSlots * (kSpareRows * 2 * 2048 * 4);
+    constexpr size_t kMost = (size_t)Plan::kSets * Plan::kReduceSlots * (kSpareRows * 2 * 2048 * 4);
     const Plan p = plan(k, kSpareRows, false);
     if (p.total <= kStatic) return p;
     if (p.total <= kStatic + kMost) {
@@ -173,6 +175,7 @@ class ResnetModel : public Model {
   Plan plan(int k, int spare_rows, bool by_place) const {
     Plan p;
     p.spare_rows = spare_rows;
+    p.first = spare_rows && !by_place;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes, 256); return o; };
     const int cut = num_units - k;
@@ -249,7 +252,13 @@ class ResnetModel : public Model {
     return p;
   }
 
-  size_t workspace_size(int k) const override { return plan(k).total; }
+  size_t workspace_need(int k) const override { return plan(k).total; }
+  // Each plan grows with the depth, but a depth that is past the first plan may need less than a shallower one that is not.  The latter fits the
+  // library's own workspace, so asking for as much as that holds keeps the size from falling.
+  size_t workspace_size(int k) const override {
+    const Plan p = plan(k);
+    return p.first ? p.total : std::max(p.total, kStatic);
+  }
 
   // ---- products ----------------------------------------------------------------------------------
   ConvGeom geom(const Conv& c) const {

@@ -183,6 +183,22 @@ def test_partial_sums_are_sized_by_their_place(cfg, k, most):
         spb.spb_model_destroy(m)
 
 
+# Small CNNs change from one plan of the workspace to another as the depth grows; a workspace for the deepest worker does for all.
+@pytest.mark.parametrize("family,batch,image,stem,blocks,widths", [
+    ("resnet_bottleneck", 4, 9, 16, [1, 1, 1, 1], [64, 128, 256, 512]), ("resnet_basic", 3, 31, 32, [1, 1, 1], [16, 32, 64]),
+    ("resnet_bottleneck", 12, 16, 32, [1, 1, 2, 3], [32, 64, 128, 256]), ("resnet_bottleneck", 2, 6, 32, [1, 2], [256, 512]),
+    ("resnet_bottleneck", 4, 29, 16, [2, 1, 2, 1], [32, 64, 128, 256])])
+def test_a_deeper_pass_of_a_small_cnn_needs_no_less_workspace(family, batch, image, stem, blocks, widths):
+    cfg = dict(family=family, dtype="bf16", batch=batch, image=[image, image, 3], stem=dict(kernel=3, stride=1, pad=1, pool=False, width=stem),
+               stage_blocks=blocks, stage_widths=widths, classes=10)
+    m = spb.spb_model_create(spb.desc_from_config(cfg))
+    try:
+        sizes = [spb.spb_workspace_size(m, k) for k in range(spb.spb_num_units(m) + 1)]
+        assert sizes == sorted(sizes), sizes
+    finally:
+        spb.spb_model_destroy(m)
+
+
 # Column sums of input gradients by pixel parity take three rows more: a model that fits the library's own workspace only without them does so.
 def test_a_model_at_the_library_workspaces_limit_fits():
     m = spb.spb_model_create(spb.desc_from_config(_plain_cnn(5, 8, 3, [1, 1], [64, 128])))
