@@ -125,7 +125,7 @@ class ResnetModel : public Model {
     // backward transients, gradients of activations: 0, 1 the gradient handed from unit to unit where it is stored
     // unmasked (the top unit's, the stem's), 2 a convolution's input gradient on its way to an unfused affine pass,
     // 3 the projection's input gradient; then three sets (units i % 3) of: dy (three in rotation), the projection's
-    // dy, and the unit's masked output gradient (what its shortcut carries)
+    // dy (the chain's alone: one buffer serves all sets of a large model), and the unit's masked output gradient (what its shortcut carries)
     static constexpr int kSets = 3, kSetBase = 4, kPerSet = 5;
     size_t g[kSetBase + kSets * kPerSet];
     static constexpr int kReduceSlots = 4, kProjSlot = kReduceSlots - 1;   // a unit has at most three convolutions and a projection, which has the last place
@@ -159,8 +159,8 @@ class ResnetModel : public Model {
   // A model that fits the library's own workspace only without the spare rows does without them (its stride-2 input gradients are then
   // the gathering product's).  They are at most 48 KB of each of the buffers: 2048 channels.
   // Partial sums lie in one buffer per set and convolution of a unit.  Small models have them all of one size; beyond the library's workspace
-  // each is as large as the convolutions in its place need (the 32-pixel basic CNN of 18 layers, batch 128: 994 -> 889 MB; the
-  // 224-pixel bottleneck CNN of 50, batch 64: 5821 -> 5763).
+  // each is as large as the convolutions in its place need, and a projection, whose column sums are its unit's last convolution's, has
+  // none for those (the 224-pixel bottleneck CNN of 50 layers, batch 64: 4639 MB, and 225 more with these and a projection's dy in every set).
   static constexpr size_t kStatic = SPB_STATIC_WORKSPACE_BYTES;
   Plan plan(int k) const {
     constexpr size_t kMost = (size_t)Plan::kSets * Plan::kReduceSlots * (kSpareRows * 2 * 2048 * 4);
@@ -231,12 +231,15 @@ class ResnetModel : public Model {
     for (int h = 0; h < Plan::kSets; ++h)
       for (int j = 0; j < Plan::kReduceSlots; ++j) p.affine_partial[h][j] = p.wgrad_partial[h][j] = 0;
     if (k >= 2) {
-      for (auto& g : p.g) g = take(amax);
+      for (int i = 0; i < Plan::kSetBase + Plan::kSets * Plan::kPerSet; ++i)
+        p.g[i] = by_place && i >= Plan::kSetBase + Plan::kPerSet && (i - Plan::kSetBase) % Plan::kPerSet == 3 ? p.g[i - Plan::kPerSet] : take(amax);
       size_t ap[Plan::kReduceSlots] = {}, wp[Plan::kReduceSlots] = {};
       auto see = [&](const Conv& c, int place) {
         size_t &a = ap[by_place ? place : 0], &w = wp[by_place ? place : 0];
-        a = std::max(a, affine_partial_floats(c.out_rows(batch_), c.cout) * 4);
-        a = std::max(a, (size_t)((c.out_rows(batch_) + 63) / 64 + spare_rows) * 2 * c.cout * 4);   // the fused form: one row of sums per tile row
+        if (!by_place || place != Plan::kProjSlot) {
+          a = std::max(a, affine_partial_floats(c.out_rows(batch_), c.cout) * 4);
+          a = std::max(a, (size_t)((c.out_rows(batch_) + 63) / 64 + spare_rows) * 2 * c.cout * 4);   // the fused form: one row of sums per tile row
+        }
         w = std::max(w, (size_t)wgrad_splits(c) * c.cout * c.k_total() * 4);
       };
       see(stem_, 0);
@@ -497,7 +500,7 @@ class ResnetModel : public Model {
       const bool need_dx = i + 1 > cut;
       const void* x_in = w + p.unit[i].out;
       // Weight gradients and the unit's small reductions run on the second stream, beside the chain of input gradients.
-      // What they read and this chain writes (the dy buffers, the projection's dy, the partial sums, the masked output
+      // What they read and this chain writes (the dy buffers, the partial sums, the masked output
       // gradient) exists three times, unit i uses set i % 3 and the unit above already writes into the set of the
       // unit below (see the end of this loop), so the chain only has to know that the second stream is done with the
       // units three (here) and two (there) above - which it is long since; a join here would stall the chain behind

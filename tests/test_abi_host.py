@@ -183,6 +183,18 @@ def test_partial_sums_are_sized_by_their_place(cfg, k, most):
         spb.spb_model_destroy(m)
 
 
+# A projection has no column sums of its own, and its dy, which only the chain of input gradients reads and writes, exists once (with
+# both in each of the three sets: 4864 MB).
+def test_a_projection_keeps_what_the_second_stream_reads():
+    cfg = dict(family="resnet_bottleneck", dtype="bf16", batch=64, image=[224, 224, 3], stem=dict(kernel=7, stride=2, pad=3, pool=True, width=64),
+               stage_blocks=[3, 4, 6, 3], stage_widths=[256, 512, 1024, 2048], classes=1000)
+    m = spb.spb_model_create(spb.desc_from_config(cfg))
+    try:
+        assert spb.spb_workspace_size(m, 18) <= 4_640_000_000
+    finally:
+        spb.spb_model_destroy(m)
+
+
 # Small CNNs change from one plan of the workspace to another as the depth grows; a workspace for the deepest worker does for all.
 @pytest.mark.parametrize("family,batch,image,stem,blocks,widths", [
     ("resnet_bottleneck", 4, 9, 16, [1, 1, 1, 1], [64, 128, 256, 512]), ("resnet_basic", 3, 31, 32, [1, 1, 1], [16, 32, 64]),
