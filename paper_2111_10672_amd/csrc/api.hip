@@ -47,9 +47,12 @@ void Model::ensure_side_stream(hipStream_t s) {
   if (!side_ || fork_ev_) return;
   hipEvent_t ev[2 + kMarks] = {};
   bool ok = true;
-  // The events of forks and marks only order one stream of this device behind another (hipStreamWaitEvent): nobody asks them from the host, which
-  // is what a system-scope fence would be for, and that fence writes the L2s back and empties them in the middle of the pass (32-pixel
-  // basic CNN 1156 -> 1126 us, encoder of 7 x 72 tokens 1369 -> 1343).  The join, behind which a caller may look at the gradients, keeps it.
+  // The events of forks and marks only order one stream of this device behind another (hipStreamWaitEvent).  What lets a kernel of the one
+  // see what a kernel of the other wrote is what does so within a stream: a kernel releases its writes to the device when it ends and
+  // acquires the device's when it starts, and the wait makes sure that the one has ended before the other starts.  The system-scope fence that an
+  // event has besides is for the host and other devices, which nobody asks these events from; it writes the L2s back and empties them in the middle
+  // of the pass (32-pixel basic CNN 1156 -> 1126 us, encoder of 7 x 72 tokens 1369 -> 1343).  The join, behind which a caller may look at the
+  // gradients, keeps it.
   for (int i = 0; ok && i < 2 + kMarks; ++i) {
     const unsigned fence = i == 1 ? 0u : hipEventDisableSystemFence;
     ok = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming | fence) == hipSuccess;

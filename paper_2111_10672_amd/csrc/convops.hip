@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void affine_relu_bwd_kernel(const uint16_t* __
   const long long first = (long long)blockIdx.x * rows_per_block;
   const long long last = min(rows, first + rows_per_block);
   if (active) {
-    // two rows per trip, all their loads requested before the first is used
+    // four rows per trip, all their loads requested before the first is used
     auto finish = [&](size_t off, const u32x4& dw, const u32x4& yw, const u32x4& aw) {
       float d[8], o[8];
       unpack8(dw, d);

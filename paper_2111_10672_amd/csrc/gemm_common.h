@@ -72,8 +72,9 @@ __device__ __forceinline__ long long batch_offset(const BatchStride& b, int z) {
 // epilogues evaluate it once per output element, which is what bounds them, so the library erf (several times
 // the instructions, two divergent ranges) is not used.
 // erf_parts(u): t-polynomial and exp(-u^2) of the formula, for u >= 0.
-// The reciprocal is the hardware's, corrected once: the correctly rounded one for every float32 of [1, 2^63) (checked on the device), in three
-// instructions where the division takes eleven of the formula's thirty.  Beyond 1e18, where the exponential is zero, any t will do.
+// The reciprocal is the hardware's, good to a unit in the last place, corrected by one Newton step, which squares that error: what is left is the
+// step's own rounding, half a unit, far below the formula's.  Three instructions where the division takes eleven of the formula's thirty.
+// Beyond 1e18, where the exponential is zero, any t will do.
 __device__ __forceinline__ void erf_parts(float au, float& pt, float& e) {
   const float x = fmaf(0.3275911f, fminf(au, 1e18f), 1.f);
   float t = __builtin_amdgcn_rcpf(x);

@@ -1,9 +1,9 @@
 // float32 products of small dense layers (the perceptron configurations), C[m, n] = sum_k A(m, k) * B(n, k).
 //
 // Same scheme as the bfloat16 small-product kernel: such a product is a chain of latencies, so a workgroup owns
-// one 32 x 32 tile, its four waves split the k range into four contiguous parts, each wave streams its part
+// one 32 x 32 tile, its four or eight waves split the k range into as many contiguous parts, each wave streams its part
 // through a tile ring of its own in LDS with direct-to-LDS loads and waits only on its own loads (no barrier in
-// the tile loop), and the four partial tiles are added up through LDS at the end, each wave finishing 8 rows.
+// the tile loop), and the partial tiles are added up through LDS at the end, four of the waves finishing 8 rows each.
 // A tile is 32 values of k (128 bytes per row).  The matrix-core instruction is v_mfma_f32_32x32x2_f32: a lane
 // supplies one value of A (row lane % 32) and one of B per instruction, and WHICH two values of k an instruction
 // multiplies is free as long as both operands agree, so the lanes of half h take k = 4 h + e in instruction e and
@@ -357,7 +357,9 @@ hipError_t launch_gemm_f32_small(const GemmProblem& p, hipStream_t stream) {
   return launch<Layout::KRow, Layout::KRow>(p, stream);
 }
 
-// While all workgroups of both fit on the chip at once, two to a CU.
+// While all workgroups of both fit on the chip at once, two to a CU.  k does not matter: against two launches of the eight-wave kernel, steps of
+// two-layer perceptrons whose head is a pair take 0.81 to 1.01 of the time (308 shapes: batches of 32 to 4000, 32 to 512 features, 10 to 5000
+// classes; mean 0.90, for 5000 classes 0.95).
 bool gemm_f32_pair_accepts(const GemmProblem& d, const GemmProblem& w) {
   auto tiles = [](const GemmProblem& q) { return (long)((q.M + 31) / 32) * ((q.N + 31) / 32); };
   return gemm_f32_small_accepts(d) && gemm_f32_small_accepts(w) && d.a_layout == Layout::RowK && d.b_layout == Layout::KRow &&

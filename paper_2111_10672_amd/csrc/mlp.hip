@@ -163,9 +163,12 @@ class MlpModel : public Model {
 
   // Into how many slices the k range of the head's input gradient, as long as there are classes, is cut: as many as give each CU a 128 x 128 tile,
   // with eight tiles of k or more each.  Their float32 partial products go where the logits were (read for the last time by the loss),
-  // so they must fit there.  (1000 x 504 over 4999 classes: 24 us in 32 x 64 tiles, 19.5 with its reduction in 8 slices.)  Whole steps of 400
-  // perceptrons: 0.86 to 1.02 of the time (mean 0.94) from 4608 classes on where the rows of dlogits are not whole 128-byte lines, 0.86 to 1.00 for
-  // up to 64 rows; else 0.95 to 1.06, and no slices.
+  // so they must fit there.  (1000 x 504 over 4999 classes: 24 us in 32 x 64 tiles, 19.5 with its reduction in 8 slices.)
+  // What the slices save grows with the classes; the partial products' way through memory and one more launch do not.  Whole steps of two-layer perceptrons
+  // with slices against without, 80 to 4096 rows, 64 to 2048 features: level in the mean up to 3300 classes (0.94 to 1.08), 0.97 at 4300
+  // (0.87 to 1.03), 0.96 at 4551 (0.85 to 1.02), 0.94 at 4999, 0.92 at 7001, 0.87 at 10003, 0.75 at 30007, and from 4608 on none above 1.01.  So the line
+  // lies there - but not for whole tiles of k, which the unsliced product runs without a remainder and from rows of whole 128-byte lines: at 4608 to
+  // 5120 such classes 0.98 in the mean, single steps up to 1.03.  Up to 64 rows, from four slices on (2048 classes): 0.86 to 1.00.
   int head_slices(const GemmProblem& d) const {
     if (dtype != DType::BF16 || d.ldc != d.N || d.ldmask != d.N || (d.M > 64 && (d.K < 4608 || d.K % 64 == 0))) return 0;
     const long tiles = (long)((d.M + 127) / 128) * ((d.N + 127) / 128);

@@ -15,7 +15,7 @@
 //   at a unit's output       dz is in memory anyway, for the shortcut, so the weight gradients of the last convolution and of the projection
 //                            are formed from it: S = sum over pixels of dz (x) patch, dw = scale * S, and the scale's gradient is
 //                            sum over a channel's weights of w * S.  No y is kept, written or read there.
-// All but the lowest unit's first dz form in the epilogue of the input-gradient product above, where the shortcut's gradient joins too.
+// All but the top block's and the stem's first dz form in the epilogue of the input-gradient product above, where the shortcut's gradient joins too.
 #include <algorithm>
 #include <cmath>
 
